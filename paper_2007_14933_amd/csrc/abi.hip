@@ -775,7 +775,7 @@ int osbli_mlp_grad(const float *X, const uint8_t *y, int64_t n, const uint16_t *
                    float *loss, void *workspace, size_t ws_bytes, void *stream) {
     if (!X || !y || !w || !grad || !workspace || n <= 0) return OSBLI_EINVAL;
     if (ws_bytes < mlp_workspace_bytes(n)) return OSBLI_ENOSPACE;
-    return launch_mlp_grad(X, y, n, w, w_neg, grad, loss, static_cast<float *>(workspace), as_stream(stream)) ==
+    return launch_mlp_grad(X, y, n, w, w_neg, grad, loss, workspace, as_stream(stream)) ==
                    hipSuccess
                ? OSBLI_OK
                : OSBLI_EDEVICE;

@@ -146,7 +146,7 @@ hipError_t launch_sensor(const Grid &g, const Phys &ph, const double *U, int d, 
 hipError_t launch_count_u8(const uint8_t *a, int64_t n, unsigned long long *out, hipStream_t s);
 size_t mlp_workspace_bytes(int64_t n);
 hipError_t launch_mlp_grad(const float *X, const uint8_t *y, int64_t n, const uint16_t *w, float wneg,
-                           float *grad, float *loss, float *partial, hipStream_t s);
+                           float *grad, float *loss, void *workspace, hipStream_t s);
 hipError_t launch_mlp_adam(float *master, uint16_t *w, const float *grad, float *m, float *v, int64_t t,
                            float lr, float b1, float b2, float eps, hipStream_t s);
 hipError_t launch_mlp_forward(const float *X, int64_t n, const uint16_t *w, float *z, int inference,

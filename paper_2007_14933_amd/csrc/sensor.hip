@@ -58,8 +58,6 @@ k_labels(const double *__restrict__ U, Grid g, Phys ph, float *__restrict__ feat
 }
 
 // ------------------------------------------------------ FP32 training pass
-constexpr int kMB = 64;  // samples per block (one wave)
-
 struct Fwd {
     float a1[kH], a2[kH], z;
 };
@@ -85,84 +83,141 @@ __device__ __forceinline__ void fwd_fp32(const float (&x)[kIn], const float *W, 
     o.z = z;
 }
 
-// per-block partial gradients of the mean class-weighted BCE
-__global__ void __launch_bounds__(kMB)
-k_mlp_grad(const float *__restrict__ X, const uint8_t *__restrict__ y, int64_t n, const uint16_t *__restrict__ w,
-           float wneg, float inv_n, float *__restrict__ partial) {
-    __shared__ float W[kNP];
-    __shared__ float sx[kMB][kIn], sh1[kMB][kH], sd1[kMB][kH], sh2[kMB][kH], sd2[kMB][kH], sdz[kMB], sl[kMB];
-    for (int e = threadIdx.x; e < kNP; e += kMB) W[e] = bf2f(w[e]);
-    __syncthreads();
-    const int tid = threadIdx.x;
-    const int64_t s = (int64_t)blockIdx.x * kMB + tid;
-    const bool valid = s < n;
-    float x[kIn];
-#pragma unroll
-    for (int k = 0; k < kIn; ++k) x[k] = valid ? X[s * kIn + k] : 0.0f;
-    Fwd o;
-    fwd_fp32(x, W, o);
-    const float yv = valid ? (float)y[s] : 0.0f;
-    const float wt = valid ? (yv > 0.5f ? 1.0f : wneg) : 0.0f;
-    // sigmoid and the loss term in FP64 (float expf would carry its own
-    // rounding into every gradient)
-    const double zd = o.z;
-    const double sig = 1.0 / (1.0 + exp(-zd));
-    const float dz = (float)(wt * (sig - yv) * inv_n);
-    const double sp = fmax(zd, 0.0) + log1p(exp(-fabs(zd)));
-    sl[tid] = (float)(wt * (sp - yv * zd) * inv_n);
-    sdz[tid] = dz;
-    float d2[kH];
-#pragma unroll
-    for (int j = 0; j < kH; ++j) {
-        d2[j] = o.a2[j] > 0.0f ? dz * W[oW3 + j] : 0.0f;
-        sd2[tid][j] = d2[j];
-        sh2[tid][j] = fmaxf(o.a2[j], 0.0f);
-        sh1[tid][j] = fmaxf(o.a1[j], 0.0f);
-    }
-#pragma unroll
-    for (int k = 0; k < kH; ++k) {
-        float acc = 0.0f;
-#pragma unroll
-        for (int j = 0; j < kH; ++j) acc += d2[j] * W[oW2 + k * kH + j];
-        sd1[tid][k] = o.a1[k] > 0.0f ? acc : 0.0f;
-    }
-#pragma unroll
-    for (int k = 0; k < kIn; ++k) sx[tid][k] = x[k];
-    __syncthreads();
-    float *out = partial + (int64_t)blockIdx.x * kNPad;
-    for (int e = tid; e < kNPad; e += kMB) {
-        double acc = 0.0;  // FP64 sums: FP32 sequential sums of same-sign terms drift
-        if (e < oB1) {
-            const int k = e / kH, j = e % kH;
-            for (int t = 0; t < kMB; ++t) acc += (double)sx[t][k] * sd1[t][j];
-        } else if (e < oW2) {
-            const int j = e - oB1;
-            for (int t = 0; t < kMB; ++t) acc += sd1[t][j];
-        } else if (e < oB2) {
-            const int k = (e - oW2) / kH, j = (e - oW2) % kH;
-            for (int t = 0; t < kMB; ++t) acc += (double)(sh1[t][k] * sd2[t][j]);
-        } else if (e < oW3) {
-            const int j = e - oB2;
-            for (int t = 0; t < kMB; ++t) acc += sd2[t][j];
-        } else if (e < oB3) {
-            const int j = e - oW3;
-            for (int t = 0; t < kMB; ++t) acc += (double)(sh2[t][j] * sdz[t]);
-        } else if (e == oB3) {
-            for (int t = 0; t < kMB; ++t) acc += sdz[t];
-        } else {
-            for (int t = 0; t < kMB; ++t) acc += sl[t];
-        }
-        out[e] = (float)acc;
-    }
+// Gradient of the mean class-weighted BCE.  A training batch (512 samples) is
+// far too small to fill the chip, so the pass is a latency chain and the work
+// is spread as thin as the network allows: a block takes kMB = 16 samples with
+// 16 threads each, two hidden units of every layer per thread (one wave per 64
+// samples, each thread running a whole network, left 8 waves on the chip:
+// 111 us per call on a batch of 512 with its reduction, this form 10 us).  Blocks stride over the sample
+// tiles, at most kMaxBlk of them, so the partial records stay small.
+// A sample's forward and backward values are one record in LDS; every entry
+// of the gradient is the sum over the samples of a product of two record
+// entries (biases and loss: with the constant 1), FP64 products and sums.
+constexpr int kMB = 16;
+constexpr int kMaxBlk = 1024;
+constexpr int kW2S = kH + 1;  // LDS row stride of W2: rows and columns are read without bank conflicts
+// record offsets: x, relu(a1), d1, relu(a2), d2, dz, loss term, 1
+constexpr int rX = 0, rH1 = rX + kIn, rD1 = rH1 + kH, rH2 = rD1 + kH, rD2 = rH2 + kH, rDz = rD2 + kH, rL = rDz + 1,
+              rOne = rL + 1, kRec = rOne + 1;
+static_assert(kRec % 2 == 1, "odd record stride: the samples of a wave start in different banks");
+constexpr int kPerThread = (kNPad + 255) / 256;
+
+// the two record entries whose product, summed over the samples, is entry e of the gradient
+__device__ __forceinline__ void grad_entry(int e, int &a, int &b) {
+    if (e < oB1) a = rX + e / kH, b = rD1 + e % kH;
+    else if (e < oW2) a = rOne, b = rD1 + e - oB1;
+    else if (e < oB2) a = rH1 + (e - oW2) / kH, b = rD2 + (e - oW2) % kH;
+    else if (e < oW3) a = rOne, b = rD2 + e - oB2;
+    else if (e < oB3) a = rDz, b = rH2 + e - oW3;
+    else a = rOne, b = e == oB3 ? rDz : rL;
 }
 
-// fixed-order sum of the block partials -> gradient (1441) and loss
-__global__ void k_mlp_reduce(const float *__restrict__ partial, int64_t nblk, float *__restrict__ grad,
-                             float *__restrict__ loss) {
-    const int e = blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= kNPad) return;
+__global__ void __launch_bounds__(256)
+k_mlp_grad(const float *__restrict__ X, const uint8_t *__restrict__ y, int64_t n, const uint16_t *__restrict__ w,
+           float wneg, float inv_n, double *__restrict__ partial) {
+    __shared__ float W1[kIn * kH], W2[kH * kW2S], B1[kH], B2[kH], W3[kH];
+    __shared__ float rec[kMB][kRec];
+    const int tid = threadIdx.x;
+    for (int e = tid; e < kIn * kH; e += 256) W1[e] = bf2f(w[oW1 + e]);
+    for (int e = tid; e < kH * kH; e += 256) W2[(e / kH) * kW2S + e % kH] = bf2f(w[oW2 + e]);
+    if (tid < kH) {
+        B1[tid] = bf2f(w[oB1 + tid]);
+        B2[tid] = bf2f(w[oB2 + tid]);
+        W3[tid] = bf2f(w[oW3 + tid]);
+    }
+    const float b3 = bf2f(w[oB3]);
+    int ea[kPerThread], eb[kPerThread];
+    double acc[kPerThread];
+#pragma unroll
+    for (int i = 0; i < kPerThread; ++i) {
+        const int e = tid + 256 * i;
+        grad_entry(e < kNPad ? e : kNPad - 1, ea[i], eb[i]);
+        acc[i] = 0.0;
+    }
+    __syncthreads();
+    // sample sl of the tile, hidden units u and u + 16; a sample's sixteen
+    // threads lie in one wave
+    const int sl = tid >> 4, u = tid & 15;
+    float *const r = rec[sl];
+    for (int64_t s0 = (int64_t)blockIdx.x * kMB; s0 < n; s0 += (int64_t)gridDim.x * kMB) {
+        const int64_t s = s0 + sl;
+        const bool valid = s < n;
+        if (u < kIn) r[rX + u] = valid ? X[s * kIn + u] : 0.0f;
+        if (u == 15) r[rOne] = 1.0f;
+        const float yv = valid ? (float)y[s] : 0.0f;
+        wave_sync();
+        float a1[2], a2[2], d2[2], g1[2];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            a1[h] = B1[u + 16 * h];
+#pragma unroll
+            for (int k = 0; k < kIn; ++k) a1[h] = fmaf(r[rX + k], W1[k * kH + u + 16 * h], a1[h]);
+            r[rH1 + u + 16 * h] = fmaxf(a1[h], 0.0f);
+        }
+        wave_sync();
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            a2[h] = B2[u + 16 * h];
+#pragma unroll
+            for (int k = 0; k < kH; ++k) a2[h] = fmaf(r[rH1 + k], W2[k * kW2S + u + 16 * h], a2[h]);
+        }
+        float z = fmaxf(a2[0], 0.0f) * W3[u] + fmaxf(a2[1], 0.0f) * W3[u + 16];
+#pragma unroll
+        for (int off = 1; off < 16; off <<= 1) z += __shfl_xor(z, off, 64);
+        z += b3;
+        const float wt = valid ? (yv > 0.5f ? 1.0f : wneg) : 0.0f;
+        // sigmoid and the loss term in FP64 (float expf would carry its own
+        // rounding into every gradient)
+        const double zd = z, ex = exp(-fabs(zd));
+        const double sig = (zd >= 0.0 ? 1.0 : ex) / (1.0 + ex);
+        const float dz = (float)(wt * (sig - yv) * inv_n);
+        if (u == 0) {
+            r[rDz] = dz;
+            r[rL] = (float)(wt * ((fmax(zd, 0.0) + log1p(ex)) - yv * zd) * inv_n);
+        }
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            d2[h] = a2[h] > 0.0f ? dz * W3[u + 16 * h] : 0.0f;
+            r[rD2 + u + 16 * h] = d2[h];
+            r[rH2 + u + 16 * h] = fmaxf(a2[h], 0.0f);
+        }
+        wave_sync();
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            g1[h] = 0.0f;
+#pragma unroll
+            for (int j = 0; j < kH; ++j) g1[h] = fmaf(r[rD2 + j], W2[(u + 16 * h) * kW2S + j], g1[h]);
+            r[rD1 + u + 16 * h] = a1[h] > 0.0f ? g1[h] : 0.0f;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int t = 0; t < kMB; ++t)
+#pragma unroll
+            for (int i = 0; i < kPerThread; ++i) acc[i] = fma((double)rec[t][ea[i]], (double)rec[t][eb[i]], acc[i]);
+        __syncthreads();
+    }
+    double *out = partial + (int64_t)blockIdx.x * kNPad;
+#pragma unroll
+    for (int i = 0; i < kPerThread; ++i)
+        if (tid + 256 * i < kNPad) out[tid + 256 * i] = acc[i];
+}
+
+// fixed-order sum of the block partials -> gradient (1441) and loss: 32
+// entries per block, eight threads each over every eighth partial
+__global__ void __launch_bounds__(256)
+k_mlp_reduce(const double *__restrict__ partial, int nblk, float *__restrict__ grad, float *__restrict__ loss) {
+    __shared__ double part[8][32];
+    const int el = threadIdx.x & 31, q = threadIdx.x >> 5;
+    const int e = blockIdx.x * 32 + el;
     double acc = 0.0;
-    for (int64_t b = 0; b < nblk; ++b) acc += partial[b * kNPad + e];
+    if (e < kNPad)
+#pragma unroll 4
+        for (int b = q; b < nblk; b += 8) acc += partial[(int64_t)b * kNPad + e];
+    part[q][el] = acc;
+    __syncthreads();
+    if (q != 0 || e >= kNPad) return;
+#pragma unroll
+    for (int k = 1; k < 8; ++k) acc += part[k][el];
     if (e < kNP) grad[e] = (float)acc;
     else if (loss) *loss = (float)acc;
 }
@@ -345,17 +400,20 @@ hipError_t launch_sensor(const Grid &g, const Phys &ph, const double *U, int d, 
     }
 }
 
-size_t mlp_workspace_bytes(int64_t n) {
-    const int64_t nblk = (n + kMB - 1) / kMB;
-    return (size_t)nblk * kNPad * sizeof(float);
+static int64_t mlp_blocks(int64_t n) {
+    const int64_t tiles = (n + kMB - 1) / kMB;
+    return tiles < kMaxBlk ? tiles : kMaxBlk;
 }
 
+// (eight bytes more than the records: the caller's buffer may be aligned to four)
+size_t mlp_workspace_bytes(int64_t n) { return (size_t)mlp_blocks(n) * kNPad * sizeof(double) + sizeof(double); }
+
 hipError_t launch_mlp_grad(const float *X, const uint8_t *y, int64_t n, const uint16_t *w, float wneg, float *grad,
-                           float *loss, float *partial, hipStream_t s) {
-    const int64_t nblk = (n + kMB - 1) / kMB;
-    hipLaunchKernelGGL(k_mlp_grad, dim3((unsigned)nblk), dim3(kMB), 0, s, X, y, n, w, wneg, 1.0f / (float)n,
-                       partial);
-    hipLaunchKernelGGL(k_mlp_reduce, dim3((kNPad + 255) / 256), dim3(256), 0, s, partial, nblk, grad, loss);
+                           float *loss, void *workspace, hipStream_t s) {
+    const int64_t nblk = mlp_blocks(n);
+    double *partial = reinterpret_cast<double *>((reinterpret_cast<uintptr_t>(workspace) + 7) & ~uintptr_t(7));
+    hipLaunchKernelGGL(k_mlp_grad, dim3((unsigned)nblk), dim3(256), 0, s, X, y, n, w, wneg, 1.0f / (float)n, partial);
+    hipLaunchKernelGGL(k_mlp_reduce, dim3((kNPad + 31) / 32), dim3(256), 0, s, partial, (int)nblk, grad, loss);
     return hipGetLastError();
 }
 
