@@ -179,13 +179,35 @@ k_visc_flux(const double *__restrict__ U, double *__restrict__ G, Grid g, Phys p
     visc_store<ND, GEN>(phi0, Dk, G, g, ph, m, idx, ci, e0);
 }
 
+// Planes per block of the z-marching passes: a block of `c` + planes steps (the
+// c steps fill its register window) runs on one of `slots` places, so the run
+// takes ceil(blocks / slots) (planes + c) steps; the shortest such run of at
+// most `most` planes is taken.  Fixed runs of 32 (fluxes) and 16 planes (finish)
+// gave a 64^3 grid 16 and 64 blocks, 70 and 40 us; runs of two planes fill the
+// chip.  Large grids keep the longest runs (8 to 64 planes measured alike).
+inline int plane_run(int64_t tiles, int64_t Nz, int most, int slots) {
+    constexpr int c = 3;
+    int best = most;
+    int64_t cost = INT64_MAX;
+    for (int p = most; p >= 2; --p) {
+        const int64_t blocks = tiles * ((Nz + p - 1) / p);
+        const int64_t t = (blocks + slots - 1) / slots * (p + c);
+        if (t < cost) {
+            cost = t;
+            best = p;
+        }
+    }
+    return best;
+}
+
 // 3D separable meshes: a block owns a kZX x kZY tile of (x, y) columns and
-// marches kZC planes along z.  The primitives of the current plane (tile plus
+// marches zrun planes along z.  The primitives of the current plane (tile plus
 // a two-node halo, read from U including ghost copies) sit in LDS for the x
 // and y derivatives; each column keeps its own z-2 .. z+2 primitives in
 // registers.  Nodes within two of a non-periodic end take that direction's
 // closure from global loads.  The arithmetic per node is that of k_visc_flux.
-constexpr int kZX = 64, kZY = 8, kZC = 32;
+constexpr int kZX = 64, kZY = 8, kZC = 32;  // kZC: the longest run of planes
+constexpr int kZSlots = 256;                // one block per CU
 constexpr int kHX = kZX + 4, kHY = kZY + 4;
 
 // the tile's halo: two rows above and below the tile (kHX wide) and two
@@ -229,7 +251,7 @@ __device__ __forceinline__ void phi_of(const double (&u)[5], const Phys &ph, dou
 // flight spilled.
 __global__ void __launch_bounds__(kZX * kZY, 2)
 k_visc_flux_zm(const double *__restrict__ U, double *__restrict__ G, Grid g, Phys ph, Metrics m, int tx_n,
-               int ty_n, int ntiles, int per) {
+               int ty_n, int ntiles, int per, int zrun) {
     constexpr int NV = 4;
     __shared__ double tile[2][NV][kHY][kHX];
     const int L = (int)(blockIdx.x % kXcds) * per + (int)(blockIdx.x / kXcds);
@@ -239,8 +261,8 @@ k_visc_flux_zm(const double *__restrict__ U, double *__restrict__ G, Grid g, Phy
     const int64_t x0 = (int64_t)bx * kZX, y0 = (int64_t)by * kZY;
     const int64_t x = x0 + tx, y = y0 + ty;
     const int64_t Nx = g.n[0], Ny = g.n[1], Nz = g.n[2];
-    const int64_t z0 = (int64_t)bz * kZC;
-    const int64_t z1 = z0 + kZC < Nz ? z0 + kZC : Nz;
+    const int64_t z0 = (int64_t)bz * zrun;
+    const int64_t z1 = z0 + zrun < Nz ? z0 + zrun : Nz;
     const bool own = x < Nx && y < Ny;
     const int64_t cs = g.enpts, sz = g.es[2];
     const bool perx = g.periodic[0] != 0, pery = g.periodic[1] != 0, perz = g.periodic[2] != 0;
@@ -379,7 +401,7 @@ k_finish(const double *Racc, const double *__restrict__ G, double *Rout, Grid g,
 }
 
 // The same finish for 3D separable meshes, RK update only, marching along z:
-// a block owns a kBX x kBY tile of columns and kFZ planes; each thread keeps
+// a block owns a kFX x kFY tile of columns and zrun planes; each thread keeps
 // its column's G_z at z-2 .. z+2 in registers, so G_z is read once per node
 // instead of once per stencil use (the z neighbours' fluxes are otherwise
 // re-read from HBM: the plane-by-plane working set overflows the L2).  The
@@ -387,12 +409,13 @@ k_finish(const double *Racc, const double *__restrict__ G, double *Rout, Grid g,
 // the node's residual, register and state together.  Nodes
 // within two of a non-periodic end take that direction's closure from direct
 // loads; the arithmetic per node is that of k_finish.
-constexpr int kFZ = 16;
+constexpr int kFZ = 16;           // the longest run of planes
+constexpr int kFSlots = 512;      // two blocks per CU (238 registers)
 constexpr int kFX = 64, kFY = 4;  // columns per block
 
 __global__ void __launch_bounds__(kFX * kFY)
 k_finish_zm(const double *__restrict__ Racc, const double *__restrict__ G, Grid g, Metrics m, RkStage rs, double dt,
-            double *__restrict__ U, double *__restrict__ dU, int ntx, int nty, int stripe) {
+            double *__restrict__ U, double *__restrict__ dU, int ntx, int nty, int stripe, int zrun) {
     constexpr int NC = 5, NV = 4;
     // XCD k (blocks b with b % 8 == k) owns the stripe of y tiles
     // [k stripe, (k + 1) stripe); within it x tiles run fastest, then y, then
@@ -405,8 +428,8 @@ k_finish_zm(const double *__restrict__ Racc, const double *__restrict__ G, Grid 
     const int64_t y = (int64_t)byt * kFY + threadIdx.y;
     const int64_t Nx = g.n[0], Ny = g.n[1], Nz = g.n[2];
     if (x >= Nx || y >= Ny) return;  // no block-wide synchronisation below
-    const int64_t z0 = (int64_t)bzt * kFZ;
-    const int64_t z1 = z0 + kFZ < Nz ? z0 + kFZ : Nz;
+    const int64_t z0 = (int64_t)bzt * zrun;
+    const int64_t z1 = z0 + zrun < Nz ? z0 + zrun : Nz;
     const bool perx = g.periodic[0] != 0, pery = g.periodic[1] != 0, perz = g.periodic[2] != 0;
     const bool intx = perx || (x >= 2 && x <= Nx - 3);
     const bool inty = pery || (y >= 2 && y <= Ny - 3);
@@ -566,10 +589,11 @@ hipError_t finish_nd(const Grid &g, const Phys &ph, const Metrics &m, const doub
     const dim3 nb = node_grid(g), bs(kBX, kBY);
     if (ND == 3 && !GEN && ph.viscous && mode == 1) {
         const int ntx = (int)((g.n[0] + kFX - 1) / kFX), nty = (int)((g.n[1] + kFY - 1) / kFY);
-        const int ntz = (int)((g.n[2] + kFZ - 1) / kFZ), stripe = (nty + kXcds - 1) / kXcds;
+        const int zrun = plane_run((int64_t)ntx * nty, g.n[2], kFZ, kFSlots);
+        const int ntz = (int)((g.n[2] + zrun - 1) / zrun), stripe = (nty + kXcds - 1) / kXcds;
         const unsigned nblk = (unsigned)kXcds * (unsigned)(ntx * stripe * ntz);
         hipLaunchKernelGGL(k_finish_zm, dim3(nblk), dim3(kFX, kFY), 0, s, Racc, G, g, m, rs, dt, U, dU, ntx, nty,
-                           stripe);
+                           stripe, zrun);
         return hipGetLastError();
     }
     if (ph.viscous) {
@@ -608,10 +632,11 @@ hipError_t launch_viscous_fluxes(const Grid &g, const Phys &ph, const Metrics &m
                 hipLaunchKernelGGL((k_visc_flux<3, true>), nb, bs, 0, s, U, G, g, ph, m, T);
             } else {
                 const int tx_n = (int)((g.n[0] + kZX - 1) / kZX), ty_n = (int)((g.n[1] + kZY - 1) / kZY);
-                const int ntiles = tx_n * ty_n * (int)((g.n[2] + kZC - 1) / kZC);
+                const int zrun = plane_run((int64_t)tx_n * ty_n, g.n[2], kZC, kZSlots);
+                const int ntiles = tx_n * ty_n * (int)((g.n[2] + zrun - 1) / zrun);
                 const int per = (ntiles + kXcds - 1) / kXcds;
                 hipLaunchKernelGGL(k_visc_flux_zm, dim3((unsigned)(per * kXcds)), dim3(kZX, kZY), 0, s, U, G, g, ph,
-                                   m, tx_n, ty_n, ntiles, per);
+                                   m, tx_n, ty_n, ntiles, per, zrun);
             }
     }
     return hipGetLastError();

@@ -28,3 +28,22 @@ def test_mlp_gradient_sample_counts(n):
     Lo = mlp.loss(theta, X.astype(np.float64), y)
     assert np.abs(g.cpu().numpy() - go).max() <= 1e-5 * np.abs(go).max()
     assert abs(float(L.item()) - Lo) <= 1e-6 * abs(Lo)
+
+
+@pytest.mark.parametrize("ends", ["periodic", "open"])
+@pytest.mark.parametrize("n", [(65, 9, 7), (63, 8, 34), (257, 66, 41)])
+def test_viscous_plane_runs(n, ends):
+    """Runs of planes of the z-marching viscous passes: the shortest (two),
+    remainders, longer runs on grids of many columns; periodic and one-sided
+    ends.  Three steps against the oracle at the run bound 1e-11."""
+    from paper_2007_14933_amd import inputs as I
+    from parity_util import gpu_run, normwise_rel, oracle_run
+    say("[gpu shapes] plane runs", n, ends)
+    prob = I.smooth_random(3, n, seed=11, amp=0.05, Re=300.0, M=0.5)
+    if ends == "open":
+        prob = prob.with_(bc=((I.EXTRAPOLATE,) * 2,) * 3)
+    Ug, tg, _ = gpu_run(prob, 3)
+    Uo, to = oracle_run(prob, 3)
+    err = normwise_rel(I.interior_view(3, Ug), I.interior_view(3, Uo))
+    say("   ", err)
+    assert abs(tg - to) <= 1e-12 * to and err.max() <= 1e-11
