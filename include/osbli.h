@@ -161,8 +161,9 @@ typedef struct osbli_ctx osbli_ctx;
 
 /* Bytes of device workspace osbli_init_grid needs for these parameters
  * (metrics, residual accumulator, viscous fluxes, reduction slots and the
- * coordinate staging used once at set-up).  Pure host function; returns 0
- * for invalid parameters. */
+ * coordinate staging used once at set-up, and the two state copies of
+ * osbli_rk_step's one-pass stage where it applies).  Pure host function;
+ * returns 0 for invalid parameters. */
 size_t osbli_workspace_bytes(const osbli_params *p);
 
 /* Validate parameters, create the context and compute the metrics and
@@ -196,6 +197,15 @@ int osbli_residual(osbli_ctx *ctx, const double *U, double *R, void *stream);
  * second-to-last stage's value after a whole step.  Does not apply boundary
  * conditions.  U (ghosted layout) and dU (interior layout) must not alias. */
 int osbli_rk_substep(osbli_ctx *ctx, int stage, double dt, double *U, double *dU, void *stream);
+
+/* One whole Runge-Kutta step: every stage in order, each followed by the
+ * boundary conditions (the state afterwards is that of osbli_rk_substep and
+ * osbli_apply_bc stage by stage, to rounding).  U's ghosts must be valid.
+ * Inviscid 1D and 2D problems on separable meshes with periodic or
+ * extrapolated ends (six-point schemes; FP64 or routed forms; at most 2^24
+ * nodes) take one launch per stage through two state copies in the workspace,
+ * every other problem the separate calls. */
+int osbli_rk_step(osbli_ctx *ctx, double dt, double *U, double *dU, void *stream);
 
 /* Number of substages per step of the context's Runge-Kutta scheme (3 or
  * 5), and its coefficients A[s], B[s] (host arrays of at least 5). */
@@ -336,11 +346,11 @@ int osbli_mlp_forward(const float *X, int64_t n, const uint16_t *w, float *z, in
  * own context (osbli_init_grid), state U and RK register dU; the batch
  * advances all of them by one RK3 step per osbli_batch_step with its own
  * CFL time step per problem (section 2.7 scheme, dt clipped so that problem
- * p ends exactly at t_end[p], after which it is skipped).  A step is three
- * launches of captured graphs, one per substage, each a fixed sequence of
- * persistent kernels whose workgroups walk a tile queue spanning every
- * problem; dt, t and the active flag live on the device, so no host logic
- * runs between substages.  A batched problem evolves bit for bit as the
+ * p ends exactly at t_end[p], after which it is skipped).  A step is one
+ * launch of a captured graph (a substage by itself one launch of its own), a
+ * fixed sequence of persistent kernels whose workgroups walk a tile queue
+ * spanning every problem; dt, t and the active flag live on the device, so no
+ * host logic runs between substages.  A batched problem evolves bit for bit as the
  * same problem advanced alone with osbli_compute_dt / osbli_rk_substep /
  * osbli_apply_bc and the same dt clipping.
  *
@@ -379,7 +389,7 @@ int osbli_batch_set_tiles(osbli_batch *batch, const int64_t *seg, void *stream);
  * not depend on it.  Drops any captured graphs. */
 int osbli_batch_set_grid(osbli_batch *batch, int sweep_blocks);
 
-/* Capture the three substage graphs on `stream` (must not be the NULL
+/* Capture the graphs of the three substages and of a whole step on `stream` (must not be the NULL
  * stream).  Graph instantiation is the runtime's only allocation. */
 int osbli_batch_capture(osbli_batch *batch, void *stream);
 
@@ -390,8 +400,10 @@ int osbli_batch_capture(osbli_batch *batch, void *stream);
  * Stages must be issued in order 0, 1, 2.  Asynchronous. */
 int osbli_batch_substep(osbli_batch *batch, int stage, void *stream);
 
-/* One RK3 step of every active problem: osbli_batch_substep for stages 0, 1
- * and 2.  Asynchronous. */
+/* One RK3 step of every active problem, bit for bit osbli_batch_substep for
+ * stages 0, 1 and 2; between its stages the state lives in the contexts'
+ * workspaces (the one-pass stage of osbli_rk_step) wherever single grids run
+ * that way.  Asynchronous. */
 int osbli_batch_step(osbli_batch *batch, void *stream);
 
 /* Per-problem time and active flag (host arrays of nprob, may be NULL) and
@@ -416,7 +428,8 @@ enum osbli_kernel_class {
     OSBLI_K_DT = 6,        /* time-step reduction */
     OSBLI_K_SENSOR = 7,    /* learned-sensor routing masks */
     OSBLI_K_CENTRAL = 8,   /* central path: derivative and residual passes */
-    OSBLI_K_COUNT = 9
+    OSBLI_K_STAGE = 9,     /* one-pass stage of osbli_rk_step: fluxes, update, BCs */
+    OSBLI_K_COUNT = 10
 };
 
 /* Instrumentation (not part of the method): when enabled, each launch group

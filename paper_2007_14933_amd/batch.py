@@ -2,8 +2,8 @@
 calls), with a tile autotuner.
 
 Every problem keeps its own context and state; one RK3 step of the whole
-ensemble is three launches of captured graphs (one per substage) of
-persistent kernels that walk a tile queue over all problems.  Each problem
+ensemble is one launch of a captured graph of persistent kernels that walk a
+tile queue over all problems.  Each problem
 has its own CFL time step and end time, kept on the device.
 
     b = Batch(problems, form=1, sensor=1, weights=bits, threshold=thr)
@@ -144,8 +144,7 @@ class Batch:
 
     def step(self, n=1):
         for _ in range(int(n)):
-            for st in range(3):
-                self.substep(st)
+            B.check_batch(self.lib.osbli_batch_step(self.b, self._s()), self.b)
         self.steps_done += int(n)
 
     def status(self):

@@ -55,6 +55,7 @@ _SIGS = {
     "osbli_residual": (C.c_int, [_VP, _VP, _VP, _VP]),
     "osbli_rk_substep": (C.c_int, [_VP, C.c_int, C.c_double, _VP, _VP, _VP]),
     "osbli_rk_substep_noalloc": (C.c_int, [_VP, C.c_int, C.c_double, _VP, _VP, _VP]),
+    "osbli_rk_step": (C.c_int, [_VP, C.c_double, _VP, _VP, _VP]),
     "osbli_noalloc_scratch_bytes": (C.c_size_t, []),
     "osbli_rk_stages": (C.c_int, [_VP]),
     "osbli_central_store_all_bytes": (C.c_size_t, [C.POINTER(Params)]),
@@ -91,8 +92,9 @@ _SIGS = {
     "osbli_batch_destroy": (None, [_VP]),
 }
 
-K_SWEEP_X, K_SWEEP_Y, K_SWEEP_Z, K_VISC_FLUX, K_FINISH, K_BC, K_DT, K_SENSOR, K_CENTRAL = range(9)
-K_NAMES = ["sweep_x", "sweep_y", "sweep_z", "visc_flux", "finish", "bc", "dt", "sensor", "central"]
+K_SWEEP_X, K_SWEEP_Y, K_SWEEP_Z, K_VISC_FLUX, K_FINISH, K_BC, K_DT, K_SENSOR, K_CENTRAL, K_STAGE = range(10)
+K_NAMES = ["sweep_x", "sweep_y", "sweep_z", "visc_flux", "finish", "bc", "dt", "sensor", "central",
+           "stage"]
 
 
 def load():

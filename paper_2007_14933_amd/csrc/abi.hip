@@ -82,6 +82,7 @@ struct osbli_ctx {
     int nstages;           // Runge-Kutta substages per step (3 or 5)
     double rkA[5], rkB[5]; // their 2N coefficients
     void *cwork;           // central path: the store-all strategy's work arrays (null: StoreSome)
+    double *W[2];          // state copies of the one-pass stage (null: separate passes)
     char err[320];
 };
 
@@ -228,6 +229,11 @@ Layout make_layout(const osbli_params *p, const Grid &g) {
     }
     L.wts = off;
     if (p->sensor) off += align256(2 * 1441);
+    // state copies of the one-pass stage
+    for (int k = 0; k < 2; ++k) {
+        L.W[k] = off;
+        if (stage_supported(g, *p)) off += align256(sizeof(double) * g.nc * g.enpts);
+    }
     L.total = off;
     return L;
 }
@@ -463,6 +469,8 @@ int osbli_init_grid(osbli_ctx **out, const osbli_params *p, const double *x, con
     c->G = reinterpret_cast<double *>(c->ws + c->L.G);
     for (int d = 0; d < 3; ++d) c->mask[d] = reinterpret_cast<uint8_t *>(c->ws + c->L.mask[d]);
     c->wts = reinterpret_cast<uint16_t *>(c->ws + c->L.wts);
+    for (int k = 0; k < 2; ++k)
+        c->W[k] = stage_supported(c->g, *p) ? reinterpret_cast<double *>(c->ws + c->L.W[k]) : nullptr;
     c->sensor_ready = 0;
     c->sensor_every = 0;
     c->zcut = 0.0f;
@@ -576,6 +584,32 @@ int osbli_rk_substep(osbli_ctx *c, int stage, double dt, double *U, double *dU, 
     {
         Timed t(c, OSBLI_K_FINISH, s);
         HIP_TRY(c, launch_finish(c->g, c->ph, c->m, c->Racc, c->G, nullptr, stage_of(c, stage), dt, U, dU, 1, s));
+    }
+    return OSBLI_OK;
+}
+
+int osbli_rk_step(osbli_ctx *c, double dt, double *U, double *dU, void *stream) {
+    if (!c || !U || !dU) return set_err(c, OSBLI_EINVAL, "null argument");
+    if ((void *)U == (void *)dU) return set_err(c, OSBLI_EINVAL, "dU aliases U");
+    const bool route = c->p.sensor && c->sensor_ready;
+    if (!c->W[0] || (c->ph.mixed && !route)) {
+        for (int st = 0; st < c->nstages; ++st) {
+            int rc = osbli_rk_substep(c, st, dt, U, dU, stream);
+            if (rc == OSBLI_OK) rc = osbli_apply_bc(c, U, stream);
+            if (rc != OSBLI_OK) return rc;
+        }
+        return OSBLI_OK;
+    }
+    // one pass per stage: U -> W0 -> W1 -> .. -> U, each with its ghosts
+    hipStream_t s = as_stream(stream);
+    c->last = s;
+    const double *in = U;
+    for (int st = 0; st < c->nstages; ++st) {
+        double *out = st == c->nstages - 1 ? U : c->W[st & 1];
+        if (route && (st == 0 || c->sensor_every)) HIP_TRY(c, sensor_all(c, in, s));
+        Timed t(c, OSBLI_K_STAGE, s);
+        HIP_TRY(c, launch_stage(c->g, c->ph, c->m, c->p, in, out, dU, c->mask, route, stage_of(c, st), dt, c->flags, s));
+        in = out;
     }
     return OSBLI_OK;
 }
@@ -841,9 +875,10 @@ struct osbli_batch {
     BState *ds;
     int64_t *dtab;
     BatchTables T;
-    hipGraph_t graph[3];
-    hipGraphExec_t exec[3];
+    hipGraph_t graph[4];   // one per substage, and the whole step
+    hipGraphExec_t exec[4];
     int captured;
+    int one_pass;          // steps run one pass per stage
     int sweep_blocks;      // workgroups per persistent sweep launch (0: defaults)
     char err[320];
 };
@@ -867,7 +902,7 @@ int bset_err(osbli_batch *b, int code, const char *fmt, ...) {
             return bset_err((b), OSBLI_EDEVICE, "%s: %s", #call, hipGetErrorString(e__));              \
     } while (0)
 
-constexpr int kTables = 8;
+constexpr int kTables = 9;
 size_t batch_table_bytes(int P) { return align256(sizeof(int64_t) * kTables * (size_t)(P + 1)); }
 
 // default segment length of a sweep (the single-grid rule)
@@ -881,7 +916,7 @@ int upload_tables(osbli_batch *b, hipStream_t s) {
     const int P = b->P;
     std::vector<int64_t> h(kTables * (size_t)(P + 1), 0);
     int64_t *W0 = &h[0], *W1 = &h[(P + 1)], *PT = &h[2 * (P + 1)], *F0 = &h[3 * (P + 1)], *F1 = &h[4 * (P + 1)],
-            *S0 = &h[5 * (P + 1)], *S1 = &h[6 * (P + 1)], *WX = &h[7 * (P + 1)];
+            *S0 = &h[5 * (P + 1)], *S1 = &h[6 * (P + 1)], *WX = &h[7 * (P + 1)], *ST = &h[8 * (P + 1)];
     for (int p = 0; p < P; ++p) {
         BProb &q = b->hp[p];
         for (int d = 0; d < 2; ++d) {
@@ -895,6 +930,7 @@ int upload_tables(osbli_batch *b, hipStream_t s) {
         const int64_t nw0 = q.xl ? 0 : q.nseg[0] * q.wpl[0];
         const int64_t nw1 = q.nseg[1] * q.wpl[1];
         WX[p + 1] = WX[p] + nwx;
+        ST[p + 1] = ST[p] + (int64_t)q.ntx * ((q.g.n[1] + q.ty - 1) / q.ty);
         W0[p + 1] = W0[p] + nw0;
         W1[p + 1] = W1[p] + nw1;
         PT[p + 1] = PT[p] + (q.g.nint + 255) / 256;
@@ -915,6 +951,8 @@ int upload_tables(osbli_batch *b, hipStream_t s) {
     T.s[0] = b->dtab + 5 * (P + 1);
     T.s[1] = b->dtab + 6 * (P + 1);
     T.wx = b->dtab + 7 * (P + 1);
+    T.st = b->dtab + 8 * (P + 1);
+    T.tot_st = ST[P];
     T.tot_wx = WX[P];
     T.tot_w[0] = W0[P];
     T.tot_w[1] = W1[P];
@@ -928,7 +966,7 @@ int upload_tables(osbli_batch *b, hipStream_t s) {
 
 void drop_graphs(osbli_batch *b) {
     if (!b->captured) return;
-    for (int s = 0; s < 3; ++s) {
+    for (int s = 0; s < 4; ++s) {
         hipGraphExecDestroy(b->exec[s]);
         hipGraphDestroy(b->graph[s]);
     }
@@ -994,6 +1032,7 @@ int osbli_batch_create(osbli_batch **out, osbli_ctx *const *ctxs, int P, double 
     b->dtab = reinterpret_cast<int64_t *>(ws + align256(sizeof(BProb) * P) + align256(sizeof(BState) * P));
     b->hp.resize(P);
     b->hs.resize(P);
+    b->one_pass = 1;
     for (int p = 0; p < P; ++p) {
         const osbli_ctx *c = ctxs[p];
         BProb &q = b->hp[p];
@@ -1003,6 +1042,8 @@ int osbli_batch_create(osbli_batch **out, osbli_ctx *const *ctxs, int P, double 
         q.R = c->Racc;
         q.xl = c->g.n[0] + 1 >= 64 ? 1 : 0;
         q.xlpt = kXlPerTile;
+        for (int k = 0; k < 2; ++k) q.W[k] = c->W[k];
+        b->one_pass = b->one_pass && c->W[0] && !(c->ph.mixed && !b->route);
         for (int d = 0; d < 3; ++d) {
             q.invh[d] = c->m.invh[d];
             q.mask[d] = c->mask[d];
@@ -1019,6 +1060,7 @@ int osbli_batch_create(osbli_batch **out, osbli_ctx *const *ctxs, int P, double 
         st.active = 1;
         st.pad = 0;
     }
+    batch_stage_tiles(b->hp.data(), P);
     hipStream_t s = as_stream(stream);
     HIP_BTRY(b, hipMemcpyAsync(b->ds, b->hs.data(), sizeof(BState) * P, hipMemcpyHostToDevice, s));
     return upload_tables(b, s);
@@ -1049,15 +1091,30 @@ int osbli_batch_set_grid(osbli_batch *b, int sweep_blocks) {
     return OSBLI_OK;
 }
 
+static hipError_t batch_launch(osbli_batch *b, int which, hipStream_t s) {
+    if (which < 3 || !b->one_pass) {
+        hipError_t e = hipSuccess;
+        const int s0 = which < 3 ? which : 0, s1 = which < 3 ? which : 2;
+        for (int st = s0; st <= s1 && e == hipSuccess; ++st)
+            e = launch_batch_stage(b->dp, b->ds, b->T, b->P, b->ph, st, b->cfl, b->route, b->w, b->zcut, b->flags,
+                                   b->sweep_blocks, s);
+        return e;
+    }
+    hipError_t e = hipSuccess;
+    for (int st = 0; st < 3 && e == hipSuccess; ++st)
+        e = launch_batch_one_pass(b->dp, b->ds, b->T, b->P, b->ph, st, b->cfl, b->route, b->w, b->zcut, b->flags,
+                                  b->sweep_blocks, s);
+    return e;
+}
+
 int osbli_batch_capture(osbli_batch *b, void *stream) {
     if (!b) return OSBLI_EINVAL;
     hipStream_t s = as_stream(stream);
     if (!s) return bset_err(b, OSBLI_EINVAL, "capture needs a non-default stream");
     drop_graphs(b);
-    for (int st = 0; st < 3; ++st) {
+    for (int st = 0; st < 4; ++st) {
         HIP_BTRY(b, hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal));
-        hipError_t e = launch_batch_stage(b->dp, b->ds, b->T, b->P, b->ph, st, b->cfl, b->route, b->w, b->zcut,
-                                          b->flags, b->sweep_blocks, s);
+        hipError_t e = batch_launch(b, st, s);
         hipGraph_t g = nullptr;
         hipError_t e2 = hipStreamEndCapture(s, &g);
         if (e != hipSuccess || e2 != hipSuccess) {
@@ -1080,21 +1137,14 @@ int osbli_batch_substep(osbli_batch *b, int stage, void *stream) {
     if (!b) return OSBLI_EINVAL;
     if (stage < 0 || stage > 2) return bset_err(b, OSBLI_EINVAL, "stage must be 0..2");
     hipStream_t s = as_stream(stream);
-    if (b->captured) {
-        HIP_BTRY(b, hipGraphLaunch(b->exec[stage], s));
-    } else {
-        HIP_BTRY(b, launch_batch_stage(b->dp, b->ds, b->T, b->P, b->ph, stage, b->cfl, b->route, b->w, b->zcut,
-                                       b->flags, b->sweep_blocks, s));
-    }
+    HIP_BTRY(b, b->captured ? hipGraphLaunch(b->exec[stage], s) : batch_launch(b, stage, s));
     return OSBLI_OK;
 }
 
 int osbli_batch_step(osbli_batch *b, void *stream) {
     if (!b) return OSBLI_EINVAL;
-    for (int st = 0; st < 3; ++st) {
-        const int rc = osbli_batch_substep(b, st, stream);
-        if (rc != OSBLI_OK) return rc;
-    }
+    hipStream_t s = as_stream(stream);
+    HIP_BTRY(b, b->captured ? hipGraphLaunch(b->exec[3], s) : batch_launch(b, 3, s));
     return OSBLI_OK;
 }
 

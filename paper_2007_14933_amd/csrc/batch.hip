@@ -14,7 +14,7 @@
 #include "bc.hpp"
 #include "point.hpp"
 #include "sensor.hpp"
-#include "sweep.hpp"
+#include "stage.hpp"
 
 namespace osbli {
 
@@ -215,6 +215,38 @@ k_b_sensor(const BProb *__restrict__ pr, const BState *__restrict__ st, const in
     }
 }
 
+// one Runge-Kutta stage in one pass (stage.hpp); in, out: state copy read and
+// written (0, 1: W; 2: U)
+template <int SCHEME, bool MIX, bool ROUTE>
+__global__ void __launch_bounds__(256, kStageSlots)
+k_b_stage(const BProb *__restrict__ pr, const BState *__restrict__ st, const int64_t *__restrict__ off, int P,
+          int64_t total, Phys ph, RkStage rs, int in, int out, unsigned *flags) {
+    __shared__ StageLds<2> sm;
+    // a block's tiles ascend, so its problem index only moves forward
+    int p = find_prob(off, P, blockIdx.x < total ? blockIdx.x : 0);
+    for (int64_t tile = blockIdx.x; tile < total; tile += gridDim.x) {
+        while (off[p + 1] <= tile) ++p;  // block-uniform; off[P] = total
+        if (!st[p].active) continue;
+        const BProb &b = pr[p];
+        const int local = (int)(tile - off[p]), by = local / b.ntx, bx = local - by * b.ntx;
+        const int64_t x0 = (int64_t)bx * b.tx, y0 = (int64_t)by * b.ty;
+        const int nx = (int)(b.g.n[0] - x0 < b.tx ? b.g.n[0] - x0 : b.tx);
+        const int ny = (int)(b.g.n[1] - y0 < b.ty ? b.g.n[1] - y0 : b.ty);
+        const double *src = in == 2 ? b.U : b.W[in];
+        double *dst = out == 2 ? b.U : b.W[out];
+        const uint8_t *const mask[3] = {b.mask[0], b.mask[1], b.mask[2]};
+        const Metrics m = sep_metrics(b);
+        // as the single-grid launch
+        if (b.g.n[0] + 1 < 64)
+            stage_tile<2, SCHEME, MIX, ROUTE, true>(src, dst, b.dU, b.g, ph, m.invh, mask, b.bc, rs, st[p].dt, x0, y0,
+                                                    nx, ny, flags, sm);
+        else
+            stage_tile<2, SCHEME, MIX, ROUTE, false>(src, dst, b.dU, b.g, ph, m.invh, mask, b.bc, rs, st[p].dt, x0,
+                                                     y0, nx, ny, flags, sm);
+        __syncthreads();  // the next tile overwrites the points and fluxes
+    }
+}
+
 __global__ void k_b_tadvance(BState *st, int P) {
     const int p = blockIdx.x * blockDim.x + threadIdx.x;
     if (p >= P || !st[p].active) return;
@@ -246,20 +278,24 @@ static hipError_t b_sweeps(const BProb *pr, const BState *st, const BatchTables 
     return hipGetLastError();
 }
 
+// start of a step: each problem's dt, and the routing masks
+static void b_begin(const BProb *pr, BState *st, const BatchTables &T, int P, const Phys &ph, double cfl, int route,
+                    const uint16_t *w, float zcut, unsigned *flags, hipStream_t s) {
+    hipLaunchKernelGGL(k_b_dt_reset, dim3((P + 255) / 256), dim3(256), 0, s, st, P);
+    hipLaunchKernelGGL(k_b_dt, dim3(grid_of(T.tot_pt, 1, 2048)), dim3(256), 0, s, pr, st, T.pt, P, T.tot_pt, ph);
+    hipLaunchKernelGGL(k_b_dt_final, dim3((P + 255) / 256), dim3(256), 0, s, st, P, cfl, flags);
+    if (route) {
+        hipLaunchKernelGGL(k_b_sensor<0>, dim3(grid_of(T.tot_s[0], 1, 2048)), dim3(256), 0, s, pr, st, T.s[0], P,
+                           T.tot_s[0], ph, w, zcut);
+        hipLaunchKernelGGL(k_b_sensor<1>, dim3(grid_of(T.tot_s[1], 1, 2048)), dim3(256), 0, s, pr, st, T.s[1], P,
+                           T.tot_s[1], ph, w, zcut);
+    }
+}
+
 hipError_t launch_batch_stage(const BProb *pr, BState *st, const BatchTables &T, int P, const Phys &ph, int stage,
                               double cfl, int route, const uint16_t *w, float zcut, unsigned *flags, int sweep_blocks,
                               hipStream_t s) {
-    if (stage == 0) {
-        hipLaunchKernelGGL(k_b_dt_reset, dim3((P + 255) / 256), dim3(256), 0, s, st, P);
-        hipLaunchKernelGGL(k_b_dt, dim3(grid_of(T.tot_pt, 1, 2048)), dim3(256), 0, s, pr, st, T.pt, P, T.tot_pt, ph);
-        hipLaunchKernelGGL(k_b_dt_final, dim3((P + 255) / 256), dim3(256), 0, s, st, P, cfl, flags);
-        if (route) {
-            hipLaunchKernelGGL(k_b_sensor<0>, dim3(grid_of(T.tot_s[0], 1, 2048)), dim3(256), 0, s, pr, st, T.s[0], P,
-                               T.tot_s[0], ph, w, zcut);
-            hipLaunchKernelGGL(k_b_sensor<1>, dim3(grid_of(T.tot_s[1], 1, 2048)), dim3(256), 0, s, pr, st, T.s[1], P,
-                               T.tot_s[1], ph, w, zcut);
-        }
-    }
+    if (stage == 0) b_begin(pr, st, T, P, ph, cfl, route, w, zcut, flags, s);
     hipError_t e;
     const bool mix = ph.mixed != 0;
     if (ph.scheme == OSBLI_WENOZ5) {
@@ -278,6 +314,42 @@ hipError_t launch_batch_stage(const BProb *pr, BState *st, const BatchTables &T,
     for (int d = 0; d < 2; ++d)
         hipLaunchKernelGGL(k_b_bc, dim3(grid_of(T.tot_f[d], 256, 1024)), dim3(256), 0, s, pr, st, T.f[d], P,
                            T.tot_f[d], ph, d);
+    if (stage == 2) hipLaunchKernelGGL(k_b_tadvance, dim3((P + 255) / 256), dim3(256), 0, s, st, P);
+    return hipGetLastError();
+}
+
+void batch_stage_tiles(BProb *pr, int P) {
+    std::vector<const Grid *> g(P);
+    std::vector<StageTiles> t(P);
+    for (int p = 0; p < P; ++p) g[p] = &pr[p].g;
+    stage_tiles(g.data(), P, t.data());
+    for (int p = 0; p < P; ++p) {
+        pr[p].tx = t[p].tx;
+        pr[p].ty = t[p].ty;
+        pr[p].ntx = (int)t[p].nx;
+    }
+}
+
+hipError_t launch_batch_one_pass(const BProb *pr, BState *st, const BatchTables &T, int P, const Phys &ph, int stage,
+                                 double cfl, int route, const uint16_t *w, float zcut, unsigned *flags,
+                                 int sweep_blocks, hipStream_t s) {
+    if (stage == 0) b_begin(pr, st, T, P, ph, cfl, route, w, zcut, flags, s);
+    const unsigned cap = sweep_blocks > 0 ? (unsigned)sweep_blocks : 256u * kStageSlots;
+    const dim3 nb(grid_of(T.tot_st, 1, cap)), bs(256);
+    const int in = stage == 0 ? 2 : stage - 1, out = stage;  // U -> W0 -> W1 -> U
+    const RkStage rs = rk3_stage(stage);
+    if (ph.scheme == OSBLI_WENOZ5)
+        hipLaunchKernelGGL((k_b_stage<OSBLI_WENOZ5, false, false>), nb, bs, 0, s, pr, st, T.st, P, T.tot_st, ph, rs,
+                           in, out, flags);
+    else if (route && ph.mixed)
+        hipLaunchKernelGGL((k_b_stage<OSBLI_TENO5, true, true>), nb, bs, 0, s, pr, st, T.st, P, T.tot_st, ph, rs, in,
+                           out, flags);
+    else if (route)
+        hipLaunchKernelGGL((k_b_stage<OSBLI_TENO5, false, true>), nb, bs, 0, s, pr, st, T.st, P, T.tot_st, ph, rs, in,
+                           out, flags);
+    else
+        hipLaunchKernelGGL((k_b_stage<OSBLI_TENO5, false, false>), nb, bs, 0, s, pr, st, T.st, P, T.tot_st, ph, rs,
+                           in, out, flags);
     if (stage == 2) hipLaunchKernelGGL(k_b_tadvance, dim3((P + 255) / 256), dim3(256), 0, s, st, P);
     return hipGetLastError();
 }

@@ -48,7 +48,7 @@ struct Metrics {
 
 // Device workspace carve-up (byte offsets into the caller's buffer).
 struct Layout {
-    size_t flags, red, invh[3], S, J, Racc, G, stage, mask[3], wts, total;
+    size_t flags, red, invh[3], S, J, Racc, G, stage, mask[3], wts, W[2], total;
 };
 
 __host__ __device__ inline int64_t ext_index(const Grid &g, int64_t i, int64_t j, int64_t k) {
@@ -165,6 +165,15 @@ hipError_t launch_central(const Grid &g, const Phys &ph, const Metrics &m, const
                           double *R, hipStream_t s);
 hipError_t launch_dt(const Grid &g, const Phys &ph, const Metrics &m, const double *U,
                      unsigned long long *slot, hipStream_t s);
+// one Runge-Kutta stage of an inviscid 1D or 2D problem, Uin -> Uout (ghosts
+// included), dU updated in place (stage.hpp).  It needs two copies of the
+// state in the workspace, so grids beyond 2^24 nodes (1 GB of copies) keep
+// the separate passes.
+constexpr int64_t kStageMaxNodes = int64_t(1) << 24;
+bool stage_supported(const Grid &g, const osbli_params &p);
+hipError_t launch_stage(const Grid &g, const Phys &ph, const Metrics &m, const osbli_params &p, const double *Uin,
+                        double *Uout, double *dU, uint8_t *const mask[3], bool route, const RkStage &rs, double dt,
+                        unsigned *flags, hipStream_t s);
 hipError_t launch_fill_u64(unsigned long long *p, unsigned long long v, int n, hipStream_t s);
 
 // ---- batched advance of many 2D problems (batch.hip) ----
@@ -177,6 +186,8 @@ struct BProb {             // one problem, device resident
     int xl;                            // x sweep with lanes along x (rows of >= 64 interfaces)
     int xlpt;                          // 63-interface runs per tile of that sweep
     int64_t seg[3], nseg[3], wpl[3];   // sweep tiling per direction (marching sweeps)
+    double *W[2];                      // state copies of the one-pass stage
+    int tx, ty, ntx, pad;              // its tiles: nodes per tile, tiles per row
 };
 
 constexpr int kXlPerTile = 4;  // default 63-interface runs per tile of the batched x sweep
@@ -188,8 +199,8 @@ struct BState {            // per-problem time state, device resident
 };
 
 struct BatchTables {       // device prefix tables (P + 1 entries) and totals
-    int64_t *w[2], *wx, *pt, *f[2], *s[2];    // wx: x-lanes sweep waves, w[0]: marching x sweep waves
-    int64_t tot_w[2], tot_wx, tot_pt, tot_f[2], tot_s[2];
+    int64_t *w[2], *wx, *pt, *f[2], *s[2], *st;    // wx: x-lanes sweep waves, w[0]: marching x sweep waves, st: stage tiles
+    int64_t tot_w[2], tot_wx, tot_pt, tot_f[2], tot_s[2], tot_st;
 };
 
 // sweep_blocks > 0: workgroups of each persistent sweep launch (else 2048
@@ -197,5 +208,14 @@ struct BatchTables {       // device prefix tables (P + 1 entries) and totals
 hipError_t launch_batch_stage(const BProb *pr, BState *st, const BatchTables &T, int P, const Phys &ph, int stage,
                               double cfl, int route, const uint16_t *w, float zcut, unsigned *flags, int sweep_blocks,
                               hipStream_t s);
+
+// The same stage of osbli_batch_step in one pass per stage (stage.hpp):
+// stage 0 reads U, stages 0 and 1 write the state copies, stage 2 writes U.
+// Of the forms that single grids run through it.
+hipError_t launch_batch_one_pass(const BProb *pr, BState *st, const BatchTables &T, int P, const Phys &ph, int stage,
+                                 double cfl, int route, const uint16_t *w, float zcut, unsigned *flags,
+                                 int sweep_blocks, hipStream_t s);
+// tiling of the problems for it (host)
+void batch_stage_tiles(BProb *pr, int P);
 
 }  // namespace osbli

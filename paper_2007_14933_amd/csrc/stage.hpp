@@ -1,0 +1,283 @@
+// One Runge-Kutta stage of an inviscid 1D or 2D problem in one pass: the
+// convective fluxes of every direction, the 2N update and the boundary
+// conditions, from one copy of the state into another (shared by the
+// single-grid and the batched launches).
+//
+// A pass of its own per sweep, update and ghost direction costs a small grid
+// its launches (18 a step) and a large one its traffic (320 bytes per point
+// and stage in 2D, where 128 are needed); and the marching y sweep of a
+// 256 x 256 grid is 128 waves of nine serial fluxes.  Here a block owns a tile
+// of nodes, finishes its points once into LDS (three-node halo), evaluates
+// the interfaces of x and then of y one per lane, and takes each node's flux
+// differences, its update and its ghost copies from LDS.  A block reads nodes
+// that its neighbours own, so the new state goes to another buffer.
+//
+// Tiles of at most 32 x 11 nodes: 33 x 11 = 363 interfaces along x and 32 x 12
+// = 384 along y are six wave tasks each (1.09 times the interfaces of a whole
+// grid); 49 KB of LDS and 168 registers, so three blocks per CU.
+// Bound: FP64 VALU, as the sweeps.
+#pragma once
+
+#include "sweep.hpp"
+
+namespace osbli {
+namespace cf {
+
+template <int ND>
+struct StageTile {
+    static constexpr int X = ND == 1 ? 255 : 32, Y = ND == 1 ? 1 : 11;  // largest tile
+    static constexpr int HY = ND == 1 ? 0 : kGhost;                      // halo rows per side
+    static constexpr int PX = X + 2 * kGhost, PY = Y + 2 * HY;
+    static constexpr int F = ND == 1 ? X + 1 : X * (Y + 1);              // interface slots of one direction
+    static_assert(ND == 1 || (X + 1) * Y <= F, "both directions fit the flux slots");
+    static constexpr int NPT = (X * Y + 255) / 256;                      // nodes per thread
+};
+
+template <int ND>
+struct StageLds {
+    double pt[ND + 5][StageTile<ND>::PY * StageTile<ND>::PX];  // U[0..nc), 1/rho, p, a
+    double fl[ND + 2][StageTile<ND>::F];
+};
+
+// ghost copies of line position q: ne positions from e0 on (periodic images,
+// or the three extrapolated layers of a boundary node)
+struct Images {
+    int64_t e0;
+    int ne;
+};
+__device__ __forceinline__ Images images_of(int64_t q, int64_t N, int kind0, int kind1) {
+    if (kind0 == OSBLI_PERIODIC) {  // periodic directions hold at least six nodes: at most one image
+        if (q < kGhost) return Images{q + N, 1};
+        if (q >= N - kGhost) return Images{q - N, 1};
+    } else {
+        if (q == 0 && kind0 == OSBLI_EXTRAPOLATE) return Images{-kGhost, kGhost};
+        if (q == N - 1 && kind1 == OSBLI_EXTRAPOLATE) return Images{N, kGhost};
+    }
+    return Images{0, 0};
+}
+
+// characteristic (or routed) flux of one interface along DIR of a separable
+// mesh, from the point slots s0, s0 + st, .. of the tile
+template <int ND, int DIR, int SCHEME, bool MIX, bool ROUTE, bool SHARED>
+__device__ __forceinline__ void stage_flux(const StageLds<ND> &sm, int s0, int st, const Phys &ph, bool cheap,
+                                           double (&F)[ND + 2]) {
+    constexpr int NC = ND + 2, NT = ND - 1;
+    Loc<ND> P[6];
+#pragma unroll
+    for (int k = 0; k < 6; ++k) {
+        const int s = s0 + k * st;
+        P[k].r = sm.pt[0][s];
+        P[k].mn = sm.pt[1 + DIR][s];
+        if (NT >= 1) P[k].mt[0] = sm.pt[1 + Axes<ND, DIR>::T1][s];
+        P[k].E = sm.pt[ND + 1][s];
+        P[k].ri = sm.pt[NC][s];
+        P[k].p = sm.pt[NC + 1][s];
+        P[k].a = sm.pt[NC + 2][s];
+    }
+    double Fr, Fn, Ft[2], FE;
+    if (ROUTE && cheap) {
+        if (MIX) cheap_flux_mixed<ND>(P, ph, Fr, Fn, Ft, FE);
+        else cheap_flux<ND>(P, ph, Fr, Fn, Ft, FE);
+    } else {
+        // routed forms: full flux in FP64 (as in the sweeps)
+        if (MIX && !ROUTE) char_flux_mixed<ND, SCHEME>(P, ph, Fr, Fn, Ft, FE);
+        else char_flux<ND, SCHEME, SHARED>(P, ph, Fr, Fn, Ft, FE);
+    }
+    F[0] = Fr;
+    F[1 + DIR] = Fn;
+    if (NT >= 1) F[1 + Axes<ND, DIR>::T1] = Ft[0];
+    F[NC - 1] = FE;
+}
+
+// a node's flux difference over two slots; the product is rounded by itself
+// (the empty asm keeps the compiler from contracting it into the sum over the
+// directions), so that a stage gives the bits of the separate sweeps
+template <int NC, class Lds>
+__device__ __forceinline__ void flux_difference(const Lds &sm, int a, int b, double ih, double (&v)[NC]) {
+#pragma unroll
+    for (int k = 0; k < NC; ++k) {
+        v[k] = -ih * (sm.fl[k][b] - sm.fl[k][a]);
+        asm volatile("" : "+v"(v[k]));
+    }
+}
+
+// The work of one block of 256 threads: the nodes [x0, x0 + nx) x [y0, y0 +
+// ny), nx <= StageTile::X, ny <= StageTile::Y.  XSHARED: one division for both
+// sides of a split along x, as the marching x sweep of rows under 64
+// interfaces has it (the lanes-along-x sweep of longer rows divides per side),
+// so that the bits are the sweeps'.  Block-uniform arguments; every thread
+// calls it.
+template <int ND, int SCHEME, bool MIX, bool ROUTE, bool XSHARED>
+__device__ __forceinline__ void stage_tile(const double *__restrict__ Uin, double *__restrict__ Uout,
+                                           double *__restrict__ dU, const Grid &g, const Phys &ph,
+                                           const double *const (&invh)[3], const uint8_t *const (&mask)[3],
+                                           const int (&bc)[3][2], const RkStage &rs, double dt, int64_t x0,
+                                           int64_t y0, int nx, int ny, unsigned *flags, StageLds<ND> &sm) {
+    using T = StageTile<ND>;
+    constexpr int NC = ND + 2;
+    constexpr int DY = ND == 1 ? 0 : 1;
+    const int tid = threadIdx.x;
+    const int64_t cs = g.enpts;
+    bool bad = false;
+    // points of the tile and its halo (no corners: no stencil reads them)
+    const int wx = nx + 2 * kGhost, np = wx * (ny + 2 * T::HY);
+    for (int e = tid; e < np; e += 256) {
+        const int r = e / wx, c = e - r * wx;
+        if (ND == 2 && (c < kGhost || c >= nx + kGhost) && (r < kGhost || r >= ny + kGhost)) continue;
+        const int64_t src = ext_index(g, x0 - kGhost + c, y0 - T::HY + r, 0);
+        Pt<ND> w;
+#pragma unroll
+        for (int k = 0; k < NC; ++k) w.U[k] = Uin[src + k * cs];
+        finish_point<ND>(ph, w, bad);
+        const int s = r * T::PX + c;
+#pragma unroll
+        for (int k = 0; k < NC; ++k) sm.pt[k][s] = w.U[k];
+        sm.pt[NC][s] = w.ri;
+        sm.pt[NC + 1][s] = w.p;
+        sm.pt[NC + 2][s] = w.a;
+    }
+    __syncthreads();
+    // interfaces outside the line count as smooth (as in the sweeps)
+    auto routed = [&](const uint8_t *mk, int64_t at, int64_t st, int64_t p, int64_t N) {
+        auto ml = [&](int o) { return (p + o < -1 || p + o > N - 1) ? true : mk[at + o * st] != 0; };
+        return ml(0) && (ph.dilate < 1 || (ml(-1) && ml(1))) && (ph.dilate < 2 || (ml(-2) && ml(2)));
+    };
+    const int nfx = (nx + 1) * ny;
+    for (int e = tid; e < nfx; e += 256) {
+        const int r = e / (nx + 1), c = e - r * (nx + 1);
+        bool cheap = false;
+        if (ROUTE) {
+            const int64_t p = x0 + c - 1;
+            cheap = routed(mask[0], (y0 + r) * (g.n[0] + 1) + p + 1, 1, p, g.n[0]);
+        }
+        double F[NC];
+        stage_flux<ND, 0, SCHEME, MIX, ROUTE, XSHARED>(sm, (r + T::HY) * T::PX + c, 1, ph, cheap, F);
+#pragma unroll
+        for (int k = 0; k < NC; ++k) sm.fl[k][e] = F[k];
+    }
+    __syncthreads();
+    // the thread's nodes: their x flux differences, then the flux slots are free
+    double R[T::NPT][NC];
+#pragma unroll
+    for (int m = 0; m < T::NPT; ++m) {
+        const int e = tid + 256 * m;
+        if (e < nx * ny) {
+            const int r = e / nx, c = e - r * nx, f = r * (nx + 1) + c;
+            flux_difference<NC>(sm, f, f + 1, invh[0][x0 + c], R[m]);
+        }
+    }
+    if constexpr (ND == 2) {
+        __syncthreads();
+        const int nfy = nx * (ny + 1);
+        for (int e = tid; e < nfy; e += 256) {
+            const int r = e / nx, c = e - r * nx;
+            bool cheap = false;
+            if (ROUTE) {
+                const int64_t p = y0 + r - 1;
+                cheap = routed(mask[1], (p + 1) * g.n[0] + x0 + c, g.n[0], p, g.n[1]);
+            }
+            double F[NC];
+            stage_flux<ND, DY, SCHEME, MIX, ROUTE, true>(sm, r * T::PX + c + kGhost, T::PX, ph, cheap, F);
+#pragma unroll
+            for (int k = 0; k < NC; ++k) sm.fl[k][e] = F[k];
+        }
+        __syncthreads();
+    }
+#pragma unroll
+    for (int m = 0; m < T::NPT; ++m) {
+        const int e = tid + 256 * m;
+        if (e >= nx * ny) continue;
+        const int r = e / nx, c = e - r * nx;
+        const int64_t x = x0 + c, y = y0 + r;
+        if constexpr (ND == 2) {
+            double v[NC];
+            flux_difference<NC>(sm, e, e + nx, invh[1][y], v);
+#pragma unroll
+            for (int k = 0; k < NC; ++k) R[m][k] += v[k];
+        }
+        const int64_t ci = int_index(g, x, y, 0);
+        const int s = (r + T::HY) * T::PX + c + kGhost;
+        double u[NC];
+#pragma unroll
+        for (int k = 0; k < NC; ++k) {
+            const double du = (rs.first ? 0.0 : rs.A * dU[k * g.nint + ci]) + dt * R[m][k];
+            if (!rs.last) dU[k * g.nint + ci] = du;
+            u[k] = sm.pt[k][s] + rs.B * du;
+        }
+        auto put = [&](int64_t px, int64_t py) {
+            const int64_t o = ext_index(g, px, py, 0);
+#pragma unroll
+            for (int k = 0; k < NC; ++k) Uout[o + k * cs] = u[k];
+        };
+        const Images ix = images_of(x, g.n[0], bc[0][0], bc[0][1]);
+        const Images iy = ND == 2 ? images_of(y, g.n[1], bc[1][0], bc[1][1]) : Images{0, 0};
+        put(x, y);
+        for (int a = 0; a < ix.ne; ++a) put(ix.e0 + a, y);
+        for (int b = 0; b < iy.ne; ++b) {
+            put(x, iy.e0 + b);
+            for (int a = 0; a < ix.ne; ++a) put(ix.e0 + a, iy.e0 + b);
+        }
+    }
+    if (bad) atomicOr(flags, kFlagNonPhys);
+}
+
+}  // namespace cf
+
+// Tiling of one grid: tx x ty nodes per tile, nx x ny tiles.  The columns are
+// split evenly; the rows per tile are those with the shortest estimated time.
+// A tile is t wave tasks per direction (64 interfaces each) on the four SIMDs
+// of a CU that b tiles share: 2.8 us per task with one wave per SIMD, 2.45 per
+// task and SIMD with more (measured on the sweeps), and about 3 us for a
+// tile's points, update and barriers.  Small grids so get short tiles on every
+// CU (256 x 256: 22 us per stage with tiles of nine rows, 15 with four).
+constexpr int kStageSlots = 3;  // tiles per CU (51 KB of LDS, 168 registers)
+
+struct StageTiles {
+    int tx, ty;
+    int64_t nx, ny;
+};
+
+// tilings of `count` grids that run in one launch (the rows per tile are common)
+inline void stage_tiles(const Grid *const *g, int count, StageTiles *t) {
+    const bool one = g[0]->nd == 1;
+    const int mx = one ? cf::StageTile<1>::X : cf::StageTile<2>::X, my = one ? 1 : cf::StageTile<2>::Y;
+    int wide = 0;
+    for (int i = 0; i < count; ++i) {
+        t[i].nx = (g[i]->n[0] + mx - 1) / mx;
+        t[i].tx = (int)((g[i]->n[0] + t[i].nx - 1) / t[i].nx);
+        t[i].nx = (g[i]->n[0] + t[i].tx - 1) / t[i].tx;
+        wide = t[i].tx > wide ? t[i].tx : wide;
+    }
+    int rows = 1;
+    double best = 0.0;
+    for (int y = my; y >= 1; --y) {
+        int64_t blocks = 0;
+        for (int i = 0; i < count; ++i) blocks += t[i].nx * ((g[i]->n[1] + y - 1) / y);
+        const int64_t share = (blocks + 255) / 256 < kStageSlots ? (blocks + 255) / 256 : kStageSlots;
+        const int64_t rounds = (blocks + 256 * share - 1) / (256 * share);
+        auto phase = [&](int items) {
+            const int tasks = (items + 63) / 64;
+            if (share == 1) return 2.8 * ((tasks + 3) / 4);
+            const double w = 2.45 * tasks * share / 4.0;
+            return w > 2.8 ? w : 2.8;
+        };
+        const double cost = rounds * (phase((wide + 1) * y) + phase(wide * (y + 1)) + 3.0);
+        if (best == 0.0 || cost < best) {
+            best = cost;
+            rows = y;
+        }
+    }
+    for (int i = 0; i < count; ++i) {
+        t[i].ty = rows < g[i]->n[1] ? rows : (int)g[i]->n[1];
+        t[i].ny = (g[i]->n[1] + t[i].ty - 1) / t[i].ty;
+    }
+}
+
+inline StageTiles stage_tiles(const Grid &g) {
+    StageTiles t;
+    const Grid *const p = &g;
+    stage_tiles(&p, 1, &t);
+    return t;
+}
+
+}  // namespace osbli

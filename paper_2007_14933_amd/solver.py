@@ -167,9 +167,7 @@ class Solver:
 
     # ---- time loop (section 2.7 ordering: residual, update, BCs) ----
     def step(self, dt):
-        for s in range(self.nstages):
-            self.substep(s, dt)
-            self.apply_bc()
+        B.check(self.lib.osbli_rk_step(self.ctx, float(dt), _ptr(self.U), _ptr(self.dU), self._s()), self.ctx)
         self.t += dt
         self.nsteps_done += 1
 

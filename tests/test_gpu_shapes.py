@@ -47,3 +47,40 @@ def test_viscous_plane_runs(n, ends):
     err = normwise_rel(I.interior_view(3, Ug), I.interior_view(3, Uo))
     say("   ", err)
     assert abs(tg - to) <= 1e-12 * to and err.max() <= 1e-11
+
+
+@pytest.mark.parametrize("scheme", ["WENOZ5", "TENO5", "TENO6", "WENOJS5", "WENOZ3"])
+@pytest.mark.parametrize("n", [(5,), (60,), (255,), (256,), (511,), (5, 6), (6, 5), (31, 10), (32, 11), (33, 12),
+                               (64, 23), (65, 70)])
+@pytest.mark.parametrize("ends", ["periodic", "open", "mixed"])
+def test_one_pass_stage(scheme, n, ends):
+    """The one-pass stage of 1D and 2D problems at the edges of its tiles (255
+    nodes; 32 x 11), the smallest grids, periodic and extrapolated ends and
+    their mixture, three- and five-stage schemes: two steps against the
+    separate calls of the same library, every node and ghost, at 1e-13 of the
+    component's largest value (the forms differ by rounding only)."""
+    import torch
+    from paper_2007_14933_amd import inputs as I
+    from paper_2007_14933_amd.solver import Solver
+    nd = len(n)
+    n3 = n + (1,) * (3 - nd)
+    sides = {"periodic": ((0, 0), (0, 0)), "open": ((1, 1), (1, 1)), "mixed": ((1, 1), (0, 0))}[ends]
+    if any(s == (0, 0) and m < 6 for s, m in zip(sides, n)):
+        pytest.skip("periodic lines hold at least six nodes")
+    prob = I.smooth_random(nd, n3, seed=n[0], amp=0.2).with_(
+        scheme=getattr(I, scheme), bc=sides + ((0, 0),), rk=I.RK4 if ends == "mixed" else I.RK3)
+    a, b = Solver(prob), Solver(prob)
+    for s in (a, b):
+        s.apply_bc()
+    dt = a.compute_dt(0.5)
+    for _ in range(2):
+        a.step(dt)
+        for k in range(b.nstages):
+            b.substep(k, dt)
+            b.apply_bc()
+    a.check()
+    torch.cuda.synchronize()
+    scale = b.U.abs().amax(dim=(1, 2, 3), keepdim=True)
+    err = float(((a.U - b.U).abs() / scale).max())
+    assert err <= 1e-13, err
+    assert float((a.dU - b.dU).abs().max()) <= 1e-12 * float(b.dU.abs().max())
