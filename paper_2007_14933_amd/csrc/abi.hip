@@ -260,6 +260,8 @@ Phys make_phys(const osbli_params *p) {
                            ? pow(q, -1.0 / 6.0) - 1.0
                            : 0.0;
     }
+    ph.eps34 = 0.75 * p->eps;
+    ph.teno_feps = ph.teno_fast * ph.eps34;
     ph.viscous = p->Re > 0.0;
     ph.mu_re = ph.viscous ? 1.0 / p->Re : 0.0;
     ph.kheat = ph.viscous ? 1.0 / ((p->gamma - 1.0) * ph.M2 * p->Pr * p->Re) : 0.0;

@@ -14,14 +14,31 @@ namespace cf {
 template <int ND>
 struct Pt {
     double U[ND + 2];
-    double ri, p, a;
+    double ri, p, a, hu;  // hu: set by the marching sweeps
 };
 
 // Local-frame view of one stencil point: normal / tangential momentum.
+// hu = u_n / 2 (every field's flux is built from it).
 template <int ND>
 struct Loc {
-    double r, mn, mt[2], E, p, a, ri;
+    double r, mn, mt[2], E, p, a, ri, hu;
 };
+
+// what the averaged state takes from one of the interface's two nodes: the
+// weight (sqrt(rho), or one), velocities and total enthalpy
+struct Side {
+    double s, u, ut[2], H;
+};
+template <int ND>
+__device__ __forceinline__ Side side_of(const Loc<ND> &P, const Phys &ph) {
+    Side o;
+    o.s = ph.roe ? sqrt64(P.r) : 1.0;
+    o.u = P.mn * P.ri;
+#pragma unroll
+    for (int s = 0; s < ND - 1; ++s) o.ut[s] = P.mt[s] * P.ri;
+    o.H = (P.E + P.p) * P.ri;
+    return o;
+}
 
 // derived quantities of a point whose conserved state is in w.U
 template <int ND>
@@ -42,71 +59,93 @@ __device__ __forceinline__ void finish_point(const Phys &ph, Pt<ND> &w, bool &ba
 // tau_5 = |beta_0 - beta_2|; WENO-Z alpha_r = d_r (1 + (tau/(beta_r+eps))^2);
 // TENO gamma_r = (1 + tau/(beta_r+eps))^6, stencil r cut when
 // gamma_r / sum(gamma) < C_T (evaluated as gamma_r < C_T * sum), weights
-// d_r delta_r / sum(d delta).  The reconstruction is taken in two parts so
-// that the two of one LLF split share a single division: the candidate
-// values and the indicators (R5), then the weights given
-// t = tau / prod_r(beta_r+eps).  TENO's normalisation divides by one of
+// d_r delta_r / sum(d delta).  TENO's normalisation divides by one of
 // seven sums of optimal weights and is skipped when no stencil is cut
 // (sum = 1).
+//
+// The indicators are sums of two squares of the first differences d1..d4 of
+// f_{i-2..i+2}: with P = (39/64) d^2,
+//   (3/4) beta_0 = (d4 - (11/8) d3)^2 + P(d3),  (3/4) beta_1 = (d3 - (5/8) d2)^2 + P(d2),
+//   (3/4) beta_2 = (d1 - (11/8) d2)^2 + P(d2)
+// (the quadratic forms 13/12 s^2 + t^2/4 with the square completed in their
+// outer difference; the coefficients are exact), ten operations where second
+// differences and their combinations take fifteen.  Every e_r below is
+// (3/4)(beta_r + eps), which leaves all ratios tau / (beta_r + eps) unchanged.
+// The sweeps are bound by FP64 issue (84 % of the cycles, at a clock that the
+// power limit holds near 2 GHz), so operations are their time: with these
+// forms, the linear value on the differences, weights without a division by
+// prod(e) and both sides tested in one branch, 1020 -> 905 VALU instructions
+// per interface of a 256^3 Taylor-Green box with small disturbances, y and z
+// sweeps 0.637 -> 0.577 ms, x 0.692 -> 0.665 ms.
+constexpr double kP = 39.0 / 64.0;
+
 struct R5 {
-    double q0, q1, q2, tau, e0, e1, e2;
+    double f0, d1, d2, d3, d4, tau, b0, b1, b2;
 };
 
-__device__ __forceinline__ R5 recon5_ind(double fm2, double fm1, double f0, double fp1, double fp2, double eps4) {
-    // from the first differences d1..d4 of f_{i-2..i+2}: each candidate is
-    // f_i plus two differences; the indicators are taken times 4,
-    // 4 beta_r = (13/3) s_r^2 + t_r^2 (s_r the second difference, t_r the
-    // one-sided or central first-difference combination of stencil r), with
-    // eps4 = 4 eps, which leaves every ratio tau / (beta_r + eps) unchanged
-    const double d1 = fm1 - fm2, d2 = f0 - fm1, d3 = fp1 - f0, d4 = fp2 - fp1;
+__device__ __forceinline__ R5 recon5_ind(double fm2, double fm1, double f0, double fp1, double fp2) {
     R5 r;
-    r.q0 = f0 + (2.0 / 3.0) * d3 - (1.0 / 6.0) * d4;
-    r.q1 = f0 + (1.0 / 6.0) * d2 + (1.0 / 3.0) * d3;
-    r.q2 = f0 - (1.0 / 3.0) * d1 + (5.0 / 6.0) * d2;
-    const double s0 = d4 - d3, s1 = d3 - d2, s2 = d2 - d1;
-    const double t0 = d4 - 3.0 * d3, t1 = d2 + d3, t2 = 3.0 * d2 - d1;
-    const double b0 = ((13.0 / 3.0) * s0) * s0 + t0 * t0;
-    const double b1 = ((13.0 / 3.0) * s1) * s1 + t1 * t1;
-    const double b2 = ((13.0 / 3.0) * s2) * s2 + t2 * t2;
-    r.tau = fabs(b0 - b2);
-    r.e0 = b0 + eps4;
-    r.e1 = b1 + eps4;
-    r.e2 = b2 + eps4;
+    r.f0 = f0;
+    r.d1 = fm1 - fm2;
+    r.d2 = f0 - fm1;
+    r.d3 = fp1 - f0;
+    r.d4 = fp2 - fp1;
+    const double p2 = (kP * r.d2) * r.d2, p3 = (kP * r.d3) * r.d3;
+    const double w0 = r.d4 - 1.375 * r.d3, w1 = r.d3 - 0.625 * r.d2, w2 = r.d1 - 1.375 * r.d2;
+    r.b0 = w0 * w0 + p3;
+    r.b1 = w1 * w1 + p2;
+    r.b2 = w2 * w2 + p2;
+    r.tau = fabs(r.b0 - r.b2);
     return r;
 }
 
 // TENO's cut test decided by a bound: tau < X min_r(beta_r + eps) with X =
 // ph.teno_fast proves that no stencil is cut (the host derives X from C_T),
 // so the value is the linear fifth-order one and the weights, with their
-// division, are not evaluated.  Exact: the general path would keep all
-// three stencils for these data too.
-__device__ __forceinline__ bool teno5_all_kept(const R5 &r, double X) {
-    return r.tau < X * fmin(fmin(r.e0, r.e1), r.e2);
+// division and the candidates, are not evaluated.  Exact: the general path
+// would keep all three stencils for these data too.
+__device__ __forceinline__ bool teno5_all_kept(const R5 &r, const Phys &ph) {
+    return r.tau < ph.teno_fast * fmin(fmin(r.b0, r.b1), r.b2) + ph.teno_feps;
 }
-__device__ __forceinline__ double lin5(const R5 &r) { return 0.3 * r.q0 + 0.6 * r.q1 + 0.1 * r.q2; }
+// the linear value (2, -13, 47, 27, -3)/60 on the differences
+__device__ __forceinline__ double lin5(const R5 &r) {
+    return r.f0 + 0.4 * r.d3 + (11.0 / 60.0) * r.d2 - (1.0 / 30.0) * r.d1 - 0.05 * r.d4;
+}
 
+// the weighted value when a stencil may be cut.  The weights need the ratios
+// only up to a common factor, so nothing is divided by prod(e): WENO-Z takes
+// alpha_r = d_r (D^2 + (tau prod_{s != r} e_s)^2) with D = e0 e1 e2, TENO's test
+// c_r ~ (e_r + tau) prod_{s != r} e_s, brought near one (the sixth powers stay
+// in range) by the bare hardware estimate of 1/D.
 template <int SCHEME>
-__device__ __forceinline__ double recon5_fin(const R5 &r, double tinv, double CT, bool *kept) {
-    const double x0 = (r.e1 * r.e2) * tinv, x1 = (r.e0 * r.e2) * tinv, x2 = (r.e0 * r.e1) * tinv;
+__device__ __forceinline__ double recon5_gen(const R5 &r, const Phys &ph, bool *kept) {
+    const double q0 = r.f0 + (2.0 / 3.0) * r.d3 - (1.0 / 6.0) * r.d4;
+    const double q1 = r.f0 + (1.0 / 6.0) * r.d2 + (1.0 / 3.0) * r.d3;
+    const double q2 = r.f0 - (1.0 / 3.0) * r.d1 + (5.0 / 6.0) * r.d2;
+    const double e0 = r.b0 + ph.eps34, e1 = r.b1 + ph.eps34, e2 = r.b2 + ph.eps34;
+    const double e01 = e0 * e1, e02 = e0 * e2, e12 = e1 * e2;
     if (SCHEME == OSBLI_WENOZ5) {
-        const double a0 = 0.3 * (1.0 + x0 * x0);
-        const double a1 = 0.6 * (1.0 + x1 * x1);
-        const double a2 = 0.1 * (1.0 + x2 * x2);
-        return (a0 * r.q0 + a1 * r.q1 + a2 * r.q2) * rcp64(a0 + a1 + a2);
+        const double D = e01 * e2, D2 = D * D;
+        const double y0 = r.tau * e12, y1 = r.tau * e02, y2 = r.tau * e01;
+        const double a0 = 0.3 * (D2 + y0 * y0);
+        const double a1 = 0.6 * (D2 + y1 * y1);
+        const double a2 = 0.1 * (D2 + y2 * y2);
+        return (a0 * q0 + a1 * q1 + a2 * q2) * rcp64(a0 + a1 + a2);
     } else {
-        double c0 = 1.0 + x0, c1 = 1.0 + x1, c2 = 1.0 + x2;
+        const double sc = __builtin_amdgcn_rcp(e01 * e2);
+        double c0 = (e0 + r.tau) * (e12 * sc), c1 = (e1 + r.tau) * (e02 * sc), c2 = (e2 + r.tau) * (e01 * sc);
         c0 = c0 * c0 * c0;
         c1 = c1 * c1 * c1;
         c2 = c2 * c2 * c2;
         const double g0 = c0 * c0, g1 = c1 * c1, g2 = c2 * c2;
-        const double lim = CT * (g0 + g1 + g2);
+        const double lim = ph.CT * (g0 + g1 + g2);
         const bool k0 = !(g0 < lim), k1 = !(g1 < lim), k2 = !(g2 < lim);
         const double w0 = k0 ? 0.3 : 0.0;
         const double w1 = k1 ? 0.6 : 0.0;
         const double w2 = k2 ? 0.1 : 0.0;
-        const double num = w0 * r.q0 + w1 * r.q1 + w2 * r.q2;
+        const double num = w0 * q0 + w1 * q1 + w2 * q2;
         if (kept) *kept = *kept && k0 && k1 && k2;
-        if (k0 && k1 && k2) return num;
+        if (k0 & k1 & k2) return num;
         return num * rcp64(w0 + w1 + w2);
     }
 }
@@ -123,32 +162,39 @@ __device__ __forceinline__ double recon5_fin(const R5 &r, double tinv, double CT
 // optimal weights (3/10, 9/20, 1/20, 1/5) (the sixth-order reconstruction
 // when every stencil is kept).  The four ratios tau/(beta_r + eps) share
 // one division: x_r = tau prod_{s != r}(beta_s + eps) / prod_s(beta_s + eps).
+// The cubic's indicator on the differences x, y, z = d3, d4, d5 as three
+// squares (the same form with the square completed outermost first),
+//   (3/4) beta = pz (z + a y + b x)^2 + py (y + c x)^2 + px x^2,
+// with px x^2 = (px / kP) P(x); the centred cubic of WENO-7Z likewise.
+struct Quad3 {
+    double pz, a, b, py, c;
+};
+constexpr Quad3 kOneSided = {547.0 / 320.0, -2.5484460694698354, 1.6946983546617915, 1063.0 / 2188.0,
+                             -1.4896519285042333};
+constexpr Quad3 kCentred = {267.0 / 320.0, -2.0749063670411987, 0.9250936329588015, 1063.0 / 1068.0,
+                            -0.6326434619002822};
+constexpr double kPx = (10153.0 / 17008.0) / kP;
+__device__ __forceinline__ double quad3(const Quad3 &k, double x, double y, double z, double px2) {
+    const double w = z + k.a * y + k.b * x, v = y + k.c * x;
+    return (k.pz * w) * w + ((k.py * v) * v + px2);
+}
+
 __device__ __forceinline__ double recon6_teno(double fm2, double fm1, double f0, double fp1, double fp2, double fp3,
-                                              double CT, double eps, double X, bool *kept) {
-    // from the first differences d1..d5 of f_{i-2..i+3} (as recon5_ind): each
-    // candidate is f_i plus differences, and the indicators are taken times 4
-    // with 4 eps, which leaves every ratio tau / (beta_r + eps) unchanged
-    const double d1 = fm1 - fm2, d2 = f0 - fm1, d3 = fp1 - f0, d4 = fp2 - fp1, d5 = fp3 - fp2;
-    const double q0 = f0 + (2.0 / 3.0) * d3 - (1.0 / 6.0) * d4;
-    const double q1 = f0 + (1.0 / 6.0) * d2 + (1.0 / 3.0) * d3;
-    const double q2 = f0 - (1.0 / 3.0) * d1 + (5.0 / 6.0) * d2;
-    const double q3 = f0 + 0.75 * d3 - (1.0 / 3.0) * d4 + (1.0 / 12.0) * d5;
-    const double s0 = d4 - d3, s1 = d3 - d2, s2 = d2 - d1;
-    const double t0 = d4 - 3.0 * d3, t1 = d2 + d3, t2 = 3.0 * d2 - d1;
-    const double b0 = ((13.0 / 3.0) * s0) * s0 + t0 * t0;
-    const double b1 = ((13.0 / 3.0) * s1) * s1 + t1 * t1;
-    const double b2 = ((13.0 / 3.0) * s2) * s2 + t2 * t2;
-    // the cubic's combinations -11 f_i + 18 f_{i+1} - 9 f_{i+2} + 2 f_{i+3},
-    // 2 f_i - 5 f_{i+1} + 4 f_{i+2} - f_{i+3}, -f_i + 3 f_{i+1} - 3 f_{i+2} + f_{i+3}
-    const double a = 11.0 * d3 - 7.0 * d4 + 2.0 * d5;
-    const double b = 3.0 * d4 - 2.0 * d3 - d5;
-    const double c = d3 - 2.0 * d4 + d5;
-    const double b3 = ((1.0 / 9.0) * a) * a + ((13.0 / 3.0) * b) * b + ((781.0 / 180.0) * c) * c;
-    const double tau = fabs(b3 - (b0 + b2 + 4.0 * b1) * (1.0 / 6.0));
-    const double eps4 = 4.0 * eps;
-    const double e0 = b0 + eps4, e1 = b1 + eps4, e2 = b2 + eps4, e3 = b3 + eps4;
-    // cut test decided by the bound (as for TENO5): no stencil cut
-    if (tau < X * fmin(fmin(e0, e1), fmin(e2, e3))) return 0.3 * q0 + 0.45 * q1 + 0.05 * q2 + 0.2 * q3;
+                                              const Phys &ph, bool *kept) {
+    const R5 r = recon5_ind(fm2, fm1, f0, fp1, fp2);
+    const double d5 = fp3 - fp2;
+    const double b3 = quad3(kOneSided, r.d3, r.d4, d5, (kPx * kP * r.d3) * r.d3);
+    const double tau = fabs(b3 - (r.b0 + r.b2 + 4.0 * r.b1) * (1.0 / 6.0));
+    // cut test decided by the bound (as for TENO5): no stencil cut, the
+    // sixth-order value (1, -8, 37, 37, -8, 1)/60
+    if (tau < ph.teno_fast * fmin(fmin(r.b0, r.b1), fmin(r.b2, b3)) + ph.teno_feps)
+        return f0 + 0.5 * r.d3 + (7.0 / 60.0) * (r.d2 - r.d4) + (1.0 / 60.0) * (d5 - r.d1);
+    const double q0 = f0 + (2.0 / 3.0) * r.d3 - (1.0 / 6.0) * r.d4;
+    const double q1 = f0 + (1.0 / 6.0) * r.d2 + (1.0 / 3.0) * r.d3;
+    const double q2 = f0 - (1.0 / 3.0) * r.d1 + (5.0 / 6.0) * r.d2;
+    const double q3 = f0 + 0.75 * r.d3 - (1.0 / 3.0) * r.d4 + (1.0 / 12.0) * d5;
+    const double CT = ph.CT;
+    const double e0 = r.b0 + ph.eps34, e1 = r.b1 + ph.eps34, e2 = r.b2 + ph.eps34, e3 = b3 + ph.eps34;
     const double e01 = e0 * e1, e23 = e2 * e3;
     const double tq = tau * rcp64(e01 * e23);
     double c0 = 1.0 + tq * (e1 * e23), c1 = 1.0 + tq * (e0 * e23);
@@ -171,11 +217,16 @@ __device__ __forceinline__ double recon6_teno(double fm2, double fm1, double f0,
 // (beta_r + eps)^2; the normalisation cancels the common factor
 // prod_s (beta_s + eps)^2, so omega_r = d_r P_r / sum_k d_k P_k with
 // P_r = prod_{s != r} (beta_s + eps)^2 and one division per reconstruction.
-__device__ __forceinline__ double recon5_js(double fm2, double fm1, double f0, double fp1, double fp2, double eps) {
-    const R5 r = recon5_ind(fm2, fm1, f0, fp1, fp2, 4.0 * eps);
-    const double s0 = r.e0 * r.e0, s1 = r.e1 * r.e1, s2 = r.e2 * r.e2;
+__device__ __forceinline__ double recon5_js(double fm2, double fm1, double f0, double fp1, double fp2,
+                                            const Phys &ph) {
+    const R5 r = recon5_ind(fm2, fm1, f0, fp1, fp2);
+    const double e0 = r.b0 + ph.eps34, e1 = r.b1 + ph.eps34, e2 = r.b2 + ph.eps34;
+    const double q0 = f0 + (2.0 / 3.0) * r.d3 - (1.0 / 6.0) * r.d4;
+    const double q1 = f0 + (1.0 / 6.0) * r.d2 + (1.0 / 3.0) * r.d3;
+    const double q2 = f0 - (1.0 / 3.0) * r.d1 + (5.0 / 6.0) * r.d2;
+    const double s0 = e0 * e0, s1 = e1 * e1, s2 = e2 * e2;
     const double a0 = 0.3 * (s1 * s2), a1 = 0.6 * (s0 * s2), a2 = 0.1 * (s0 * s1);
-    return (a0 * r.q0 + a1 * r.q1 + a2 * r.q2) * rcp64(a0 + a1 + a2);
+    return (a0 * q0 + a1 * q1 + a2 * q2) * rcp64(a0 + a1 + a2);
 }
 
 // WENO-3Z (third-order WENO-Z, the lowest order of section 5.2) at
@@ -208,22 +259,17 @@ __device__ __forceinline__ double recon3_z(double fm1, double f0, double fp1, do
 // beta_3|, alpha_r = d_r (1 + (tau/(beta_r + eps))^2); the four ratios
 // share one division and the normalisation takes another.
 __device__ __forceinline__ double recon7_z(double fm3, double fm2, double fm1, double f0, double fp1, double fp2,
-                                           double fp3, double eps) {
+                                           double fp3, double eps34) {
     const double d1 = fm2 - fm3, d2 = fm1 - fm2, d3 = f0 - fm1, d4 = fp1 - f0, d5 = fp2 - fp1, d6 = fp3 - fp2;
     const double q0 = f0 + 0.75 * d4 - (1.0 / 3.0) * d5 + (1.0 / 12.0) * d6;
     const double q1 = f0 + (1.0 / 12.0) * d3 + 0.5 * d4 - (1.0 / 12.0) * d5;
     const double q2 = f0 - (1.0 / 12.0) * d2 + (1.0 / 3.0) * d3 + 0.25 * d4;
     const double q3 = f0 + 0.25 * d1 - (5.0 / 6.0) * d2 + (13.0 / 12.0) * d3;
-    auto ind = [](double a, double b, double c) {
-        return ((1.0 / 9.0) * a) * a + ((13.0 / 3.0) * b) * b + ((781.0 / 180.0) * c) * c;
-    };
-    const double b0 = ind(11.0 * d4 - 7.0 * d5 + 2.0 * d6, 3.0 * d5 - 2.0 * d4 - d6, d4 - 2.0 * d5 + d6);
-    const double b1 = ind(2.0 * d3 + 5.0 * d4 - d5, d4 - d3, d3 - 2.0 * d4 + d5);
-    const double b2 = ind(5.0 * d3 + 2.0 * d4 - d2, d4 - d3, d2 - 2.0 * d3 + d4);
-    const double b3 = ind(2.0 * d1 - 7.0 * d2 + 11.0 * d3, d1 - 3.0 * d2 + 2.0 * d3, d1 - 2.0 * d2 + d3);
+    const double s3 = (kPx * kP * d3) * d3, s4 = (kPx * kP * d4) * d4;
+    const double b0 = quad3(kOneSided, d4, d5, d6, s4), b1 = quad3(kCentred, d3, d4, d5, s3);
+    const double b2 = quad3(kCentred, d4, d3, d2, s4), b3 = quad3(kOneSided, d3, d2, d1, s3);
     const double tau = fabs(b0 + 3.0 * b1 - 3.0 * b2 - b3);
-    const double eps4 = 4.0 * eps;
-    const double e0 = b0 + eps4, e1 = b1 + eps4, e2 = b2 + eps4, e3 = b3 + eps4;
+    const double e0 = b0 + eps34, e1 = b1 + eps34, e2 = b2 + eps34, e3 = b3 + eps34;
     const double e01 = e0 * e1, e23 = e2 * e3;
     const double tq = tau * rcp64(e01 * e23);
     const double x0 = tq * (e1 * e23), x1 = tq * (e0 * e23), x2 = tq * (e01 * e3), x3 = tq * (e01 * e2);
@@ -238,13 +284,11 @@ __device__ __forceinline__ double recon7_z(double fm3, double fm2, double fm1, d
 // recon+(g+_{i-1..i+1}) + recon-(g-_{i+2..i}); WENO-7Z reads W = 8 points,
 // recon+(g+_{i-3..i+3}) + recon-(g-_{i+4..i-2})).  Takes V, gh = g/2 and
 // ha = alpha/2, so g+- = (g +- alpha V)/2 = gh +- ha V.
-// SHARED: one division serves both sides: with D+- = prod_r(beta_r+eps),
-// tau+/D+ = tau+ D- / (D+ D-) and likewise for the other side (D+ D- >=
-// eps^6, which the accepted range of eps keeps a normal number).  This
-// saves five divisions per interface but keeps both sides' indicators live
-// at once, which the marching sweeps can afford and the lane-per-interface
-// sweep cannot (it spills), so that one divides per side.
-template <int SCHEME, bool SHARED, int W>
+// JOINT: TENO5's cut test is taken for both sides at once, one branch per
+// field; it keeps both sides' indicators live, which the marching sweeps can
+// afford and the lane-per-interface sweep cannot (it spills), so that one
+// branches per side.
+template <int SCHEME, bool JOINT, int W>
 __device__ __forceinline__ double split_recon(const double (&V)[W], const double (&gh)[W], double ha,
                                               const Phys &ph, bool *kept = nullptr) {
     double gp[W], gm[W];
@@ -255,58 +299,48 @@ __device__ __forceinline__ double split_recon(const double (&V)[W], const double
     }
     if constexpr (SCHEME == OSBLI_WENOZ7) {
         // eight points i-3..i+4: recon+(g+_{i-3..i+3}) + recon-(g-_{i+4..i-2})
-        return recon7_z(gp[0], gp[1], gp[2], gp[3], gp[4], gp[5], gp[6], ph.eps) +
-               recon7_z(gm[7], gm[6], gm[5], gm[4], gm[3], gm[2], gm[1], ph.eps);
+        return recon7_z(gp[0], gp[1], gp[2], gp[3], gp[4], gp[5], gp[6], ph.eps34) +
+               recon7_z(gm[7], gm[6], gm[5], gm[4], gm[3], gm[2], gm[1], ph.eps34);
     } else if constexpr (SCHEME == OSBLI_TENO6) {
-        return recon6_teno(gp[0], gp[1], gp[2], gp[3], gp[4], gp[5], ph.CT, ph.eps, ph.teno_fast, kept) +
-               recon6_teno(gm[5], gm[4], gm[3], gm[2], gm[1], gm[0], ph.CT, ph.eps, ph.teno_fast, kept);
+        return recon6_teno(gp[0], gp[1], gp[2], gp[3], gp[4], gp[5], ph, kept) +
+               recon6_teno(gm[5], gm[4], gm[3], gm[2], gm[1], gm[0], ph, kept);
     } else if constexpr (SCHEME == OSBLI_WENOJS5) {
-        return recon5_js(gp[0], gp[1], gp[2], gp[3], gp[4], ph.eps) +
-               recon5_js(gm[5], gm[4], gm[3], gm[2], gm[1], ph.eps);
+        return recon5_js(gp[0], gp[1], gp[2], gp[3], gp[4], ph) +
+               recon5_js(gm[5], gm[4], gm[3], gm[2], gm[1], ph);
     } else if constexpr (SCHEME == OSBLI_WENOZ3) {
         return recon3_z(gp[1], gp[2], gp[3], ph.eps) + recon3_z(gm[4], gm[3], gm[2], ph.eps);
-    } else if (SHARED) {
-        const double eps4 = 4.0 * ph.eps;
-        const R5 a = recon5_ind(gp[0], gp[1], gp[2], gp[3], gp[4], eps4);
-        const R5 b = recon5_ind(gm[5], gm[4], gm[3], gm[2], gm[1], eps4);
-        if (SCHEME == OSBLI_TENO5 && teno5_all_kept(a, ph.teno_fast) && teno5_all_kept(b, ph.teno_fast))
-            return lin5(a) + lin5(b);
-        const double da = (a.e0 * a.e1) * a.e2, db = (b.e0 * b.e1) * b.e2;
-        const double inv = rcp64(da * db);
-        return recon5_fin<SCHEME>(a, (a.tau * db) * inv, ph.CT, kept) +
-               recon5_fin<SCHEME>(b, (b.tau * da) * inv, ph.CT, kept);
+    } else if (JOINT) {
+        const R5 a = recon5_ind(gp[0], gp[1], gp[2], gp[3], gp[4]);
+        const R5 b = recon5_ind(gm[5], gm[4], gm[3], gm[2], gm[1]);
+        if (SCHEME == OSBLI_TENO5 && (teno5_all_kept(a, ph) & teno5_all_kept(b, ph))) return lin5(a) + lin5(b);
+        return recon5_gen<SCHEME>(a, ph, kept) + recon5_gen<SCHEME>(b, ph, kept);
     } else {
-        const double eps4 = 4.0 * ph.eps;
-        const R5 a = recon5_ind(gp[0], gp[1], gp[2], gp[3], gp[4], eps4);
-        double ha5;
-        if (SCHEME == OSBLI_TENO5 && teno5_all_kept(a, ph.teno_fast)) ha5 = lin5(a);
-        else ha5 = recon5_fin<SCHEME>(a, a.tau * rcp64((a.e0 * a.e1) * a.e2), ph.CT, kept);
-        const R5 b = recon5_ind(gm[5], gm[4], gm[3], gm[2], gm[1], eps4);
-        if (SCHEME == OSBLI_TENO5 && teno5_all_kept(b, ph.teno_fast)) return ha5 + lin5(b);
-        return ha5 + recon5_fin<SCHEME>(b, b.tau * rcp64((b.e0 * b.e1) * b.e2), ph.CT, kept);
+        auto side = [&](const R5 &r) -> double {
+            if (SCHEME == OSBLI_TENO5 && teno5_all_kept(r, ph)) return lin5(r);
+            return recon5_gen<SCHEME>(r, ph, kept);
+        };
+        const double ha5 = side(recon5_ind(gp[0], gp[1], gp[2], gp[3], gp[4]));
+        return ha5 + side(recon5_ind(gm[5], gm[4], gm[3], gm[2], gm[1]));
     }
 }
 
 // Interface flux in the local frame (unit |S|) from the W stencil points
-// i-W/2+1 .. i+W/2 (W = 6, or 8 for WENO-7Z).  Outputs: mass, normal
-// momentum, tangential momenta, energy.
-template <int ND, int SCHEME, bool SHARED = true, int W = 6>
-__device__ __forceinline__ void char_flux(const Loc<ND> (&P)[W], const Phys &ph, double &Fr, double &Fn,
-                                          double (&Ft)[2], double &FE, bool *kept = nullptr) {
+// i-W/2+1 .. i+W/2 (W = 6, or 8 for WENO-7Z) and the Sides of the two nodes
+// next to the interface.  Outputs: mass, normal momentum, tangential momenta,
+// energy.
+template <int ND, int SCHEME, bool JOINT, int W>
+__device__ __forceinline__ void char_flux_sides(const Loc<ND> (&P)[W], const Side &SL, const Side &SR,
+                                                const Phys &ph, double &Fr, double &Fn, double (&Ft)[2], double &FE,
+                                                bool *kept = nullptr) {
     constexpr int NT = ND - 1;  // tangents
-    constexpr int L = W / 2 - 1, R = W / 2;  // the nodes either side of the interface
     // averaged state at the half node (Roe, or arithmetic mean with unit weights)
-    double sl = 1.0, sr = 1.0;
-    if (ph.roe) {
-        sl = sqrt64(P[L].r);
-        sr = sqrt64(P[R].r);
-    }
+    const double sl = SL.s, sr = SR.s;
     const double iw = rcp64(sl + sr);
-    const double un = (sl * (P[L].mn * P[L].ri) + sr * (P[R].mn * P[R].ri)) * iw;
+    const double un = (sl * SL.u + sr * SR.u) * iw;
     double ut[2] = {0.0, 0.0};
 #pragma unroll
-    for (int s = 0; s < NT; ++s) ut[s] = (sl * (P[L].mt[s] * P[L].ri) + sr * (P[R].mt[s] * P[R].ri)) * iw;
-    const double Hh = (sl * ((P[L].E + P[L].p) * P[L].ri) + sr * ((P[R].E + P[R].p) * P[R].ri)) * iw;
+    for (int s = 0; s < NT; ++s) ut[s] = (sl * SL.ut[s] + sr * SR.ut[s]) * iw;
+    const double Hh = (sl * SL.H + sr * SR.H) * iw;
     double K = un * un;
 #pragma unroll
     for (int s = 0; s < NT; ++s) K += ut[s] * ut[s];
@@ -321,7 +355,7 @@ __device__ __forceinline__ void char_flux(const Loc<ND> (&P)[W], const Phys &ph,
     double hu[W], A[W], B[W], am[W], ap[W], a0 = 0.0;
 #pragma unroll
     for (int k = 0; k < W; ++k) {
-        hu[k] = P[k].mn * (0.5 * P[k].ri);
+        hu[k] = P[k].hu;
         double um = un * P[k].mn;
 #pragma unroll
         for (int s = 0; s < NT; ++s) um += ut[s] * P[k].mt[s];
@@ -345,21 +379,21 @@ __device__ __forceinline__ void char_flux(const Loc<ND> (&P)[W], const Phys &ph,
         V[k] = A[k] + B[k];
         gh[k] = hu[k] * V[k] + P[k].p * (hb * hu[k] - cm);
     }
-    const double h0 = split_recon<SCHEME, SHARED, W>(V, gh, 0.5 * aminus, ph, kept);
+    const double h0 = split_recon<SCHEME, JOINT, W>(V, gh, 0.5 * aminus, ph, kept);
     // field u_n + a
 #pragma unroll
     for (int k = 0; k < W; ++k) {
         V[k] = A[k] - B[k];
         gh[k] = hu[k] * V[k] + P[k].p * (hb * hu[k] - cp);
     }
-    const double h4 = split_recon<SCHEME, SHARED, W>(V, gh, 0.5 * aplus, ph, kept);
+    const double h4 = split_recon<SCHEME, JOINT, W>(V, gh, 0.5 * aplus, ph, kept);
     // entropy field: V = rho - b (K rho - u.m + E), g = u_n V + p b (un - u_n)
 #pragma unroll
     for (int k = 0; k < W; ++k) {
         V[k] = P[k].r - 2.0 * A[k];
         gh[k] = hu[k] * V[k] + P[k].p * (hbun - b * hu[k]);
     }
-    const double h1 = split_recon<SCHEME, SHARED, W>(V, gh, a0, ph, kept);
+    const double h1 = split_recon<SCHEME, JOINT, W>(V, gh, a0, ph, kept);
     // shear fields: V = m_t - ut rho, g = u_n V
     double ht[2] = {0.0, 0.0};
 #pragma unroll
@@ -369,7 +403,7 @@ __device__ __forceinline__ void char_flux(const Loc<ND> (&P)[W], const Phys &ph,
             V[k] = P[k].mt[s] - ut[s] * P[k].r;
             gh[k] = hu[k] * V[k];
         }
-        ht[s] = split_recon<SCHEME, SHARED, W>(V, gh, a0, ph, kept);
+        ht[s] = split_recon<SCHEME, JOINT, W>(V, gh, a0, ph, kept);
     }
     // back to physical space: F = R ghat
     const double hs = h0 + h1 + h4;
@@ -382,6 +416,14 @@ __device__ __forceinline__ void char_flux(const Loc<ND> (&P)[W], const Phys &ph,
         Ft[s] = ut[s] * hs + ht[s];
         FE += ut[s] * ht[s];
     }
+}
+
+// the same with the Sides evaluated here
+template <int ND, int SCHEME, bool JOINT = true, int W = 6>
+__device__ __forceinline__ void char_flux(const Loc<ND> (&P)[W], const Phys &ph, double &Fr, double &Fn,
+                                          double (&Ft)[2], double &FE, bool *kept = nullptr) {
+    char_flux_sides<ND, SCHEME, JOINT, W>(P, side_of<ND>(P[W / 2 - 1], ph), side_of<ND>(P[W / 2], ph), ph, Fr, Fn, Ft,
+                                          FE, kept);
 }
 
 // ---------------------------------------------------------------- mixed form

@@ -81,6 +81,7 @@ k_sweep_wz7(const double *__restrict__ U, double *__restrict__ R, Grid g, Phys p
         P[k].p = sw[NC + 1][sl];
         P[k].a = sw[NC + 2][sl];
         P[k].ri = sw[NC][sl];
+        P[k].hu = P[k].mn * (0.5 * P[k].ri);
     }
     double Fr, Fn, Ft[2], FE;
     char_flux<ND, OSBLI_WENOZ7, true, 8>(P, ph, Fr, Fn, Ft, FE);
@@ -111,7 +112,7 @@ k_sweep_wz7(const double *__restrict__ U, double *__restrict__ R, Grid g, Phys p
 // its 1/rho, p and a, per step): the flux of interface f, the node f from
 // this flux and the previous one (kept in registers)
 template <int ND, int DIR>
-__global__ void __launch_bounds__(64 * kWaves)
+__global__ void __launch_bounds__(64 * kWaves, 2)
 k_sweep_wz7_march(const double *__restrict__ U, double *__restrict__ R, Grid g, Phys ph, Metrics m, int64_t seg,
                   int64_t nseg, int64_t waves, int first, unsigned *flags) {
     constexpr int NC = ND + 2;
@@ -155,6 +156,7 @@ k_sweep_wz7_march(const double *__restrict__ U, double *__restrict__ R, Grid g, 
         P.p = pt.p;
         P.a = pt.a;
         P.ri = pt.ri;
+        P.hu = P.mn * (0.5 * P.ri);
     };
     // window of the eight stencil points f-3 .. f+4, one new point per step
     Loc<ND> P[8];

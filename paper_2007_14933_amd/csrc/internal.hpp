@@ -29,6 +29,7 @@ struct Grid {
 struct Phys {
     double gamma, gm1, Re, Pr, Minf, M2, Ts, CT, eps;
     double teno_fast;  // TENO: every stencil is kept when tau < teno_fast * min_r(beta_r + eps)
+    double eps34, teno_feps;  // (3/4) eps (the kernels' indicators carry that factor), teno_fast times it
     double mu_re;      // 1/Re
     double kheat;      // 1/((gamma-1) M^2 Pr Re)
     double nu_fac;     // max(4/3, gamma/Pr)

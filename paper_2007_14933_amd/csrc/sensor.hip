@@ -50,6 +50,7 @@ k_labels(const double *__restrict__ U, Grid g, Phys ph, float *__restrict__ feat
         P[k].p = w.p;
         P[k].a = w.a;
         P[k].ri = w.ri;
+        P[k].hu = P[k].mn * (0.5 * w.ri);
     }
     bool kept = true;
     double Fr, Fn, Ft[2], FE;

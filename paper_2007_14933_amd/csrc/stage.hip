@@ -42,7 +42,7 @@ hipError_t launch_one(const Grid &g, const Phys &ph, const StageArgs &a, const d
 template <int SCHEME, bool MIX, bool ROUTE>
 hipError_t launch_nd(const Grid &g, const Phys &ph, const StageArgs &a, const double *Uin, double *Uout, double *dU,
                      const RkStage &rs, double dt, unsigned *flags, hipStream_t s) {
-    // the other schemes divide per side everywhere
+    // the other schemes reconstruct side by side everywhere
     if constexpr (SCHEME == OSBLI_WENOZ5 || SCHEME == OSBLI_TENO5)
         if (g.n[0] + 1 < 64)
             return g.nd == 1 ? launch_one<1, SCHEME, MIX, ROUTE, true>(g, ph, a, Uin, Uout, dU, rs, dt, flags, s)

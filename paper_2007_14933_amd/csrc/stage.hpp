@@ -58,7 +58,7 @@ __device__ __forceinline__ Images images_of(int64_t q, int64_t N, int kind0, int
 
 // characteristic (or routed) flux of one interface along DIR of a separable
 // mesh, from the point slots s0, s0 + st, .. of the tile
-template <int ND, int DIR, int SCHEME, bool MIX, bool ROUTE, bool SHARED>
+template <int ND, int DIR, int SCHEME, bool MIX, bool ROUTE, bool JOINT>
 __device__ __forceinline__ void stage_flux(const StageLds<ND> &sm, int s0, int st, const Phys &ph, bool cheap,
                                            double (&F)[ND + 2]) {
     constexpr int NC = ND + 2, NT = ND - 1;
@@ -73,6 +73,7 @@ __device__ __forceinline__ void stage_flux(const StageLds<ND> &sm, int s0, int s
         P[k].ri = sm.pt[NC][s];
         P[k].p = sm.pt[NC + 1][s];
         P[k].a = sm.pt[NC + 2][s];
+        P[k].hu = P[k].mn * (0.5 * P[k].ri);
     }
     double Fr, Fn, Ft[2], FE;
     if (ROUTE && cheap) {
@@ -81,7 +82,7 @@ __device__ __forceinline__ void stage_flux(const StageLds<ND> &sm, int s0, int s
     } else {
         // routed forms: full flux in FP64 (as in the sweeps)
         if (MIX && !ROUTE) char_flux_mixed<ND, SCHEME>(P, ph, Fr, Fn, Ft, FE);
-        else char_flux<ND, SCHEME, SHARED>(P, ph, Fr, Fn, Ft, FE);
+        else char_flux<ND, SCHEME, JOINT>(P, ph, Fr, Fn, Ft, FE);
     }
     F[0] = Fr;
     F[1 + DIR] = Fn;
@@ -102,12 +103,12 @@ __device__ __forceinline__ void flux_difference(const Lds &sm, int a, int b, dou
 }
 
 // The work of one block of 256 threads: the nodes [x0, x0 + nx) x [y0, y0 +
-// ny), nx <= StageTile::X, ny <= StageTile::Y.  XSHARED: one division for both
+// ny), nx <= StageTile::X, ny <= StageTile::Y.  XJOINT: one cut test for both
 // sides of a split along x, as the marching x sweep of rows under 64
-// interfaces has it (the lanes-along-x sweep of longer rows divides per side),
+// interfaces has it (the lanes-along-x sweep of longer rows tests per side),
 // so that the bits are the sweeps'.  Block-uniform arguments; every thread
 // calls it.
-template <int ND, int SCHEME, bool MIX, bool ROUTE, bool XSHARED>
+template <int ND, int SCHEME, bool MIX, bool ROUTE, bool XJOINT>
 __device__ __forceinline__ void stage_tile(const double *__restrict__ Uin, double *__restrict__ Uout,
                                            double *__restrict__ dU, const Grid &g, const Phys &ph,
                                            const double *const (&invh)[3], const uint8_t *const (&mask)[3],
@@ -151,7 +152,7 @@ __device__ __forceinline__ void stage_tile(const double *__restrict__ Uin, doubl
             cheap = routed(mask[0], (y0 + r) * (g.n[0] + 1) + p + 1, 1, p, g.n[0]);
         }
         double F[NC];
-        stage_flux<ND, 0, SCHEME, MIX, ROUTE, XSHARED>(sm, (r + T::HY) * T::PX + c, 1, ph, cheap, F);
+        stage_flux<ND, 0, SCHEME, MIX, ROUTE, XJOINT>(sm, (r + T::HY) * T::PX + c, 1, ph, cheap, F);
 #pragma unroll
         for (int k = 0; k < NC; ++k) sm.fl[k][e] = F[k];
     }

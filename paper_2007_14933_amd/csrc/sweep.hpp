@@ -123,6 +123,7 @@ __device__ __forceinline__ void sweep_wave(const double *__restrict__ U, double 
 #pragma unroll
         for (int c = 0; c < NC; ++c) w.U[c] = ab[slot][c][lane];
         finish_point<ND>(ph, w, bad);
+        w.hu = w.U[1 + DIR] * (0.5 * w.ri);
     };
 
     int64_t cbase = p0 - 3 - kChunk;  // first point held in the chunk buffer
@@ -156,6 +157,7 @@ __device__ __forceinline__ void sweep_wave(const double *__restrict__ U, double 
             for (int c = 0; c < NC; ++c) w.U[c] = U[base + qp * st + c * cs];
         }
         finish_point<ND>(ph, w, bad);
+        w.hu = w.U[1 + DIR] * (0.5 * w.ri);
     };
 
     Pt<ND> w[6];
@@ -194,7 +196,22 @@ __device__ __forceinline__ void sweep_wave(const double *__restrict__ U, double 
         for (int k = 0; k < 5; ++k) mw[k] = mload(p0 - 3 + k);
     }
 
+    // a window point in the frame of the line (separable meshes)
+    auto local = [&](const Pt<ND> &q) {
+        Loc<ND> o;
+        o.r = q.U[0];
+        o.mn = q.U[1 + DIR];
+        if (NT >= 1) o.mt[0] = q.U[1 + Axes<ND, DIR>::T1];
+        if (NT >= 2) o.mt[1] = q.U[1 + Axes<ND, DIR>::T2];
+        o.E = q.U[ND + 1];
+        o.p = q.p;
+        o.a = q.a;
+        o.ri = q.ri;
+        o.hu = q.hu;
+        return o;
+    };
     double Fp[NC];
+    Side SL = side_of<ND>(local(w[2]), ph);  // of the left node (plain FP64 form)
     for (int64_t f = p0 - 1; f < p1; ++f) {
         if (ROUTE && f >= p0) {
 #pragma unroll
@@ -237,16 +254,7 @@ __device__ __forceinline__ void sweep_wave(const double *__restrict__ U, double 
         double nv[3] = {0.0, 0.0, 0.0}, t1[3] = {0.0, 0.0, 0.0}, t2[3] = {0.0, 0.0, 0.0};
         if (!GEN) {
 #pragma unroll
-            for (int k = 0; k < 6; ++k) {
-                P[k].r = w[k].U[0];
-                P[k].mn = w[k].U[1 + DIR];
-                if (NT >= 1) P[k].mt[0] = w[k].U[1 + Axes<ND, DIR>::T1];
-                if (NT >= 2) P[k].mt[1] = w[k].U[1 + Axes<ND, DIR>::T2];
-                P[k].E = w[k].U[ND + 1];
-                P[k].p = w[k].p;
-                P[k].a = w[k].a;
-                P[k].ri = w[k].ri;
-            }
+            for (int k = 0; k < 6; ++k) P[k] = local(w[k]);
         } else {
             double Sh[3] = {0.0, 0.0, 0.0};
             double s2 = 0.0;
@@ -294,6 +302,7 @@ __device__ __forceinline__ void sweep_wave(const double *__restrict__ U, double 
                 P[k].p = w[k].p;
                 P[k].a = w[k].a;
                 P[k].ri = w[k].ri;
+                P[k].hu = mn * (0.5 * w[k].ri);
             }
         }
         double Fr, Fn, Ft[2], FE;
@@ -308,8 +317,16 @@ __device__ __forceinline__ void sweep_wave(const double *__restrict__ U, double 
             // the routed forms fall back to the full flux in FP64: near a shock
             // the deviations from the reference flux are as large as the jump,
             // and their FP32 rounding is the precision form's main error there
-            if (MIX && !ROUTE) char_flux_mixed<ND, SCHEME>(P, ph, Fr, Fn, Ft, FE);
-            else char_flux<ND, SCHEME>(P, ph, Fr, Fn, Ft, FE);
+            if constexpr (MIX && !ROUTE) {
+                char_flux_mixed<ND, SCHEME>(P, ph, Fr, Fn, Ft, FE);
+            } else if constexpr (GEN || ROUTE) {
+                char_flux<ND, SCHEME>(P, ph, Fr, Fn, Ft, FE);
+            } else {
+                // the right node of this interface is the left one of the next
+                const Side SR = side_of<ND>(P[3], ph);
+                char_flux_sides<ND, SCHEME, true, 6>(P, SL, SR, ph, Fr, Fn, Ft, FE);
+                SL = SR;
+            }
         }
         F[0] = Fr * Smag;
         F[NC - 1] = FE * Smag;
@@ -496,6 +513,7 @@ __device__ __forceinline__ void sweep_x_lanes(const double *__restrict__ U, doub
         P[k].ri = sm.pt[NC][slot];
         P[k].p = sm.pt[NC + 1][slot];
         P[k].a = sm.pt[NC + 2][slot];
+        P[k].hu = P[k].mn * (0.5 * P[k].ri);
     }
     bool cheap = false;
     if (ROUTE) {
