@@ -246,7 +246,8 @@ size_t osbli_noalloc_scratch_bytes(void);
 /* dt = cfl / max over interior nodes of
  *   sum_d J|S_d| (|u.n_d| + a) + 2 nu_eff sum_d (J|S_d|)^2,
  * nu_eff = max(4/3, gamma/Pr) mu/(rho Re) when viscous.  Deterministic
- * device max-reduction; synchronising (one host read-back). */
+ * device max-reduction; returns when the value has reached the host, with all
+ * earlier work of the stream done. */
 int osbli_compute_dt(osbli_ctx *ctx, const double *U, double cfl, double *dt_out, void *stream);
 
 /* Synchronises the context's last stream; returns OSBLI_ENONPHYS if any

@@ -47,6 +47,48 @@ void *resolve_scratch(int dev, hipError_t *err) {
 }
 }  // namespace
 
+// Pinned host words of the dt reduction, one slot per context out of one page
+// that lives while any context does.  A context that finds the page full or
+// not allocatable does without (it copies the device result back).
+namespace {
+constexpr int kDtSlots = 64;
+std::mutex dt_mu;
+struct alignas(64) DtCell {
+    DtSlot s;
+};
+DtCell *dt_page = nullptr;
+uint64_t dt_used = 0;
+
+DtSlot *take_dt_slot() {
+    std::lock_guard<std::mutex> lk(dt_mu);
+    if (!dt_page) {
+        void *p = nullptr;
+        if (hipHostMalloc(&p, sizeof(DtCell) * kDtSlots, hipHostMallocPortable | hipHostMallocMapped) != hipSuccess) {
+            (void)hipGetLastError();
+            return nullptr;
+        }
+        dt_page = static_cast<DtCell *>(p);
+    }
+    for (int k = 0; k < kDtSlots; ++k)
+        if (!((dt_used >> k) & 1)) {
+            dt_used |= uint64_t(1) << k;
+            dt_page[k].s = DtSlot{0, 0};
+            return &dt_page[k].s;
+        }
+    return nullptr;
+}
+
+void give_dt_slot(DtSlot *s) {
+    if (!s) return;
+    std::lock_guard<std::mutex> lk(dt_mu);
+    dt_used &= ~(uint64_t(1) << (reinterpret_cast<DtCell *>(s) - dt_page));
+    if (dt_used == 0) {
+        (void)hipHostFree(dt_page);
+        dt_page = nullptr;
+    }
+}
+}  // namespace
+
 // optional HIP-event timing of each kernel class on the launch stream
 struct Prof {
     int on = 0;
@@ -83,6 +125,8 @@ struct osbli_ctx {
     double rkA[5], rkB[5]; // their 2N coefficients
     void *cwork;           // central path: the store-all strategy's work arrays (null: StoreSome)
     double *W[2];          // state copies of the one-pass stage (null: separate passes)
+    DtSlot *dt_slot;       // the dt reduction's host words (null: copy back)
+    unsigned long long dt_seq;
     char err[320];
 };
 
@@ -222,6 +266,11 @@ Layout make_layout(const osbli_params *p, const Grid &g) {
         stage = align256(sizeof(double) * (g.n[0] + g.n[1] + g.n[2]));
     L.stage = off;
     size_t region = racc + gsz > stage ? racc + gsz : stage;
+    // the one-pass stage's state copies: it uses no residual accumulator, so the
+    // first shares this region
+    const size_t copy = stage_supported(g, *p) ? align256(sizeof(double) * g.nc * g.enpts) : 0;
+    if (copy > region) region = copy;
+    L.W[0] = L.Racc;
     off += region;
     for (int d = 0; d < 3; ++d) {
         L.mask[d] = off;
@@ -229,11 +278,8 @@ Layout make_layout(const osbli_params *p, const Grid &g) {
     }
     L.wts = off;
     if (p->sensor) off += align256(2 * 1441);
-    // state copies of the one-pass stage
-    for (int k = 0; k < 2; ++k) {
-        L.W[k] = off;
-        if (stage_supported(g, *p)) off += align256(sizeof(double) * g.nc * g.enpts);
-    }
+    L.W[1] = off;
+    off += copy;
     L.total = off;
     return L;
 }
@@ -461,6 +507,7 @@ int osbli_init_grid(osbli_ctx **out, const osbli_params *p, const double *x, con
     // the allocation-free substep's scratch on this device (a failure here
     // only disables that entry point)
     c->scratch = static_cast<char *>(resolve_scratch(c->device, &c->scratch_err));
+    c->dt_slot = take_dt_slot();
     hipStream_t s = as_stream(stream);
     c->last = s;
     c->ws = static_cast<char *>(workspace);
@@ -691,14 +738,38 @@ int osbli_compute_dt(osbli_ctx *c, const double *U, double cfl, double *dt_out, 
     if (!c || !U || !dt_out) return set_err(c, OSBLI_EINVAL, "null argument");
     hipStream_t s = as_stream(stream);
     c->last = s;
+    const unsigned long long seq = ++c->dt_seq;
     {
         Timed t(c, OSBLI_K_DT, s);
-        HIP_TRY(c, launch_fill_u64(c->red, 0ull, 1, s));
-        HIP_TRY(c, launch_dt(c->g, c->ph, c->m, U, c->red, s));
+        HIP_TRY(c, launch_dt(c->g, c->ph, c->m, U, c->red, c->dt_slot, seq, s));
     }
     unsigned long long bits = 0;
-    HIP_TRY(c, hipMemcpyAsync(&bits, c->red, sizeof bits, hipMemcpyDeviceToHost, s));
-    HIP_TRY(c, hipStreamSynchronize(s));
+    if (c->dt_slot) {
+        // the kernel's last block writes the value and then the call's number
+        // here; waiting for them takes the copy and the stream's
+        // synchronisation (some 20 us) out of every step
+        const unsigned long long *const now = &c->dt_slot->seq;
+        for (int spin = 1; __atomic_load_n(now, __ATOMIC_ACQUIRE) != seq; ++spin) {
+            if ((spin & 1023) != 0) {
+                __builtin_ia32_pause();
+                continue;
+            }
+            // an error of the stream (also: a capture, which never runs) ends the
+            // wait; a finished stream has written the words
+            const hipError_t e = hipStreamQuery(s);
+            if (e == hipErrorNotReady) {
+                (void)hipGetLastError();  // not an error: do not leave it to the next launch's check
+                continue;
+            }
+            HIP_TRY(c, e);
+            if (__atomic_load_n(now, __ATOMIC_ACQUIRE) != seq)
+                return set_err(c, OSBLI_EDEVICE, "time-step reduction left no result");
+        }
+        bits = c->dt_slot->bits;
+    } else {
+        HIP_TRY(c, hipMemcpyAsync(&bits, c->red + 2, sizeof bits, hipMemcpyDeviceToHost, s));
+        HIP_TRY(c, hipStreamSynchronize(s));
+    }
     double smax;
     memcpy(&smax, &bits, sizeof smax);
     *dt_out = smax > 0.0 ? cfl / smax : 0.0;
@@ -752,14 +823,14 @@ int osbli_sensor_stats(osbli_ctx *c, int64_t *smooth, int64_t *total) {
     if (!c || !smooth || !total) return set_err(c, OSBLI_EINVAL, "null argument");
     if (!c->p.sensor || !c->sensor_ready) return set_err(c, OSBLI_EINVAL, "sensor weights not set");
     hipStream_t s = c->last;
-    HIP_TRY(c, launch_fill_u64(c->red + 1, 0ull, 1, s));
+    HIP_TRY(c, launch_fill_u64(c->red + 3, 0ull, 1, s));
     int64_t tot = 0;
     for (int d = 0; d < c->g.nd; ++d) {
-        HIP_TRY(c, launch_count_u8(c->mask[d], iface_count(c->g, d), c->red + 1, s));
+        HIP_TRY(c, launch_count_u8(c->mask[d], iface_count(c->g, d), c->red + 3, s));
         tot += iface_count(c->g, d);
     }
     unsigned long long cnt = 0;
-    HIP_TRY(c, hipMemcpyAsync(&cnt, c->red + 1, sizeof cnt, hipMemcpyDeviceToHost, s));
+    HIP_TRY(c, hipMemcpyAsync(&cnt, c->red + 3, sizeof cnt, hipMemcpyDeviceToHost, s));
     HIP_TRY(c, hipStreamSynchronize(s));
     *smooth = (int64_t)cnt;
     *total = tot;
@@ -856,6 +927,7 @@ void osbli_destroy(osbli_ctx *c) {
     if (!c) return;
     resolve_profile(c);
     for (hipEvent_t e : c->prof.pool) hipEventDestroy(e);
+    give_dt_slot(c->dt_slot);
     delete c;
 }
 

@@ -164,12 +164,20 @@ hipError_t launch_finish(const Grid &g, const Phys &ph, const Metrics &m, const 
 size_t central_work_bytes(const Grid &g, bool viscous);
 hipError_t launch_central(const Grid &g, const Phys &ph, const Metrics &m, const double *U, double *Gs, void *work,
                           double *R, hipStream_t s);
-hipError_t launch_dt(const Grid &g, const Phys &ph, const Metrics &m, const double *U,
-                     unsigned long long *slot, hipStream_t s);
+// pinned host words that the dt reduction's kernel writes its result to: the
+// value, then the call's number
+struct DtSlot {
+    unsigned long long bits, seq;
+};
+// max CFL denominator into red[2] and, if host is not null, into *host; red[0]
+// and red[1] are zero before and after (zeroed once at set-up)
+constexpr int kDtBlocks = 256;  // one per CU
+hipError_t launch_dt(const Grid &g, const Phys &ph, const Metrics &m, const double *U, unsigned long long *red,
+                     DtSlot *host, unsigned long long seq, hipStream_t s);
 // one Runge-Kutta stage of an inviscid 1D or 2D problem, Uin -> Uout (ghosts
 // included), dU updated in place (stage.hpp).  It needs two copies of the
-// state in the workspace, so grids beyond 2^24 nodes (1 GB of copies) keep
-// the separate passes.
+// state in the workspace (one in the residual accumulator's place), so grids
+// beyond 2^24 nodes (0.5 GB for the other) keep the separate passes.
 constexpr int64_t kStageMaxNodes = int64_t(1) << 24;
 bool stage_supported(const Grid &g, const osbli_params &p);
 hipError_t launch_stage(const Grid &g, const Phys &ph, const Metrics &m, const osbli_params &p, const double *Uin,

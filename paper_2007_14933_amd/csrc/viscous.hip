@@ -548,30 +548,63 @@ __device__ __forceinline__ double wave_max(double v) {
     return v;
 }
 
-// dt denominator, max over nodes; positive doubles compare as unsigned 64-bit.
-// Blocks stride over z planes so that only a few hundred blocks issue the
-// final atomic (a max is order independent, so the result is deterministic).
+// dt denominator, max over nodes (a max is order independent, so the result is
+// deterministic).  Blocks of sixteen waves stride over the nodes, one per CU:
+// every block is two atomics on the same two words, some 12 ns each, which was
+// the whole time of a mid-size grid with a block per 256 nodes (1024 x 512: 27
+// us, now 11; 256^3 0.160 ms, now 0.137; two blocks per CU 0.155).  The last block to finish (red[1] counts them) hands the
+// result to red[2] and to the host's words and leaves red[0] and red[1] zero for
+// the next call, so there is no fill before and no copy after the kernel.
+constexpr int kDtThreads = 1024;
+
 template <int ND, bool GEN>
-__global__ void __launch_bounds__(256)
-k_dt(const double *__restrict__ U, Grid g, Phys ph, Metrics m, unsigned long long *slot) {
-    __shared__ double part[4];
+__global__ void __launch_bounds__(kDtThreads)
+k_dt(const double *__restrict__ U, Grid g, Phys ph, Metrics m, unsigned long long *red, DtSlot *host,
+     unsigned long long seq) {
+    __shared__ double part[kDtThreads / 64];
     double s = 0.0;
-    int64_t idx[3];
-    idx[0] = (int64_t)blockIdx.x * kBX + threadIdx.x;
-    idx[1] = (int64_t)blockIdx.y * kBY + threadIdx.y;
-    const bool inplane = idx[0] < g.n[0] && idx[1] < g.n[1];
-    for (idx[2] = blockIdx.z; inplane && idx[2] < g.n[2]; idx[2] += gridDim.z) {
-        double sn = dt_node<ND, GEN>(U, g, ph, m, idx);
-        s = fmax(s, sn);
+    const int64_t step = (int64_t)gridDim.x * kDtThreads;
+    // coordinates of the thread's first node and of its stride: the others
+    // follow by addition with carry
+    auto split = [&](int64_t ci, int64_t (&q)[3]) {
+        const int64_t r = ND > 1 ? ci / g.n[0] : 0;
+        q[0] = ci - r * g.n[0];
+        q[2] = ND == 3 ? r / g.n[1] : 0;
+        q[1] = r - q[2] * g.n[1];
+    };
+    int64_t idx[3], inc[3];
+    split((int64_t)blockIdx.x * kDtThreads + threadIdx.x, idx);
+    split(step, inc);
+    for (int64_t ci = (int64_t)blockIdx.x * kDtThreads + threadIdx.x; ci < g.nint; ci += step) {
+        s = fmax(s, dt_node<ND, GEN>(U, g, ph, m, idx));
+#pragma unroll
+        for (int d = 0; d < 3; ++d) idx[d] += inc[d];
+#pragma unroll
+        for (int d = 0; d + 1 < ND; ++d)
+            if (idx[d] >= g.n[d]) {
+                idx[d] -= g.n[d];
+                ++idx[d + 1];
+            }
     }
     s = wave_max(s);
-    const int lane = threadIdx.x & 63, wv = threadIdx.y;
-    if (lane == 0) part[wv] = s;
+    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = s;
     __syncthreads();
-    if (threadIdx.x == 0 && threadIdx.y == 0) {
-        double b = part[0];
-        for (int k = 1; k < (int)blockDim.y; ++k) b = fmax(b, part[k]);
-        atomicMax(slot, (unsigned long long)__double_as_longlong(b));
+    if (threadIdx.x >= 64) return;
+    s = wave_max(threadIdx.x < kDtThreads / 64 ? part[threadIdx.x] : 0.0);
+    if (threadIdx.x != 0) return;
+    unsigned long long bits = (unsigned long long)__double_as_longlong(s);  // positive doubles compare as integers
+    if (gridDim.x > 1) {
+        atomicMax(&red[0], bits);
+        __threadfence();
+        if (atomicAdd(&red[1], 1ull) != (unsigned long long)gridDim.x - 1) return;
+        __threadfence();
+        bits = atomicExch(&red[0], 0ull);
+        atomicExch(&red[1], 0ull);
+    }
+    red[2] = bits;
+    if (host) {
+        __hip_atomic_store(&host->bits, bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        __hip_atomic_store(&host->seq, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
     }
 }
 
@@ -656,25 +689,20 @@ hipError_t launch_finish(const Grid &g, const Phys &ph, const Metrics &m, const 
     }
 }
 
-hipError_t launch_dt(const Grid &g, const Phys &ph, const Metrics &m, const double *U, unsigned long long *slot,
-                     hipStream_t s) {
-    dim3 nb = node_grid(g);
-    const dim3 bs(kBX, kBY);
-    const unsigned plane_blocks = nb.x * nb.y;
-    unsigned gz = (1024 + plane_blocks - 1) / plane_blocks;
-    if (gz < 1) gz = 1;
-    if (gz > nb.z) gz = nb.z;
-    nb.z = gz;
+hipError_t launch_dt(const Grid &g, const Phys &ph, const Metrics &m, const double *U, unsigned long long *red,
+                     DtSlot *host, unsigned long long seq, hipStream_t s) {
+    const int64_t n = (g.nint + kDtThreads - 1) / kDtThreads;
+    const dim3 nb((unsigned)(n < kDtBlocks ? n : kDtBlocks)), bs(kDtThreads);
     const bool gen = m.general != 0;
     switch (g.nd) {
-        case 1: hipLaunchKernelGGL((k_dt<1, false>), nb, bs, 0, s, U, g, ph, m, slot); break;
+        case 1: hipLaunchKernelGGL((k_dt<1, false>), nb, bs, 0, s, U, g, ph, m, red, host, seq); break;
         case 2:
-            if (gen) hipLaunchKernelGGL((k_dt<2, true>), nb, bs, 0, s, U, g, ph, m, slot);
-            else hipLaunchKernelGGL((k_dt<2, false>), nb, bs, 0, s, U, g, ph, m, slot);
+            if (gen) hipLaunchKernelGGL((k_dt<2, true>), nb, bs, 0, s, U, g, ph, m, red, host, seq);
+            else hipLaunchKernelGGL((k_dt<2, false>), nb, bs, 0, s, U, g, ph, m, red, host, seq);
             break;
         default:
-            if (gen) hipLaunchKernelGGL((k_dt<3, true>), nb, bs, 0, s, U, g, ph, m, slot);
-            else hipLaunchKernelGGL((k_dt<3, false>), nb, bs, 0, s, U, g, ph, m, slot);
+            if (gen) hipLaunchKernelGGL((k_dt<3, true>), nb, bs, 0, s, U, g, ph, m, red, host, seq);
+            else hipLaunchKernelGGL((k_dt<3, false>), nb, bs, 0, s, U, g, ph, m, red, host, seq);
     }
     return hipGetLastError();
 }
