@@ -107,8 +107,8 @@ enum osbli_scheme {
  *              + sum_b (d_b kappa d_b T + kappa d_bb T),
  * pure second derivatives with the printed second-derivative operator and
  * its one-sided closures, mixed ones as first derivatives of first
- * derivatives.  Two storage strategies (section 6.1): StoreSome (default;
- * only the velocity gradients are stored, in the workspace) and store-all
+ * derivatives.  Two storage strategies (section 6.1): StoreSome (default; at
+ * most the velocity gradients are stored, in the workspace) and store-all
  * (osbli_central_store_all). */
 
 /* Low-storage (2N) Runge-Kutta schemes of section 2.7,

@@ -32,10 +32,10 @@ FLAGS = [
 NO_CONTRACT = {"sensor.hip"}
 
 # translation units built without loop strength reduction: in the z-marching
-# viscous kernel it turns every address stream of the march into a 64-bit
-# induction variable of its own, which spills the registers the loads issued
-# ahead need
-NO_LSR = {"viscous.hip"}
+# viscous and central kernels it turns every address stream of the march into a
+# 64-bit induction variable of its own, which spills the registers the loads
+# issued ahead need
+NO_LSR = {"viscous.hip", "central.hip"}
 
 
 def _compile(src: str) -> str:

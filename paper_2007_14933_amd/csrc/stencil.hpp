@@ -57,4 +57,32 @@ inline dim3 node_grid(const Grid &g) {
     return dim3((unsigned)((g.n[0] + kBX - 1) / kBX), (unsigned)((g.n[1] + kBY - 1) / kBY), (unsigned)g.n[2]);
 }
 
+// Tile placement: workgroups go to the eight XCDs (each with its own L2) in
+// turn, so a 1D grid of 8 * per blocks is used and the linear block id b is
+// remapped to the tile (b % 8) * per + b / 8: each XCD then owns one
+// contiguous run of tiles (x fastest, then y, then z), and the stencil
+// neighbours that adjacent tiles share are read through one L2.
+constexpr int kXcds = 8;
+
+// Planes per block of the z-marching passes: a block of `c` + planes steps (the
+// c steps fill its register window) runs on one of `slots` places, so the run
+// takes ceil(blocks / slots) (planes + c) steps; the shortest such run of at
+// most `most` planes is taken.  Fixed runs of 32 (fluxes) and 16 planes (finish)
+// gave a 64^3 grid 16 and 64 blocks, 70 and 40 us; runs of two planes fill the
+// chip.  Large grids keep the longest runs (8 to 64 planes measured alike).
+inline int plane_run(int64_t tiles, int64_t Nz, int most, int slots) {
+    constexpr int c = 3;
+    int best = most;
+    int64_t cost = INT64_MAX;
+    for (int p = most; p >= 2; --p) {
+        const int64_t blocks = tiles * ((Nz + p - 1) / p);
+        const int64_t t = (blocks + slots - 1) / slots * (p + c);
+        if (t < cost) {
+            cost = t;
+            best = p;
+        }
+    }
+    return best;
+}
+
 }  // namespace osbli

@@ -16,13 +16,6 @@
 namespace osbli {
 namespace {
 
-// Tile placement: workgroups go to the eight XCDs (each with its own L2) in
-// turn, so a 1D grid of 8 * per blocks is used and the linear block id b is
-// remapped to the tile (b % 8) * per + b / 8: each XCD then owns one
-// contiguous run of tiles (x fastest, then y, then z), and the stencil
-// neighbours that adjacent tiles share are read through one L2.
-constexpr int kXcds = 8;
-
 struct NodeTiles {
     int tx, ty, nt, per;  // tiles along x, along y, in all; tiles per XCD
 };
@@ -177,27 +170,6 @@ k_visc_flux(const double *__restrict__ U, double *__restrict__ G, Grid g, Phys p
 #pragma unroll
     for (int kk = 0; kk < ND; ++kk) dk_global<ND>(U, e0, cs, ph, g, kk, idx[kk], Dk[kk]);
     visc_store<ND, GEN>(phi0, Dk, G, g, ph, m, idx, ci, e0);
-}
-
-// Planes per block of the z-marching passes: a block of `c` + planes steps (the
-// c steps fill its register window) runs on one of `slots` places, so the run
-// takes ceil(blocks / slots) (planes + c) steps; the shortest such run of at
-// most `most` planes is taken.  Fixed runs of 32 (fluxes) and 16 planes (finish)
-// gave a 64^3 grid 16 and 64 blocks, 70 and 40 us; runs of two planes fill the
-// chip.  Large grids keep the longest runs (8 to 64 planes measured alike).
-inline int plane_run(int64_t tiles, int64_t Nz, int most, int slots) {
-    constexpr int c = 3;
-    int best = most;
-    int64_t cost = INT64_MAX;
-    for (int p = most; p >= 2; --p) {
-        const int64_t blocks = tiles * ((Nz + p - 1) / p);
-        const int64_t t = (blocks + slots - 1) / slots * (p + c);
-        if (t < cost) {
-            cost = t;
-            best = p;
-        }
-    }
-    return best;
 }
 
 // 3D separable meshes: a block owns a kZX x kZY tile of (x, y) columns and

@@ -123,3 +123,24 @@ def test_time_step_reduction(n, general):
         want = 0.5 / rate.max()
         got = s.compute_dt(0.5)
         assert abs(got - want) <= 1e-12 * want, (got, want)
+
+
+@pytest.mark.parametrize("sutherland", [0, 1])
+@pytest.mark.parametrize("Re", [0.0, 300.0])
+@pytest.mark.parametrize("ends", ["periodic", "open", "mixed"])
+@pytest.mark.parametrize("n", [(32, 8, 6), (33, 9, 7), (31, 7, 12), (70, 18, 37)])
+def test_central_z_march(n, ends, Re, sutherland):
+    """The z-marching central residual at the edges of its 32 x 8 tiles and its
+    runs of planes, with the node passes at the ends: two steps against the
+    oracle at the run bound 1e-11."""
+    from paper_2007_14933_amd import inputs as I
+    from parity_util import gpu_run, normwise_rel, oracle_run
+    if sutherland and Re == 0.0:
+        pytest.skip("no viscosity")
+    prob = I.smooth_random(3, n, seed=n[0], amp=0.05, Re=Re, M=0.5).with_(scheme=I.CENTRAL4, sutherland=sutherland)
+    bc = {"periodic": ((0, 0),) * 3, "open": ((1, 1),) * 3, "mixed": ((0, 0), (1, 1), (0, 0))}[ends]
+    prob = prob.with_(bc=bc)
+    Ug, tg, _ = gpu_run(prob, 2)
+    Uo, to = oracle_run(prob, 2)
+    err = normwise_rel(I.interior_view(3, Ug), I.interior_view(3, Uo))
+    assert abs(tg - to) <= 1e-12 * to and err.max() <= 1e-11, err
