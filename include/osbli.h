@@ -257,7 +257,7 @@ int osbli_check(osbli_ctx *ctx);
 
 /* Launch shape of the convective sweeps (not part of the method; results do
  * not depend on it): seg[d] nodes per wave segment along direction d, 0 for
- * the default rule (about 2^18 lanes per sweep, at least 8 nodes). */
+ * the default rule (the shortest estimated time). */
 int osbli_set_sweep_segments(osbli_ctx *ctx, const int64_t *seg);
 
 /* Last error message of the context (never NULL). */

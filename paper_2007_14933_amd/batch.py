@@ -35,7 +35,7 @@ GRID_CANDIDATES = (512, 1024, 2048, 4096, 8192)  # workgroups per persistent swe
 
 
 def default_seg(n_d, lines):
-    """The single-grid launch's segment rule (about 2^18 threads per sweep)."""
+    """The library's default segment of a batched sweep (about 2^18 threads)."""
     target = 1 << 18
     seg = max(8, -(-n_d * lines // target))
     return min(seg, n_d)

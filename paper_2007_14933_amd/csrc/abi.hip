@@ -979,7 +979,7 @@ int bset_err(osbli_batch *b, int code, const char *fmt, ...) {
 constexpr int kTables = 9;
 size_t batch_table_bytes(int P) { return align256(sizeof(int64_t) * kTables * (size_t)(P + 1)); }
 
-// default segment length of a sweep (the single-grid rule)
+// default segment length of a sweep
 int64_t default_seg(const Grid &g, int d) {
     const int o1 = d == 0 ? 1 : 0, o2 = d == 2 ? 1 : 2;
     return default_segment(g.n[d], g.n[o1] * g.n[o2]);

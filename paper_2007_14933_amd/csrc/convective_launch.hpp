@@ -25,7 +25,7 @@ hipError_t launch_one(const Grid &g, const Phys &ph, const Metrics &m, const dou
                            g, ph, m, totalJ, first, flags, mask);
         return hipGetLastError();
     }
-    int64_t seg = seg_req > 0 ? seg_req : default_segment(N, lines);
+    int64_t seg = seg_req > 0 ? seg_req : march_segment(N, lines, GEN);
     if (seg > N) seg = N;
     const int64_t nseg = (N + seg - 1) / seg;
     const int64_t waves = ((lines + 63) / 64) * nseg;

@@ -196,7 +196,7 @@ hipError_t launch_wz7_dir(const Grid &g, const Phys &ph, const Metrics &m, const
     const int64_t lines = g.n[O1] * g.n[O2];
     const int64_t N = g.n[DIR];
     if (DIR != 0) {
-        const int64_t seg = default_segment(N, lines);
+        const int64_t seg = march_segment(N, lines, false);
         const int64_t nseg = (N + seg - 1) / seg;
         const int64_t waves = ((lines + 63) / 64) * nseg;
         const int64_t nb = (waves + kWaves - 1) / kWaves;

@@ -125,13 +125,37 @@ hipError_t launch_metrics_general(const Grid &g, const double *coords, double *s
 hipError_t launch_bc(const Grid &g, const Phys &ph, const osbli_params &p, double *U, hipStream_t s);
 // one convective sweep along dir; first != 0 stores R, otherwise accumulates;
 // mask (may be null): routing mask of the direction's interfaces
-// segment length (nodes per wave along the sweep) of the single-grid rule:
-// about 2^18 lanes per launch, at least 8 nodes per segment
+// segment length (nodes per wave along the sweep) of a batch's problems by
+// default: about 2^18 lanes per problem, at least 8 nodes per segment
 inline int64_t default_segment(int64_t N, int64_t lines) {
     const int64_t target = int64_t(1) << 18;
     int64_t seg = (N * lines + target - 1) / target;
     if (seg < 8) seg = 8;
     return seg < N ? seg : N;
+}
+
+// Segment length of a marching sweep over one grid: the one with the shortest
+// estimated time.  A wave marches its segment and one more interface; one wave
+// alone on a SIMD takes 2.8 us per interface, two together 4.9 (measured; a
+// single round of pairs 5 % more), so the waves run in rounds of 2048 (general
+// meshes: one wave per SIMD, 1024).  The batch's rule above (segments of 8
+// nodes or longer) left a 64^3 grid with 512 waves of nine interfaces: 35 us
+// per sweep, 24 with segments of four.
+inline int64_t march_segment(int64_t N, int64_t lines, bool general) {
+    const int64_t wl = (lines + 63) / 64, slots = general ? 1024 : 2048;
+    int64_t best = 1;
+    double cost = 0.0;
+    for (int64_t seg = N < 128 ? N : 128; seg >= 1; --seg) {
+        const int64_t nseg = (N + seg - 1) / seg, W = wl * nseg, full = W / slots, rest = W - full * slots;
+        const double len = (W > slots ? (double)N / (double)nseg : (double)seg) + 1.0;
+        const double pair = general ? 2.8 : (W > 2048 ? 4.9 : 5.15);
+        const double t = len * (pair * (double)full + (rest == 0 ? 0.0 : (rest <= 1024 ? 2.8 : pair)));
+        if (cost == 0.0 || t < cost) {
+            cost = t;
+            best = seg;
+        }
+    }
+    return best;
 }
 
 // seg_req > 0 overrides the segment length of the sweep

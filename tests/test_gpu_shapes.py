@@ -144,3 +144,24 @@ def test_central_z_march(n, ends, Re, sutherland):
     Uo, to = oracle_run(prob, 2)
     err = normwise_rel(I.interior_view(3, Ug), I.interior_view(3, Uo))
     assert abs(tg - to) <= 1e-12 * to and err.max() <= 1e-11, err
+
+
+@pytest.mark.parametrize("general", [False, True])
+@pytest.mark.parametrize("n", [(64, 7, 9), (66, 33, 20), (70, 131)])
+def test_march_segments(n, general):
+    """Segments of the marching sweeps from one node to the whole line, the
+    remainder of a last segment among them, give the default's bits."""
+    import torch
+    from paper_2007_14933_amd import inputs as I
+    from paper_2007_14933_amd.solver import Solver
+    nd = len(n)
+    prob = I.smooth_random(nd, n + (1,) * (3 - nd), seed=9, amp=0.2)
+    if general:
+        prob = prob.with_(coords1d=None, coords_full=prob.coords)
+    s = Solver(prob)
+    s.apply_bc()
+    ref = s.residual().clone()
+    for seg in (1, 2, 3, 5, 64, 200):
+        s.set_sweep_segments([seg if general else 0, seg, seg])
+        assert torch.equal(s.residual(), ref), seg
+    s.check()
