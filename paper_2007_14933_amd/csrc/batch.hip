@@ -319,14 +319,11 @@ hipError_t launch_batch_stage(const BProb *pr, BState *st, const BatchTables &T,
 }
 
 void batch_stage_tiles(BProb *pr, int P) {
-    std::vector<const Grid *> g(P);
-    std::vector<StageTiles> t(P);
-    for (int p = 0; p < P; ++p) g[p] = &pr[p].g;
-    stage_tiles(g.data(), P, t.data());
     for (int p = 0; p < P; ++p) {
-        pr[p].tx = t[p].tx;
-        pr[p].ty = t[p].ty;
-        pr[p].ntx = (int)t[p].nx;
+        const StageTiles t = stage_tiles(pr[p].g);
+        pr[p].tx = t.tx;
+        pr[p].ty = t.ty;
+        pr[p].ntx = (int)t.nx;
     }
 }
 

@@ -12,9 +12,13 @@
 // differences, its update and its ghost copies from LDS.  A block reads nodes
 // that its neighbours own, so the new state goes to another buffer.
 //
-// Tiles of at most 32 x 11 nodes: 33 x 11 = 363 interfaces along x and 32 x 12
-// = 384 along y are six wave tasks each (1.09 times the interfaces of a whole
-// grid); 49 KB of LDS and 168 registers, so three blocks per CU.
+// Tiles of at most 32 x 7 nodes: 33 x 7 interfaces along x and 32 x 8 along y,
+// one per thread in either direction (1.09 times the interfaces of a whole
+// grid, 1.14 times the lanes); 36 KB of LDS and 168 registers, so three blocks
+// per CU.  Tall tiles repeat fewer interfaces but leave waves idle: per stage
+// of 1024 x 1024, 512 x 512 and 256 x 256 seven rows take 81, 31 and 18 us,
+// eleven (six wave tasks on four waves) 92, 34 and 21, fifteen (eight tasks
+// on four waves, two blocks per CU) 96, 40 and 22, five 98, 36 and 17.
 // Bound: FP64 VALU, as the sweeps.
 #pragma once
 
@@ -25,12 +29,12 @@ namespace cf {
 
 template <int ND>
 struct StageTile {
-    static constexpr int X = ND == 1 ? 255 : 32, Y = ND == 1 ? 1 : 11;  // largest tile
-    static constexpr int HY = ND == 1 ? 0 : kGhost;                      // halo rows per side
+    static constexpr int X = ND == 1 ? 255 : 32, Y = ND == 1 ? 1 : 7;  // largest tile
+    static constexpr int HY = ND == 1 ? 0 : kGhost;                     // halo rows per side
     static constexpr int PX = X + 2 * kGhost, PY = Y + 2 * HY;
-    static constexpr int F = ND == 1 ? X + 1 : X * (Y + 1);              // interface slots of one direction
+    static constexpr int F = ND == 1 ? X + 1 : X * (Y + 1);             // interface slots of one direction
     static_assert(ND == 1 || (X + 1) * Y <= F, "both directions fit the flux slots");
-    static constexpr int NPT = (X * Y + 255) / 256;                      // nodes per thread
+    static_assert(F <= 256, "one interface per thread and direction, one node per thread");
 };
 
 template <int ND>
@@ -143,9 +147,8 @@ __device__ __forceinline__ void stage_tile(const double *__restrict__ Uin, doubl
         auto ml = [&](int o) { return (p + o < -1 || p + o > N - 1) ? true : mk[at + o * st] != 0; };
         return ml(0) && (ph.dilate < 1 || (ml(-1) && ml(1))) && (ph.dilate < 2 || (ml(-2) && ml(2)));
     };
-    const int nfx = (nx + 1) * ny;
-    for (int e = tid; e < nfx; e += 256) {
-        const int r = e / (nx + 1), c = e - r * (nx + 1);
+    if (tid < (nx + 1) * ny) {
+        const int r = tid / (nx + 1), c = tid - r * (nx + 1);
         bool cheap = false;
         if (ROUTE) {
             const int64_t p = x0 + c - 1;
@@ -154,54 +157,45 @@ __device__ __forceinline__ void stage_tile(const double *__restrict__ Uin, doubl
         double F[NC];
         stage_flux<ND, 0, SCHEME, MIX, ROUTE, XJOINT>(sm, (r + T::HY) * T::PX + c, 1, ph, cheap, F);
 #pragma unroll
-        for (int k = 0; k < NC; ++k) sm.fl[k][e] = F[k];
+        for (int k = 0; k < NC; ++k) sm.fl[k][tid] = F[k];
     }
     __syncthreads();
-    // the thread's nodes: their x flux differences, then the flux slots are free
-    double R[T::NPT][NC];
-#pragma unroll
-    for (int m = 0; m < T::NPT; ++m) {
-        const int e = tid + 256 * m;
-        if (e < nx * ny) {
-            const int r = e / nx, c = e - r * nx, f = r * (nx + 1) + c;
-            flux_difference<NC>(sm, f, f + 1, invh[0][x0 + c], R[m]);
-        }
+    // the thread's node: its x flux difference, then the flux slots are free
+    const int r = tid / nx, c = tid - r * nx;
+    const int64_t x = x0 + c, y = y0 + r;
+    double R[NC];
+    if (r < ny) {
+        const int f = r * (nx + 1) + c;
+        flux_difference<NC>(sm, f, f + 1, invh[0][x], R);
     }
     if constexpr (ND == 2) {
         __syncthreads();
-        const int nfy = nx * (ny + 1);
-        for (int e = tid; e < nfy; e += 256) {
-            const int r = e / nx, c = e - r * nx;
+        if (r <= ny) {
             bool cheap = false;
             if (ROUTE) {
-                const int64_t p = y0 + r - 1;
-                cheap = routed(mask[1], (p + 1) * g.n[0] + x0 + c, g.n[0], p, g.n[1]);
+                const int64_t p = y - 1;
+                cheap = routed(mask[1], y * g.n[0] + x, g.n[0], p, g.n[1]);
             }
             double F[NC];
             stage_flux<ND, DY, SCHEME, MIX, ROUTE, true>(sm, r * T::PX + c + kGhost, T::PX, ph, cheap, F);
 #pragma unroll
-            for (int k = 0; k < NC; ++k) sm.fl[k][e] = F[k];
+            for (int k = 0; k < NC; ++k) sm.fl[k][tid] = F[k];
         }
         __syncthreads();
     }
-#pragma unroll
-    for (int m = 0; m < T::NPT; ++m) {
-        const int e = tid + 256 * m;
-        if (e >= nx * ny) continue;
-        const int r = e / nx, c = e - r * nx;
-        const int64_t x = x0 + c, y = y0 + r;
+    if (r < ny) {
         if constexpr (ND == 2) {
             double v[NC];
-            flux_difference<NC>(sm, e, e + nx, invh[1][y], v);
+            flux_difference<NC>(sm, tid, tid + nx, invh[1][y], v);
 #pragma unroll
-            for (int k = 0; k < NC; ++k) R[m][k] += v[k];
+            for (int k = 0; k < NC; ++k) R[k] += v[k];
         }
         const int64_t ci = int_index(g, x, y, 0);
         const int s = (r + T::HY) * T::PX + c + kGhost;
         double u[NC];
 #pragma unroll
         for (int k = 0; k < NC; ++k) {
-            const double du = (rs.first ? 0.0 : rs.A * dU[k * g.nint + ci]) + dt * R[m][k];
+            const double du = (rs.first ? 0.0 : rs.A * dU[k * g.nint + ci]) + dt * R[k];
             if (!rs.last) dU[k * g.nint + ci] = du;
             u[k] = sm.pt[k][s] + rs.B * du;
         }
@@ -224,60 +218,24 @@ __device__ __forceinline__ void stage_tile(const double *__restrict__ Uin, doubl
 
 }  // namespace cf
 
-// Tiling of one grid: tx x ty nodes per tile, nx x ny tiles.  The columns are
-// split evenly; the rows per tile are those with the shortest estimated time.
-// A tile is t wave tasks per direction (64 interfaces each) on the four SIMDs
-// of a CU that b tiles share: 2.8 us per task with one wave per SIMD, 2.45 per
-// task and SIMD with more (measured on the sweeps), and about 3 us for a
-// tile's points, update and barriers.  Small grids so get short tiles on every
-// CU (256 x 256: 22 us per stage with tiles of nine rows, 15 with four).
-constexpr int kStageSlots = 3;  // tiles per CU (51 KB of LDS, 168 registers)
+constexpr int kStageSlots = 3;  // tiles per CU
 
+// Tiling of one grid: nx x ny tiles of at most tx x ty nodes, split evenly.
 struct StageTiles {
     int tx, ty;
     int64_t nx, ny;
 };
 
-// tilings of `count` grids that run in one launch (the rows per tile are common)
-inline void stage_tiles(const Grid *const *g, int count, StageTiles *t) {
-    const bool one = g[0]->nd == 1;
-    const int mx = one ? cf::StageTile<1>::X : cf::StageTile<2>::X, my = one ? 1 : cf::StageTile<2>::Y;
-    int wide = 0;
-    for (int i = 0; i < count; ++i) {
-        t[i].nx = (g[i]->n[0] + mx - 1) / mx;
-        t[i].tx = (int)((g[i]->n[0] + t[i].nx - 1) / t[i].nx);
-        t[i].nx = (g[i]->n[0] + t[i].tx - 1) / t[i].tx;
-        wide = t[i].tx > wide ? t[i].tx : wide;
-    }
-    int rows = 1;
-    double best = 0.0;
-    for (int y = my; y >= 1; --y) {
-        int64_t blocks = 0;
-        for (int i = 0; i < count; ++i) blocks += t[i].nx * ((g[i]->n[1] + y - 1) / y);
-        const int64_t share = (blocks + 255) / 256 < kStageSlots ? (blocks + 255) / 256 : kStageSlots;
-        const int64_t rounds = (blocks + 256 * share - 1) / (256 * share);
-        auto phase = [&](int items) {
-            const int tasks = (items + 63) / 64;
-            if (share == 1) return 2.8 * ((tasks + 3) / 4);
-            const double w = 2.45 * tasks * share / 4.0;
-            return w > 2.8 ? w : 2.8;
-        };
-        const double cost = rounds * (phase((wide + 1) * y) + phase(wide * (y + 1)) + 3.0);
-        if (best == 0.0 || cost < best) {
-            best = cost;
-            rows = y;
-        }
-    }
-    for (int i = 0; i < count; ++i) {
-        t[i].ty = rows < g[i]->n[1] ? rows : (int)g[i]->n[1];
-        t[i].ny = (g[i]->n[1] + t[i].ty - 1) / t[i].ty;
-    }
-}
-
 inline StageTiles stage_tiles(const Grid &g) {
+    const bool one = g.nd == 1;
+    const int mx = one ? cf::StageTile<1>::X : cf::StageTile<2>::X, my = one ? 1 : cf::StageTile<2>::Y;
     StageTiles t;
-    const Grid *const p = &g;
-    stage_tiles(&p, 1, &t);
+    t.nx = (g.n[0] + mx - 1) / mx;
+    t.tx = (int)((g.n[0] + t.nx - 1) / t.nx);
+    t.nx = (g.n[0] + t.tx - 1) / t.tx;
+    t.ny = (g.n[1] + my - 1) / my;
+    t.ty = (int)((g.n[1] + t.ny - 1) / t.ny);
+    t.ny = (g.n[1] + t.ty - 1) / t.ty;
     return t;
 }
 
