@@ -162,7 +162,7 @@ typedef struct osbli_ctx osbli_ctx;
 /* Bytes of device workspace osbli_init_grid needs for these parameters
  * (metrics, residual accumulator, viscous fluxes, reduction slots and the
  * coordinate staging used once at set-up, and the two state copies of
- * osbli_rk_step's one-pass stage where it applies).  Pure host function;
+ * osbli_rk_step where it uses them).  Pure host function;
  * returns 0 for invalid parameters. */
 size_t osbli_workspace_bytes(const osbli_params *p);
 
@@ -203,8 +203,12 @@ int osbli_rk_substep(osbli_ctx *ctx, int stage, double dt, double *U, double *dU
  * osbli_apply_bc stage by stage, to rounding).  U's ghosts must be valid.
  * Inviscid 1D and 2D problems on separable meshes with periodic or
  * extrapolated ends (six-point schemes; FP64 or routed forms; at most 2^24
- * nodes) take one launch per stage through two state copies in the workspace,
- * every other problem the separate calls. */
+ * nodes) take one launch per stage through two state copies in the workspace.
+ * 3D problems on separable meshes without Dirichlet sides (at most 2^28 nodes
+ * with ghosts) go through two copies as well, which lets one pass read the
+ * neighbours' states and update: viscous ones periodic along z, after the
+ * sweeps, and the central scheme on fully periodic grids.  Every other problem
+ * takes the separate calls. */
 int osbli_rk_step(osbli_ctx *ctx, double dt, double *U, double *dU, void *stream);
 
 /* Number of substages per step of the context's Runge-Kutta scheme (3 or

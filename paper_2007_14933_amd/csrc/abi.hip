@@ -124,7 +124,7 @@ struct osbli_ctx {
     int nstages;           // Runge-Kutta substages per step (3 or 5)
     double rkA[5], rkB[5]; // their 2N coefficients
     void *cwork;           // central path: the store-all strategy's work arrays (null: StoreSome)
-    double *W[2];          // state copies of the one-pass stage (null: separate passes)
+    double *W[2];          // state copies of whole steps (null: separate passes)
     DtSlot *dt_slot;       // the dt reduction's host words (null: copy back)
     unsigned long long dt_seq;
     char err[320];
@@ -266,11 +266,15 @@ Layout make_layout(const osbli_params *p, const Grid &g) {
         stage = align256(sizeof(double) * (g.n[0] + g.n[1] + g.n[2]));
     L.stage = off;
     size_t region = racc + gsz > stage ? racc + gsz : stage;
-    // the one-pass stage's state copies: it uses no residual accumulator, so the
-    // first shares this region
-    const size_t copy = stage_supported(g, *p) ? align256(sizeof(double) * g.nc * g.enpts) : 0;
-    if (copy > region) region = copy;
-    L.W[0] = L.Racc;
+    // state copies of whole steps, in the place of what these do not use: the
+    // one-pass stage no residual accumulator (its other copy lies at the end),
+    // the 3D viscous step no stored fluxes, the 3D central one neither residual
+    // nor gradients
+    const bool one = stage_supported(g, *p), march = march_supported(g, *p);
+    const size_t copy = one || march ? align256(sizeof(double) * g.nc * g.enpts) : 0;
+    L.W[0] = march && p->scheme != OSBLI_CENTRAL4 ? L.G : L.Racc;
+    const size_t copies = L.W[0] - L.Racc + (march ? 2 : 1) * copy;
+    if (copy && copies > region) region = copies;
     off += region;
     for (int d = 0; d < 3; ++d) {
         L.mask[d] = off;
@@ -278,8 +282,8 @@ Layout make_layout(const osbli_params *p, const Grid &g) {
     }
     L.wts = off;
     if (p->sensor) off += align256(2 * 1441);
-    L.W[1] = off;
-    off += copy;
+    L.W[1] = march ? L.W[0] + copy : off;
+    if (one) off += copy;
     L.total = off;
     return L;
 }
@@ -519,7 +523,9 @@ int osbli_init_grid(osbli_ctx **out, const osbli_params *p, const double *x, con
     for (int d = 0; d < 3; ++d) c->mask[d] = reinterpret_cast<uint8_t *>(c->ws + c->L.mask[d]);
     c->wts = reinterpret_cast<uint16_t *>(c->ws + c->L.wts);
     for (int k = 0; k < 2; ++k)
-        c->W[k] = stage_supported(c->g, *p) ? reinterpret_cast<double *>(c->ws + c->L.W[k]) : nullptr;
+        c->W[k] = stage_supported(c->g, *p) || march_supported(c->g, *p)
+                      ? reinterpret_cast<double *>(c->ws + c->L.W[k])
+                      : nullptr;
     c->sensor_ready = 0;
     c->sensor_every = 0;
     c->zcut = 0.0f;
@@ -641,7 +647,8 @@ int osbli_rk_step(osbli_ctx *c, double dt, double *U, double *dU, void *stream) 
     if (!c || !U || !dU) return set_err(c, OSBLI_EINVAL, "null argument");
     if ((void *)U == (void *)dU) return set_err(c, OSBLI_EINVAL, "dU aliases U");
     const bool route = c->p.sensor && c->sensor_ready;
-    if (!c->W[0] || (c->ph.mixed && !route)) {
+    const bool march = c->g.nd == 3, central = c->p.scheme == OSBLI_CENTRAL4;
+    if (!c->W[0] || (march ? c->nstages < 2 || (central && c->cwork) : c->ph.mixed && !route)) {
         for (int st = 0; st < c->nstages; ++st) {
             int rc = osbli_rk_substep(c, st, dt, U, dU, stream);
             if (rc == OSBLI_OK) rc = osbli_apply_bc(c, U, stream);
@@ -649,13 +656,27 @@ int osbli_rk_step(osbli_ctx *c, double dt, double *U, double *dU, void *stream) 
         }
         return OSBLI_OK;
     }
-    // one pass per stage: U -> W0 -> W1 -> .. -> U, each with its ghosts
+    // the state goes U -> W0 -> W1 -> .. -> U, each with its ghosts: in one pass
+    // per stage, or (march) with one pass after the sweeps, or for the central
+    // scheme alone
     hipStream_t s = as_stream(stream);
     c->last = s;
     const double *in = U;
     for (int st = 0; st < c->nstages; ++st) {
         double *out = st == c->nstages - 1 ? U : c->W[st & 1];
         if (route && (st == 0 || c->sensor_every)) HIP_TRY(c, sensor_all(c, in, s));
+        if (march) {
+            if (!central) HIP_TRY(c, convective_all(c, in, c->Racc, s));
+            {
+                Timed t(c, central ? OSBLI_K_CENTRAL : OSBLI_K_FINISH, s);
+                HIP_TRY(c, central ? launch_central_step(c->g, c->ph, c->m, in, out, dU, stage_of(c, st), dt, s)
+                                   : launch_viscous_step(c->g, c->ph, c->m, in, out, c->Racc, dU, stage_of(c, st), dt, s));
+            }
+            Timed t(c, OSBLI_K_BC, s);
+            HIP_TRY(c, launch_bc(c->g, c->ph, c->p, out, s));
+            in = out;
+            continue;
+        }
         Timed t(c, OSBLI_K_STAGE, s);
         HIP_TRY(c, launch_stage(c->g, c->ph, c->m, c->p, in, out, dU, c->mask, route, stage_of(c, st), dt, c->flags, s));
         in = out;

@@ -182,6 +182,10 @@ hipError_t launch_viscous_fluxes(const Grid &g, const Phys &ph, const Metrics &m
 hipError_t launch_finish(const Grid &g, const Phys &ph, const Metrics &m, const double *Racc,
                          const double *G, double *Rout, RkStage rs, double dt, double *U, double *dU,
                          int mode, hipStream_t s);
+// 3D separable meshes, periodic along z: Uout, dU from Uin (interior nodes; the
+// state's copies must differ) with the viscous divergence added to Racc
+hipError_t launch_viscous_step(const Grid &g, const Phys &ph, const Metrics &m, const double *Uin, double *Uout,
+                               const double *Racc, double *dU, RkStage rs, double dt, hipStream_t s);
 // fourth-order central path: residual R of U (ghosts valid); Gs: velocity
 // gradients (nd^2 per node), used by the StoreSome strategy (work == null);
 // work: the store-all strategy's arrays (central_work_bytes)
@@ -193,11 +197,21 @@ hipError_t launch_central(const Grid &g, const Phys &ph, const Metrics &m, const
 struct DtSlot {
     unsigned long long bits, seq;
 };
+// fully periodic 3D central path: Uout, dU from Uin without a stored residual
+hipError_t launch_central_step(const Grid &g, const Phys &ph, const Metrics &m, const double *Uin, double *Uout,
+                               double *dU, RkStage rs, double dt, hipStream_t s);
 // max CFL denominator into red[2] and, if host is not null, into *host; red[0]
 // and red[1] are zero before and after (zeroed once at set-up)
 constexpr int kDtBlocks = 256;  // one per CU
 hipError_t launch_dt(const Grid &g, const Phys &ph, const Metrics &m, const double *U, unsigned long long *red,
                      DtSlot *host, unsigned long long seq, hipStream_t s);
+// whether whole steps of a 3D problem write each stage's state to a copy
+// (launch_viscous_step, launch_central_step): separable meshes; the boundary
+// conditions must set every ghost (Dirichlet data lives in the caller's ghosts
+// only); up to 2^28 nodes with ghosts (32-bit byte offsets), where the copies, which take the stored fluxes' or
+// gradients' place, add at most 5 GB to the workspace
+constexpr int64_t kMarchMaxNodes = int64_t(1) << 28;
+bool march_supported(const Grid &g, const osbli_params &p);
 // one Runge-Kutta stage of an inviscid 1D or 2D problem, Uin -> Uout (ghosts
 // included), dU updated in place (stage.hpp).  It needs two copies of the
 // state in the workspace (one in the residual accumulator's place), so grids

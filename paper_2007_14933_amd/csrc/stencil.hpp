@@ -42,6 +42,21 @@ __device__ __forceinline__ double d2line(const At &at, int64_t p, int64_t N, boo
     return (-20.0 * d1 + 6.0 * d2 + 4.0 * d3 - d4) * (1.0 / 12.0);
 }
 
+// value at a 32-bit byte offset from a block-uniform base
+__device__ __forceinline__ double &at32(double *base, unsigned off) {
+    return *reinterpret_cast<double *>(reinterpret_cast<char *>(base) + off);
+}
+__device__ __forceinline__ const double &at32(const double *base, unsigned off) {
+    return *reinterpret_cast<const double *>(reinterpret_cast<const char *>(base) + off);
+}
+
+// element at a block-uniform index of an array that the kernel does not write,
+// through the scalar cache (a vector load is waited for together with every
+// vector load requested before it, such as the next plane's)
+__device__ __forceinline__ double uniform_at(const double *p, int64_t i) {
+    return *reinterpret_cast<const __attribute__((address_space(4))) double *>(reinterpret_cast<uintptr_t>(p + i));
+}
+
 // pointwise kernels: blocks of 64 x 4 threads over (i, j) of one k plane
 constexpr int kBX = 64, kBY = 4;
 

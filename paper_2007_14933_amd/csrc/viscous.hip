@@ -10,6 +10,8 @@
 // stress once, see gslot).
 // Pass 2 (k_finish): per node, J sum_k D_k G_k added to the convective
 // residual, then either stored (residual call) or folded into the RK update.
+// Whole steps of 3D problems that are periodic along z take both in one pass
+// (k_visc_step).
 #include "point.hpp"
 #include "stencil.hpp"
 
@@ -95,6 +97,31 @@ __device__ __forceinline__ void dk_global(const double *__restrict__ U, int64_t 
     }
 }
 
+// stress tensor and heat flux of one node from its primitives and gradients:
+// Fv[b] = (tau_b., u . tau_b - q_b)
+template <int ND>
+__device__ __forceinline__ void visc_node(const double (&phi0)[ND + 1], const double (&grad)[ND + 1][ND],
+                                          const Phys &ph, double (&Fv)[ND][ND + 1]) {
+    const double T = phi0[ND];
+    const double mu = viscosity(ph, T);
+    double divu = 0.0;
+#pragma unroll
+    for (int a = 0; a < ND; ++a) divu += grad[a][a];
+    const double mre = mu * ph.mu_re;
+#pragma unroll
+    for (int b = 0; b < ND; ++b) {
+        double work = 0.0;
+#pragma unroll
+        for (int a = 0; a < ND; ++a) {
+            double tab = mre * (grad[a][b] + grad[b][a] - (a == b ? (2.0 / 3.0) * divu : 0.0));
+            Fv[b][a] = tab;
+            work += phi0[a] * tab;
+        }
+        const double qb = -mu * ph.kheat * grad[ND][b];
+        Fv[b][ND] = work - qb;
+    }
+}
+
 // gradients from D_k, stress tensor, heat flux and the stored contravariant
 // viscous fluxes G_k = S_k . Fv of one node
 template <int ND, bool GEN>
@@ -119,25 +146,8 @@ __device__ __forceinline__ void visc_store(const double (&phi0)[ND + 1], const d
                 grad[v][j] = Jc * s;
             }
         }
-    const double T = phi0[ND];
-    const double mu = viscosity(ph, T);
-    double divu = 0.0;
-#pragma unroll
-    for (int a = 0; a < ND; ++a) divu += grad[a][a];
-    const double mre = mu * ph.mu_re;
     double Fv[ND][NV];
-#pragma unroll
-    for (int b = 0; b < ND; ++b) {
-        double work = 0.0;
-#pragma unroll
-        for (int a = 0; a < ND; ++a) {
-            double tab = mre * (grad[a][b] + grad[b][a] - (a == b ? (2.0 / 3.0) * divu : 0.0));
-            Fv[b][a] = tab;
-            work += phi0[a] * tab;
-        }
-        const double qb = -mu * ph.kheat * grad[ND][b];
-        Fv[b][ND] = work - qb;
-    }
+    visc_node<ND>(phi0, grad, ph, Fv);
 #pragma unroll
     for (int kk = 0; kk < ND; ++kk)
 #pragma unroll
@@ -514,6 +524,268 @@ k_finish_zm(const double *__restrict__ Racc, const double *__restrict__ G, Grid 
     }
 }
 
+// ------------------------------------------------ 3D separable, whole stage
+// Viscous divergence and Runge-Kutta update in one pass, Uin -> Uout (a step
+// has its state copies, so neighbours still read the old state), for grids
+// that are periodic along z.  The two passes above write nine flux arrays and
+// read them back with their neighbours, 18 of the 48 values a node costs them;
+// here a node's fluxes never leave the CU.  256^3: 1.00 ms (0.42 + 0.89), 192^3
+// 0.41 (0.58), 96^3 0.057 (0.076), 512 x 256 x 256 with a wall and Sutherland's
+// law 2.13 (2.87), 64^3 and below as before or a little faster.
+// A block updates a tile of at most kSX x kSY columns and marches along z; its
+// threads are the tile's columns and two more either side, so that the fluxes
+// that the tile's x and y differences read are the block's own (320 of 504
+// threads update).  Each thread keeps its column's primitives at five planes
+// for the z gradients, and the divergence so far of the five planes that its
+// G_z enters (kept instead of G_z itself: 32 registers fewer); the primitives
+// of four planes (with two more nodes around) and the fluxes G_x and G_y of two
+// sit in LDS, so that one barrier a plane is enough.  While the fluxes of plane
+// c are computed, the states of plane c + 3 and what plane c - 2's update needs
+// are on their way; every load is requested after the previous plane's stores
+// and awaited a plane later.
+// Bound: LDS, VALU and loads one after the other (two waves per SIMD, in step;
+// VALU busy 25 %): without the update's traffic 0.62 ms, without the stress
+// arithmetic 0.94.  Blocks of 16 x 8 columns, two per CU, 1.07 ms (240 threads
+// for 128 columns); 28 x 12 columns 1.14.
+constexpr int kSX = 32, kSY = 10, kSEX = kSX + 4, kSEY = kSY + 4, kSPX = kSEX + 4, kSPY = kSEY + 4;
+constexpr int kSThreads = 512, kSHalo = 4 * kSEX + 4 * kSEY;
+static_assert(kSEX * kSEY <= kSThreads && kSHalo <= kSThreads, "one column and one halo position per thread");
+
+struct StepTiles {
+    int tx, ty, tz, nt, per;
+};
+
+// Runs of planes: a block's run costs its planes and about six steps (four
+// planes of fluxes more than it updates, the first loads), one block per CU.
+inline StepTiles step_tiles(const Grid &g) {
+    StepTiles T;
+    T.tx = (int)((g.n[0] + kSX - 1) / kSX);
+    T.ty = (int)((g.n[1] + kSY - 1) / kSY);
+    int64_t cost = INT64_MAX;
+    T.tz = 1;
+    for (int64_t k = 1; k <= g.n[2]; ++k) {
+        const int64_t blocks = T.tx * T.ty * k, run = (g.n[2] + k - 1) / k;
+        const int64_t t = (blocks + 255) / 256 * (run + 6);
+        if (t < cost) {
+            cost = t;
+            T.tz = (int)k;
+        }
+    }
+    T.nt = T.tx * T.ty * T.tz;
+    T.per = (T.nt + kXcds - 1) / kXcds;
+    return T;
+}
+
+// First derivative along a line from LDS.  Bounded lines: one sum over the five
+// nodes that the position's operator reads (centred, or the closure of dline) of
+// differences from the node's own value, so that constants give 0.  The weights
+// are a row of a table in LDS, read for each derivative: held in registers they
+// spill (512 x 256 x 256 with a wall: 3.1 ms), and with the closures as branches
+// per node the blocks at the ends run all of them (2.3 ms, 64 x 64 x 64 54 us;
+// this form 2.1 ms and 36 us).
+constexpr double kLineW[5][5] = {{-25.0 / 12.0, 4.0, -3.0, 4.0 / 3.0, -0.25},
+                                 {-0.25, -10.0 / 12.0, 1.5, -0.5, 1.0 / 12.0},
+                                 {1.0 / 12.0, -2.0 / 3.0, 0.0, 2.0 / 3.0, -1.0 / 12.0},
+                                 {-1.0 / 12.0, 0.5, -1.5, 10.0 / 12.0, 0.25},
+                                 {0.25, -4.0 / 3.0, 3.0, -4.0, 25.0 / 12.0}};
+
+template <bool BOUNDED>
+struct LineOp {
+    int r = 2;  // the position's row of the table, and its place among its nodes
+    __device__ __forceinline__ LineOp(int64_t p, int64_t N) {
+        // positions off the line take the centred operator (their values are unused)
+        if (BOUNDED && p >= 0 && p < N) r = p < 2 ? (int)p : (p > N - 3 ? (int)(p - (N - 5)) : 2);
+    }
+    template <int ST>
+    __device__ __forceinline__ double d1(const double *f, const double (&W)[5][5]) const {
+        if constexpr (!BOUNDED) return (2.0 / 3.0) * (f[ST] - f[-ST]) - (1.0 / 12.0) * (f[2 * ST] - f[-2 * ST]);
+        const double c = f[0];
+        const double *q = f - r * ST;
+        double s = W[r][0] * (q[0] - c);
+#pragma unroll
+        for (int k = 1; k < 5; ++k) s += W[r][k] * (q[k * ST] - c);
+        return s;
+    }
+};
+
+// BX, BY: lines along x, y are bounded.
+template <bool BX, bool BY>
+__global__ void __launch_bounds__(kSThreads, 2)
+k_visc_step(const double *__restrict__ Uin, double *__restrict__ Uout, const double *__restrict__ Racc,
+            double *__restrict__ dU, Grid g, Phys ph, Metrics m, RkStage rs, double dt, StepTiles T) {
+    constexpr int NV = 4, NC = 5;
+    __shared__ double prim[4][NV][kSPY][kSPX];
+    __shared__ double W[5][5];
+    __shared__ double flux[2][7][kSEY][kSEX];  // xx, yy, xy, xz, yz, energy x, energy y
+    const int L = (int)(blockIdx.x % kXcds) * T.per + (int)(blockIdx.x / kXcds);
+    if (L >= T.nt) return;  // block-uniform
+    const int bx = L % T.tx, by = (L / T.tx) % T.ty, bz = L / (T.tx * T.ty);
+    const int64_t Nx = g.n[0], Ny = g.n[1], Nz = g.n[2];
+    // even split: a tile is at least three columns wide where a line has several,
+    // so the one-sided closures' five nodes are the block's own
+    const int64_t x0 = bx * Nx / T.tx, x1 = (bx + 1) * Nx / T.tx;
+    const int64_t y0 = by * Ny / T.ty, y1 = (by + 1) * Ny / T.ty;
+    const int64_t z0 = bz * Nz / T.tz, z1 = (bz + 1) * Nz / T.tz;
+    const int tid = threadIdx.x;
+    const bool col = tid < kSEX * kSEY, hal = tid < kSHalo;
+    const int ey = col ? tid / kSEX : 0, ex = col ? tid - ey * kSEX : 0;
+    const int64_t x = x0 - 2 + ex, y = y0 - 2 + ey;
+    const bool own = col && x >= x0 && x < x1 && y >= y0 && y < y1;
+    // a line position's node; positions off a bounded line, and beyond what the
+    // tile's stencils read, get some node of it
+    auto node = [](int64_t q, int64_t N, bool per) -> int64_t {
+        q = q > N + 3 ? N + 3 : q;
+        if (per) return q < 0 ? q + N : (q >= N ? q - N : q);
+        return q < 0 ? 0 : (q >= N ? N - 1 : q);
+    };
+    const int64_t cs = g.enpts, sz = g.es[2];
+    unsigned ecol = 8u * (unsigned)ext_index(g, node(x, Nx, !BX), node(y, Ny, !BY), 0);
+    // halo: two rows above and below the columns, two columns either side
+    int hx = 2, hy = 2;
+    if (tid < 4 * kSEX) {
+        const int r = tid / kSEX;
+        hx = 2 + tid - r * kSEX;
+        hy = r < 2 ? r : kSEY + r;
+    } else if (hal) {
+        const int r = tid - 4 * kSEX, s = r & 3;
+        hy = 2 + (r >> 2);
+        hx = s < 2 ? s : kSEX + s;
+    }
+    unsigned hcol = 8u * (unsigned)ext_index(g, node(x0 - 4 + hx, Nx, !BX), node(y0 - 4 + hy, Ny, !BY), 0);
+    auto plane = [&](int64_t z) { return (z < 0 ? z + Nz : (z >= Nz ? z - Nz : z)) * sz; };
+    auto load = [&](unsigned col, int64_t pl, double (&u)[NC]) {
+#pragma unroll
+        for (int c = 0; c < NC; ++c) u[c] = at32(Uin + (c * cs + pl), col);
+    };
+    const LineOp<BX> lx(x, Nx);
+    const LineOp<BY> ly(y, Ny);
+    const double ihx = m.invh[0][node(x, Nx, !BX)], ihy = m.invh[1][node(y, Ny, !BY)];
+
+    if ((BX || BY) && tid < 25) W[tid / 5][tid % 5] = kLineW[tid / 5][tid % 5];
+
+    double w[5][NV];    // the column's primitives at planes c-2 .. c+2
+    double acc[5][NV];  // its divergence so far at planes c-2 .. c+2
+    double ou[NC], hu[NC];         // states of the column and the halo node at plane c+3
+    double R[NC], d0[NC], u0[NC];  // residual, register and state of plane c-2
+#pragma unroll
+    for (int k = 0; k < 5; ++k)
+#pragma unroll
+        for (int v = 0; v < NV; ++v) acc[k][v] = 0.0;
+    // a plane's primitives into LDS
+    auto stage = [&](int slot, const double (&h)[NC], const double (&o)[NV]) {
+        if (hal) {
+            double f[NV];
+            phi_of(h, ph, f);
+#pragma unroll
+            for (int v = 0; v < NV; ++v) prim[slot][v][hy][hx] = f[v];
+        }
+        if (col)
+#pragma unroll
+            for (int v = 0; v < NV; ++v) prim[slot][v][ey + 2][ex + 2] = o[v];
+    };
+    // planes z0-4 .. z0 of the column; the last three, with their halo, into LDS
+    // (all requested at once: a short run is mostly these loads)
+    {
+        double u[5][NC], h[3][NC];
+#pragma unroll
+        for (int k = 0; k < 5; ++k) load(ecol, plane(z0 - 4 + k), u[k]);
+        if (hal) {
+#pragma unroll
+            for (int k = 0; k < 3; ++k) load(hcol, plane(z0 - 2 + k), h[k]);
+        }
+        load(ecol, plane(z0 + 1), ou);
+#pragma unroll
+        for (int k = 0; k < 5; ++k) phi_of(u[k], ph, w[k]);
+#pragma unroll
+        for (int k = 0; k < 3; ++k) stage(k, h[k], w[2 + k]);
+    }
+    if (hal) load(hcol, plane(z0 + 1), hu);
+    int slot = 0, cur = 0;  // LDS buffers of plane c
+    unsigned ci0 = 8u * (unsigned)(own ? int_index(g, x, y, 0) : 0);
+#pragma unroll 1
+    for (int64_t c = z0 - 2; c < z1 + 2; ++c) {
+        __syncthreads();
+        // the thread's offsets stay apart from the planes' bases (scalar), which are
+        // otherwise folded into two-register addresses per array
+        asm volatile("" : "+v"(ecol), "+v"(hcol), "+v"(ci0));
+#pragma unroll
+        for (int v = 0; v < NV; ++v) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) acc[k][v] = acc[k + 1][v];
+            acc[4][v] = 0.0;
+        }
+        if (col) {
+            double(&P)[NV][kSPY][kSPX] = prim[slot];
+            const int cx = ex + 2, cy = ey + 2;
+            auto invhz = [&](int64_t z) { return uniform_at(m.invh[2], z < 0 ? z + Nz : (z >= Nz ? z - Nz : z)); };
+            const double ihz = invhz(c);
+            double grad[NV][3], Fv[3][NV];
+#pragma unroll
+            for (int v = 0; v < NV; ++v) {
+                grad[v][0] = ihx * lx.template d1<1>(&P[v][cy][cx], W);
+                grad[v][1] = ihy * ly.template d1<kSPX>(&P[v][cy][cx], W);
+                grad[v][2] = ihz * ((2.0 / 3.0) * (w[3][v] - w[1][v]) - (1.0 / 12.0) * (w[4][v] - w[0][v]));
+            }
+            visc_node<3>(w[2], grad, ph, Fv);
+            double(&F)[7][kSEY][kSEX] = flux[cur];
+#pragma unroll
+            for (int v = 0; v < NV; ++v) {
+                // G_z's share of the four planes' z differences that read it
+                acc[0][v] -= (1.0 / 12.0) * invhz(c - 2) * Fv[2][v];
+                acc[1][v] += (2.0 / 3.0) * invhz(c - 1) * Fv[2][v];
+                acc[3][v] -= (2.0 / 3.0) * invhz(c + 1) * Fv[2][v];
+                acc[4][v] += (1.0 / 12.0) * invhz(c + 2) * Fv[2][v];
+            }
+            F[0][ey][ex] = Fv[0][0];
+            F[1][ey][ex] = Fv[1][1];
+            F[2][ey][ex] = Fv[0][1];
+            F[3][ey][ex] = Fv[0][2];
+            F[4][ey][ex] = Fv[1][2];
+            F[5][ey][ex] = Fv[0][3];
+            F[6][ey][ex] = Fv[1][3];
+        }
+        cur ^= 1;
+        if (own) {
+            double(&F)[7][kSEY][kSEX] = flux[cur];  // plane c-1
+            constexpr int sx[NV] = {0, 2, 3, 5}, sy[NV] = {2, 1, 4, 6};
+#pragma unroll
+            for (int v = 0; v < NV; ++v)
+                acc[1][v] +=
+                    ihx * lx.template d1<1>(&F[sx[v]][ey][ex], W) + ihy * ly.template d1<kSEX>(&F[sy[v]][ey][ex], W);
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+#pragma unroll
+            for (int v = 0; v < NV; ++v) w[k][v] = w[k + 1][v];
+        phi_of(ou, ph, w[4]);
+        stage((slot + 3) & 3, hu, w[4]);
+        slot = (slot + 1) & 3;
+        const int64_t pn = plane(c + 4 < z1 + 4 ? c + 4 : z1 + 3);
+        load(ecol, pn, ou);
+        if (hal) load(hcol, pn, hu);
+        const int64_t d = c - 2;
+        if (own && d >= z0) {
+            const int64_t pd = d * g.is[2], ed = d * sz;
+#pragma unroll
+            for (int v = 0; v < NV; ++v) R[1 + v] += acc[0][v];
+#pragma unroll
+            for (int k = 0; k < NC; ++k) {
+                const double du = (rs.first ? 0.0 : rs.A * d0[k]) + dt * R[k];
+                if (!rs.last) at32(dU + (k * g.nint + pd), ci0) = du;
+                at32(Uout + (k * cs + ed), ecol) = u0[k] + rs.B * du;
+            }
+        }
+        if (own && d + 1 >= z0 && d + 1 < z1) {
+            const int64_t pd = (d + 1) * g.is[2], ed = (d + 1) * sz;
+#pragma unroll
+            for (int k = 0; k < NC; ++k) R[k] = at32(Racc + (k * g.nint + pd), ci0);
+#pragma unroll
+            for (int k = 0; k < NC; ++k) d0[k] = rs.first ? 0.0 : at32(dU + (k * g.nint + pd), ci0);
+            load(ecol, ed, u0);
+        }
+    }
+}
+
 __device__ __forceinline__ double wave_max(double v) {
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) v = fmax(v, __shfl_xor(v, off, 64));
@@ -659,6 +931,25 @@ hipError_t launch_finish(const Grid &g, const Phys &ph, const Metrics &m, const 
             return gen ? finish_nd<3, true>(g, ph, m, Racc, G, Rout, rs, dt, U, dU, mode, s)
                        : finish_nd<3, false>(g, ph, m, Racc, G, Rout, rs, dt, U, dU, mode, s);
     }
+}
+
+bool march_supported(const Grid &g, const osbli_params &p) {
+    if (g.nd != 3 || p.mesh == OSBLI_MESH_GENERAL || g.enpts > kMarchMaxNodes) return false;
+    for (int d = 0; d < 3; ++d)
+        if (p.bc_kind[d][0] == OSBLI_DIRICHLET || p.bc_kind[d][1] == OSBLI_DIRICHLET) return false;
+    if (p.scheme == OSBLI_CENTRAL4) return g.periodic[0] && g.periodic[1] && g.periodic[2];
+    return p.Re > 0.0 && g.periodic[2];
+}
+
+hipError_t launch_viscous_step(const Grid &g, const Phys &ph, const Metrics &m, const double *Uin, double *Uout,
+                               const double *Racc, double *dU, RkStage rs, double dt, hipStream_t s) {
+    const StepTiles T = step_tiles(g);
+    const bool bx = !g.periodic[0], by = !g.periodic[1];
+    const auto k = bx ? (by ? k_visc_step<true, true> : k_visc_step<true, false>)
+                      : (by ? k_visc_step<false, true> : k_visc_step<false, false>);
+    hipLaunchKernelGGL(k, dim3((unsigned)(T.per * kXcds)), dim3(kSThreads), 0, s, Uin, Uout, Racc, dU, g, ph, m, rs, dt,
+                       T);
+    return hipGetLastError();
 }
 
 hipError_t launch_dt(const Grid &g, const Phys &ph, const Metrics &m, const double *U, unsigned long long *red,

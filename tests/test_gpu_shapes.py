@@ -165,3 +165,44 @@ def test_march_segments(n, general):
         s.set_sweep_segments([seg if general else 0, seg, seg])
         assert torch.equal(s.residual(), ref), seg
     s.check()
+
+
+@pytest.mark.parametrize("scheme,Re,sutherland", [("TENO5", 200.0, 0), ("TENO6", 200.0, 1), ("CENTRAL4", 0.0, 0),
+                                                  ("CENTRAL4", 200.0, 0), ("CENTRAL4", 200.0, 1)])
+@pytest.mark.parametrize("ends", ["periodic", "open_x", "wall", "open"])
+@pytest.mark.parametrize("n", [(6, 7, 6), (32, 10, 9), (33, 11, 8), (70, 21, 37)])
+def test_step_through_state_copies(n, ends, scheme, Re, sutherland):
+    """Whole steps of 3D problems that write each stage to a copy of the state
+    (tiles of 32 x 10 columns and their remainders, lines shorter than a tile,
+    runs of planes; periodic and bounded lines): two steps against the separate
+    calls of the same library, every node and ghost, at 1e-13 of the component's
+    largest value (the forms differ by the rounding of the viscous differences:
+    a few 1e-16 of the fluxes over a step)."""
+    import torch
+    from paper_2007_14933_amd import inputs as I
+    from paper_2007_14933_amd.solver import Solver
+    P, X = (I.PERIODIC,) * 2, (I.EXTRAPOLATE,) * 2
+    if ends == "wall":  # isothermal wall, extrapolation, stretched in y
+        if scheme == "CENTRAL4":
+            pytest.skip("the central scheme takes uniform meshes")
+        prob = I.wall_flow(*n, scheme=getattr(I, scheme)).with_(sutherland=sutherland)
+    else:
+        bc = {"periodic": (P, P, P), "open_x": (X, P, P), "open": (X, X, P)}[ends]
+        prob = I.smooth_random(3, n, seed=n[0], amp=0.2, Re=Re).with_(
+            scheme=getattr(I, scheme), bc=bc, sutherland=sutherland, Minf=0.5, Pr=0.72,
+            rk=I.RK4 if ends == "open_x" else I.RK3)
+    a, b = Solver(prob), Solver(prob)
+    for s in (a, b):
+        s.apply_bc()
+    dt = 0.5 * a.compute_dt(0.5)
+    for _ in range(2):
+        a.step(dt)
+        for k in range(b.nstages):
+            b.substep(k, dt)
+            b.apply_bc()
+    a.check()
+    torch.cuda.synchronize()
+    scale = b.U.abs().amax(dim=(1, 2, 3), keepdim=True)
+    err = float(((a.U - b.U).abs() / scale).max())
+    assert err <= 1e-13, err
+    assert float((a.dU - b.dU).abs().max()) <= 1e-11 * float(b.dU.abs().max())
