@@ -204,8 +204,8 @@ int osbli_rk_substep(osbli_ctx *ctx, int stage, double dt, double *U, double *dU
  * Inviscid 1D and 2D problems on separable meshes with periodic or
  * extrapolated ends (six-point schemes; FP64 or routed forms; at most 2^24
  * nodes) take one launch per stage through two state copies in the workspace.
- * 3D problems on separable meshes without Dirichlet sides (at most 2^28 nodes
- * with ghosts) go through two copies as well, which lets one pass read the
+ * 3D problems on separable meshes without Dirichlet sides (from about 28^3
+ * nodes to 2^28 with ghosts) go through two copies as well, which lets one pass read the
  * neighbours' states and update: viscous ones periodic along z, after the
  * sweeps, and the central scheme on fully periodic grids.  Every other problem
  * takes the separate calls. */

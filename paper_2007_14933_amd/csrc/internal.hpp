@@ -208,8 +208,7 @@ hipError_t launch_dt(const Grid &g, const Phys &ph, const Metrics &m, const doub
 // whether whole steps of a 3D problem write each stage's state to a copy
 // (launch_viscous_step, launch_central_step): separable meshes; the boundary
 // conditions must set every ghost (Dirichlet data lives in the caller's ghosts
-// only); up to 2^28 nodes with ghosts (32-bit byte offsets), where the copies, which take the stored fluxes' or
-// gradients' place, add at most 5 GB to the workspace
+// only); from about 28^3 nodes up to 2^28 with ghosts (32-bit byte offsets)
 constexpr int64_t kMarchMaxNodes = int64_t(1) << 28;
 bool march_supported(const Grid &g, const osbli_params &p);
 // one Runge-Kutta stage of an inviscid 1D or 2D problem, Uin -> Uout (ghosts

@@ -935,6 +935,9 @@ hipError_t launch_finish(const Grid &g, const Phys &ph, const Metrics &m, const 
 
 bool march_supported(const Grid &g, const osbli_params &p) {
     if (g.nd != 3 || p.mesh == OSBLI_MESH_GENERAL || g.enpts > kMarchMaxNodes) return false;
+    // small grids are mostly ghosts: the copies, which take the flux arrays' place,
+    // would need more than twice their memory, to save traffic of a few us
+    if (g.nc * g.enpts > gflux_count(3, false) * g.nint) return false;
     for (int d = 0; d < 3; ++d)
         if (p.bc_kind[d][0] == OSBLI_DIRICHLET || p.bc_kind[d][1] == OSBLI_DIRICHLET) return false;
     if (p.scheme == OSBLI_CENTRAL4) return g.periodic[0] && g.periodic[1] && g.periodic[2];

@@ -170,14 +170,15 @@ def test_march_segments(n, general):
 @pytest.mark.parametrize("scheme,Re,sutherland", [("TENO5", 200.0, 0), ("TENO6", 200.0, 1), ("CENTRAL4", 0.0, 0),
                                                   ("CENTRAL4", 200.0, 0), ("CENTRAL4", 200.0, 1)])
 @pytest.mark.parametrize("ends", ["periodic", "open_x", "wall", "open"])
-@pytest.mark.parametrize("n", [(6, 7, 6), (32, 10, 9), (33, 11, 8), (70, 21, 37)])
+@pytest.mark.parametrize("n", [(28, 29, 28), (33, 31, 40), (70, 21, 37), (10, 100, 128), (128, 10, 100), (100, 128, 10)])
 def test_step_through_state_copies(n, ends, scheme, Re, sutherland):
     """Whole steps of 3D problems that write each stage to a copy of the state
-    (tiles of 32 x 10 columns and their remainders, lines shorter than a tile,
-    runs of planes; periodic and bounded lines): two steps against the separate
-    calls of the same library, every node and ghost, at 1e-13 of the component's
-    largest value (the forms differ by the rounding of the viscous differences:
-    a few 1e-16 of the fluxes over a step)."""
+    (tiles of 32 x 10 columns and their remainders, a line of one tile, runs of
+    planes, the smallest grids that do; periodic and bounded lines): two steps
+    against the separate calls of the same library, every node and ghost and the
+    register, at 1e-13 of the state component's largest value (the forms differ by
+    the rounding of the viscous differences: a few 1e-16 of the fluxes, which a
+    step weighs by at most its CFL number)."""
     import torch
     from paper_2007_14933_amd import inputs as I
     from paper_2007_14933_amd.solver import Solver
@@ -205,4 +206,4 @@ def test_step_through_state_copies(n, ends, scheme, Re, sutherland):
     scale = b.U.abs().amax(dim=(1, 2, 3), keepdim=True)
     err = float(((a.U - b.U).abs() / scale).max())
     assert err <= 1e-13, err
-    assert float((a.dU - b.dU).abs().max()) <= 1e-11 * float(b.dU.abs().max())
+    assert float(((a.dU - b.dU).abs() / scale).max()) <= 1e-13
