@@ -439,10 +439,16 @@ RkStage stage_of(const osbli_ctx *c, int s) {
     return RkStage{c->rkA[s], c->rkB[s], s == 0, s == c->nstages - 1};
 }
 
-// convective sweeps of every direction into R (first stores, later accumulate)
-hipError_t convective_all(osbli_ctx *c, const double *U, double *R, hipStream_t s) {
+// convective sweeps of every direction into R (first stores, later accumulate);
+// Z, if not null: 3D, the y and z sweeps in one launch, z's contribution into Z
+hipError_t convective_all(osbli_ctx *c, const double *U, double *R, double *Z, hipStream_t s) {
     const bool route = c->p.sensor && c->sensor_ready;
     for (int d = 0; d < c->g.nd; ++d) {
+        if (Z && d == 1) {
+            Timed t(c, OSBLI_K_SWEEP_Y, s);
+            return launch_convective_yz(c->g, c->ph, c->m, U, R, Z, c->flags, route ? c->mask[1] : nullptr,
+                                        route ? c->mask[2] : nullptr, c->seg, s);
+        }
         Timed t(c, OSBLI_K_SWEEP_X + d, s);
         hipError_t e = launch_convective(c->g, c->ph, c->m, U, R, c->flags, d, d == 0, route ? c->mask[d] : nullptr,
                                          c->seg[d], s);
@@ -594,7 +600,7 @@ int osbli_residual(osbli_ctx *c, const double *U, double *R, void *stream) {
         Timed t(c, OSBLI_K_VISC_FLUX, s);
         HIP_TRY(c, launch_viscous_fluxes(c->g, c->ph, c->m, U, c->G, s));
     }
-    HIP_TRY(c, convective_all(c, U, R, s));
+    HIP_TRY(c, convective_all(c, U, R, nullptr, s));
     if (c->ph.viscous) {
         Timed t(c, OSBLI_K_FINISH, s);
         HIP_TRY(c, launch_finish(c->g, c->ph, c->m, R, c->G, R, RkStage{0.0, 0.0, 1, 1}, 0.0, nullptr, nullptr, 0, s));
@@ -635,7 +641,7 @@ int osbli_rk_substep(osbli_ctx *c, int stage, double dt, double *U, double *dU, 
         Timed t(c, OSBLI_K_VISC_FLUX, s);
         HIP_TRY(c, launch_viscous_fluxes(c->g, c->ph, c->m, U, c->G, s));
     }
-    HIP_TRY(c, convective_all(c, U, c->Racc, s));
+    HIP_TRY(c, convective_all(c, U, c->Racc, nullptr, s));
     {
         Timed t(c, OSBLI_K_FINISH, s);
         HIP_TRY(c, launch_finish(c->g, c->ph, c->m, c->Racc, c->G, nullptr, stage_of(c, stage), dt, U, dU, 1, s));
@@ -666,11 +672,13 @@ int osbli_rk_step(osbli_ctx *c, double dt, double *U, double *dU, void *stream) 
         double *out = st == c->nstages - 1 ? U : c->W[st & 1];
         if (route && (st == 0 || c->sensor_every)) HIP_TRY(c, sensor_all(c, in, s));
         if (march) {
-            if (!central) HIP_TRY(c, convective_all(c, in, c->Racc, s));
+            const bool yz = !central && c->p.scheme != OSBLI_WENOZ7 && !(c->ph.mixed && !route) &&
+                            c->g.nint <= kYzMaxNodes;
+            if (!central) HIP_TRY(c, convective_all(c, in, c->Racc, yz ? out : nullptr, s));
             {
                 Timed t(c, central ? OSBLI_K_CENTRAL : OSBLI_K_FINISH, s);
                 HIP_TRY(c, central ? launch_central_step(c->g, c->ph, c->m, in, out, dU, stage_of(c, st), dt, s)
-                                   : launch_viscous_step(c->g, c->ph, c->m, in, out, c->Racc, dU, stage_of(c, st), dt, s));
+                                   : launch_viscous_step(c->g, c->ph, c->m, in, out, c->Racc, yz, dU, stage_of(c, st), dt, s));
             }
             Timed t(c, OSBLI_K_BC, s);
             HIP_TRY(c, launch_bc(c->g, c->ph, c->p, out, s));

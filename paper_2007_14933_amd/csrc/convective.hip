@@ -21,6 +21,8 @@ namespace cvl {
 // the two fifth-order schemes of every form (plain, precision, routed)
 template hipError_t launch_convective_s<OSBLI_WENOZ5> OSBLI_CONVECTIVE_SIG;
 template hipError_t launch_convective_s<OSBLI_TENO5> OSBLI_CONVECTIVE_SIG;
+template hipError_t launch_yz_s<OSBLI_WENOZ5> OSBLI_YZ_SIG;
+template hipError_t launch_yz_s<OSBLI_TENO5> OSBLI_YZ_SIG;
 }  // namespace cvl
 
 hipError_t launch_convective(const Grid &g, const Phys &ph, const Metrics &m, const double *U, double *R,
@@ -34,6 +36,20 @@ hipError_t launch_convective(const Grid &g, const Phys &ph, const Metrics &m, co
             return cvl::launch_convective_s<OSBLI_WENOJS5>(g, ph, m, U, R, flags, dir, first, mask, sq, s);
         case OSBLI_WENOZ3: return cvl::launch_convective_s<OSBLI_WENOZ3>(g, ph, m, U, R, flags, dir, first, mask, sq, s);
         case OSBLI_WENOZ7: return cvl::launch_convective_wz7(g, ph, m, U, R, flags, dir, first, mask, sq, s);
+        default: return hipErrorInvalidValue;
+    }
+}
+
+hipError_t launch_convective_yz(const Grid &g, const Phys &ph, const Metrics &m, const double *U, double *R, double *Z,
+                                unsigned *flags, const uint8_t *my, const uint8_t *mz, const int64_t *sq,
+                                hipStream_t s) {
+    if (g.nd != 3 || m.general) return hipErrorInvalidValue;
+    switch (ph.scheme) {
+        case OSBLI_WENOZ5: return cvl::launch_yz_s<OSBLI_WENOZ5>(g, ph, m, U, R, Z, flags, my, mz, sq, s);
+        case OSBLI_TENO5: return cvl::launch_yz_s<OSBLI_TENO5>(g, ph, m, U, R, Z, flags, my, mz, sq, s);
+        case OSBLI_TENO6: return cvl::launch_yz_s<OSBLI_TENO6>(g, ph, m, U, R, Z, flags, my, mz, sq, s);
+        case OSBLI_WENOJS5: return cvl::launch_yz_s<OSBLI_WENOJS5>(g, ph, m, U, R, Z, flags, my, mz, sq, s);
+        case OSBLI_WENOZ3: return cvl::launch_yz_s<OSBLI_WENOZ3>(g, ph, m, U, R, Z, flags, my, mz, sq, s);
         default: return hipErrorInvalidValue;
     }
 }

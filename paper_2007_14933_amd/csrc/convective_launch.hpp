@@ -83,6 +83,45 @@ hipError_t launch_convective_s(const Grid &g, const Phys &ph, const Metrics &m, 
     }
 }
 
+template <int SCHEME, bool MIX, bool ROUTE>
+hipError_t launch_yz_r(const Grid &g, const Phys &ph, const Metrics &m, const double *U, double *R, double *Z,
+                       unsigned *flags, const uint8_t *masky, const uint8_t *maskz, const int64_t *sq, hipStream_t s) {
+    const int64_t ly = g.n[0] * g.n[2], lz = g.n[0] * g.n[1];
+    const int64_t both = march_segment(g.n[1], ly, false, g.n[2], lz);
+    int64_t seg[2], nseg[2], nb[2];
+    for (int k = 0; k < 2; ++k) {
+        const int64_t N = g.n[1 + k], waves = ((k ? lz : ly) + 63) / 64;
+        seg[k] = sq[1 + k] > 0 ? sq[1 + k] : both;
+        if (seg[k] > N) seg[k] = N;
+        nseg[k] = (N + seg[k] - 1) / seg[k];
+        nb[k] = (waves * nseg[k] + kWaves - 1) / kWaves;
+    }
+    hipLaunchKernelGGL((k_sweep_yz<SCHEME, MIX, ROUTE>), dim3((unsigned)(nb[0] + nb[1])), dim3(64 * kWaves), 0, s, U,
+                       R, Z, g, ph, m, seg[0], nseg[0], seg[1], nseg[1], (int)nb[0], flags, masky, maskz);
+    return hipGetLastError();
+}
+
+template <int SCHEME>
+hipError_t launch_yz_s(const Grid &g, const Phys &ph, const Metrics &m, const double *U, double *R, double *Z,
+                       unsigned *flags, const uint8_t *my, const uint8_t *mz, const int64_t *sq, hipStream_t s) {
+    if constexpr (SCHEME == OSBLI_TENO5)
+        if (my) {
+            if (ph.mixed) return launch_yz_r<SCHEME, true, true>(g, ph, m, U, R, Z, flags, my, mz, sq, s);
+            return launch_yz_r<SCHEME, false, true>(g, ph, m, U, R, Z, flags, my, mz, sq, s);
+        }
+    if (ph.mixed) return hipErrorInvalidValue;
+    return launch_yz_r<SCHEME, false, false>(g, ph, m, U, R, Z, flags, nullptr, nullptr, sq, s);
+}
+
+#define OSBLI_YZ_SIG                                                                                         \
+    (const Grid &, const Phys &, const Metrics &, const double *, double *, double *, unsigned *,           \
+     const uint8_t *, const uint8_t *, const int64_t *, hipStream_t)
+extern template hipError_t launch_yz_s<OSBLI_WENOZ5> OSBLI_YZ_SIG;
+extern template hipError_t launch_yz_s<OSBLI_TENO5> OSBLI_YZ_SIG;
+extern template hipError_t launch_yz_s<OSBLI_TENO6> OSBLI_YZ_SIG;
+extern template hipError_t launch_yz_s<OSBLI_WENOJS5> OSBLI_YZ_SIG;
+extern template hipError_t launch_yz_s<OSBLI_WENOZ3> OSBLI_YZ_SIG;
+
 #define OSBLI_CONVECTIVE_SIG                                                                                 \
     (const Grid &, const Phys &, const Metrics &, const double *, double *, unsigned *, int, int,          \
      const uint8_t *, int64_t, hipStream_t)

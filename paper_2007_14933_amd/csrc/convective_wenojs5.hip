@@ -4,5 +4,6 @@
 namespace osbli {
 namespace cvl {
 template hipError_t launch_convective_s<OSBLI_WENOJS5> OSBLI_CONVECTIVE_SIG;
+template hipError_t launch_yz_s<OSBLI_WENOJS5> OSBLI_YZ_SIG;
 }  // namespace cvl
 }  // namespace osbli

@@ -134,20 +134,23 @@ inline int64_t default_segment(int64_t N, int64_t lines) {
     return seg < N ? seg : N;
 }
 
-// Segment length of a marching sweep over one grid: the one with the shortest
+// Segment length of a marching sweep over one grid (or of two sweeps in one
+// launch, the second of N2 nodes and lines2): the one with the shortest
 // estimated time.  A wave marches its segment and one more interface; one wave
 // alone on a SIMD takes 2.8 us per interface, two together 4.9 (measured; a
 // single round of pairs 5 % more), so the waves run in rounds of 2048 (general
 // meshes: one wave per SIMD, 1024).  The batch's rule above (segments of 8
 // nodes or longer) left a 64^3 grid with 512 waves of nine interfaces: 35 us
 // per sweep, 24 with segments of four.
-inline int64_t march_segment(int64_t N, int64_t lines, bool general) {
-    const int64_t wl = (lines + 63) / 64, slots = general ? 1024 : 2048;
+inline int64_t march_segment(int64_t N, int64_t lines, bool general, int64_t N2 = 0, int64_t lines2 = 0) {
+    const int64_t wl = (lines + 63) / 64, wl2 = (lines2 + 63) / 64, slots = general ? 1024 : 2048;
+    const int64_t longest = N > N2 ? N : N2;
     int64_t best = 1;
     double cost = 0.0;
-    for (int64_t seg = N < 128 ? N : 128; seg >= 1; --seg) {
-        const int64_t nseg = (N + seg - 1) / seg, W = wl * nseg, full = W / slots, rest = W - full * slots;
-        const double len = (W > slots ? (double)N / (double)nseg : (double)seg) + 1.0;
+    for (int64_t seg = longest < 128 ? longest : 128; seg >= 1; --seg) {
+        const int64_t W = wl * ((N + seg - 1) / seg) + wl2 * ((N2 + seg - 1) / seg);
+        const int64_t full = W / slots, rest = W - full * slots;
+        const double len = (W > slots ? (double)(wl * N + wl2 * N2) / (double)W : (double)seg) + 1.0;
         const double pair = general ? 2.8 : (W > 2048 ? 4.9 : 5.15);
         const double t = len * (pair * (double)full + (rest == 0 ? 0.0 : (rest <= 1024 ? 2.8 : pair)));
         if (cost == 0.0 || t < cost) {
@@ -162,6 +165,19 @@ inline int64_t march_segment(int64_t N, int64_t lines, bool general) {
 hipError_t launch_convective(const Grid &g, const Phys &ph, const Metrics &m, const double *U,
                              double *R, unsigned *flags, int dir, int first, const uint8_t *mask,
                              int64_t seg_req, hipStream_t s);
+// the y and z sweeps of a 3D separable grid in one launch: y's contribution is
+// added to R, z's stored in Z (the state's ghosted layout); all but WENO-7Z and the
+// unrouted precision form (its FP32 arithmetic may be contracted differently in
+// another kernel)
+// Each sweep alone leaves waves idle at its end, and a small grid much of the
+// chip throughout; the update then reads one part of the residual more.  Both
+// sweeps and the update, together and one after the other: 32^3 35 and 47 us,
+// 64^3 74 and 84, 96^3 160 and 172, 112^3 248 and 250, 128^3 345 and 337, 256^3
+// 2.22 and 2.12 ms.
+constexpr int64_t kYzMaxNodes = 3 << 19;
+hipError_t launch_convective_yz(const Grid &g, const Phys &ph, const Metrics &m, const double *U, double *R, double *Z,
+                                unsigned *flags, const uint8_t *masky, const uint8_t *maskz, const int64_t *seg_req,
+                                hipStream_t s);
 // learned sensor
 int64_t iface_count(const Grid &g, int d);
 hipError_t launch_labels(const Grid &g, const Phys &ph, const double *U, int d, float *feat, uint8_t *lab,
@@ -183,9 +199,10 @@ hipError_t launch_finish(const Grid &g, const Phys &ph, const Metrics &m, const 
                          const double *G, double *Rout, RkStage rs, double dt, double *U, double *dU,
                          int mode, hipStream_t s);
 // 3D separable meshes, periodic along z: Uout, dU from Uin (interior nodes; the
-// state's copies must differ) with the viscous divergence added to Racc
+// state's copies must differ) with the viscous divergence added to Racc and, if
+// more is set, to what Uout holds (a part of the residual, node by node)
 hipError_t launch_viscous_step(const Grid &g, const Phys &ph, const Metrics &m, const double *Uin, double *Uout,
-                               const double *Racc, double *dU, RkStage rs, double dt, hipStream_t s);
+                               const double *Racc, bool more, double *dU, RkStage rs, double dt, hipStream_t s);
 // fourth-order central path: residual R of U (ghosts valid); Gs: velocity
 // gradients (nd^2 per node), used by the StoreSome strategy (work == null);
 // work: the store-all strategy's arrays (central_work_bytes)

@@ -46,7 +46,8 @@ using AheadLds = double[2][ND + 3][64];
 // The work of one wave: lines line0 .. line0+63 (clamped), segment sg of
 // length seg along DIR.  sbuf: this wave's staging buffer (x sweep only);
 // ab: this wave's ahead-load buffer (y and z sweeps).
-template <int ND, int DIR, int SCHEME, bool GEN, bool MIX, bool ROUTE, bool AHEAD>
+// EXTR: R has the state's ghosted layout (and is stored, not accumulated).
+template <int ND, int DIR, int SCHEME, bool GEN, bool MIX, bool ROUTE, bool AHEAD, bool EXTR = false>
 __device__ __forceinline__ void sweep_wave(const double *__restrict__ U, double *__restrict__ R, const Grid &g,
                                            const Phys &ph, const Metrics &m, int64_t seg, int64_t sg, int64_t line0,
                                            int first, unsigned *flags, const uint8_t *__restrict__ mask,
@@ -75,8 +76,8 @@ __device__ __forceinline__ void sweep_wave(const double *__restrict__ U, double 
     const int64_t base = ext_index(g, q[0], q[1], q[2]);
     const int64_t st = g.es[DIR];
     const int64_t cs = g.enpts;
-    const int64_t ibase = int_index(g, q[0], q[1], q[2]);
-    const int64_t ist = g.is[DIR];
+    const int64_t ibase = EXTR ? base : int_index(g, q[0], q[1], q[2]);
+    const int64_t ist = EXTR ? st : g.is[DIR], rcs = EXTR ? cs : g.nint;
     bool bad = false;
 
     // Ahead-loading (AHEAD: y and z sweeps of separable meshes, for waves
@@ -233,7 +234,7 @@ __device__ __forceinline__ void sweep_wave(const double *__restrict__ U, double 
             // flux: its memory latency hides behind the flux arithmetic
             if (!first) {
 #pragma unroll
-                for (int c = 0; c < NC; ++c) rold[c] = R[c * g.nint + ibase + f * ist];
+                for (int c = 0; c < NC; ++c) rold[c] = R[c * rcs + ibase + f * ist];
             }
             if (GEN) {
 #pragma unroll
@@ -349,10 +350,10 @@ __device__ __forceinline__ void sweep_wave(const double *__restrict__ U, double 
             for (int c = 0; c < NC; ++c) v[c] = -sc * (F[c] - Fp[c]);
             if (first) {
 #pragma unroll
-                for (int c = 0; c < NC; ++c) R[c * g.nint + ibase + f * ist] = v[c];
+                for (int c = 0; c < NC; ++c) R[c * rcs + ibase + f * ist] = v[c];
             } else {
 #pragma unroll
-                for (int c = 0; c < NC; ++c) R[c * g.nint + ibase + f * ist] = rold[c] + v[c];
+                for (int c = 0; c < NC; ++c) R[c * rcs + ibase + f * ist] = rold[c] + v[c];
             }
         }
 #pragma unroll
@@ -361,45 +362,72 @@ __device__ __forceinline__ void sweep_wave(const double *__restrict__ U, double 
     if (bad) atomicOr(flags, kFlagNonPhys);
 }
 
-// One convective sweep along DIR over a whole grid.  first != 0: R =
+// Block blk of a convective sweep along DIR over a whole grid.  first != 0: R =
 // contribution, else R +=.  Thread mapping: every wave owns 64 consecutive
 // lines and one segment [p0, p1) along DIR (wave-uniform), lane l owns line
 // line0 + l.  Along y and z the lanes' loads are contiguous in x; along x
 // the lines are strided, so the wave stages chunks of kChunk points of its 64
 // rows through LDS with contiguous loads and each lane reads its own row back.
-// One wave per SIMD for general meshes and for the mixed-precision routed
-// variant (both flux paths plus the FP64 reference in one loop): at two
-// waves they spill, which cost more (1.29 vs 0.93 ms at 256^3) than the
-// lost occupancy.
-template <int ND, int DIR, int SCHEME, bool GEN, bool MIX, bool ROUTE>
-__global__ void __launch_bounds__(256, GEN ? 1 : 2)
-k_sweep(const double *__restrict__ U, double *__restrict__ R, Grid g, Phys ph, Metrics m, int64_t seg,
-        int64_t nseg, int first, unsigned *flags, const uint8_t *__restrict__ mask) {
-    __shared__ double sbuf[DIR == 0 ? kWaves : 1][ND + 2][kChunk][64];
-    __shared__ double abuf[DIR == 0 || GEN ? 1 : kWaves][2][ND + 3][64];
+template <int ND, int DIR, int SCHEME, bool GEN, bool MIX, bool ROUTE, bool EXTR>
+__device__ __forceinline__ void sweep_block(const double *__restrict__ U, double *__restrict__ R, const Grid &g,
+                                            const Phys &ph, const Metrics &m, int64_t seg, int64_t nseg, int first,
+                                            unsigned *flags, const uint8_t *__restrict__ mask, int64_t blk,
+                                            SweepLds<ND> *sbuf, AheadLds<ND> *abuf) {
     constexpr int O1 = DIR == 0 ? 1 : 0;
     constexpr int O2 = DIR == 2 ? 1 : 2;
     const int64_t lines = g.n[O1] * g.n[O2];
     const int64_t wpl = (lines + 63) >> 6;  // waves per segment
     // wave index made explicitly uniform, so that the segment bounds and the
     // loop over it live in scalar registers
-    const int64_t gw = (int64_t)blockIdx.x * (blockDim.x >> 6) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t gw = blk * kWaves + wv;
     const int64_t sg = gw / wpl;
     if (sg >= nseg) return;  // wave-uniform
     const int64_t line0 = (gw - sg * wpl) << 6;
-    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     if constexpr (DIR != 0 && !GEN) {
         const int64_t n1 = g.n[O1];
         if ((line0 % n1) + 64 <= n1 && line0 + 64 <= lines)  // wave-uniform: 64 consecutive x nodes
-            sweep_wave<ND, DIR, SCHEME, GEN, MIX, ROUTE, true>(U, R, g, ph, m, seg, sg, line0, first, flags, mask,
-                                                               sbuf[0], abuf[wv]);
+            sweep_wave<ND, DIR, SCHEME, GEN, MIX, ROUTE, true, EXTR>(U, R, g, ph, m, seg, sg, line0, first, flags,
+                                                                     mask, sbuf[0], abuf[wv]);
         else
-            sweep_wave<ND, DIR, SCHEME, GEN, MIX, ROUTE, false>(U, R, g, ph, m, seg, sg, line0, first, flags, mask,
-                                                                sbuf[0], abuf[wv]);
+            sweep_wave<ND, DIR, SCHEME, GEN, MIX, ROUTE, false, EXTR>(U, R, g, ph, m, seg, sg, line0, first, flags,
+                                                                      mask, sbuf[0], abuf[wv]);
     } else {
-        sweep_wave<ND, DIR, SCHEME, GEN, MIX, ROUTE, false>(U, R, g, ph, m, seg, sg, line0, first, flags, mask,
-                                                            sbuf[DIR == 0 ? wv : 0], abuf[0]);
+        sweep_wave<ND, DIR, SCHEME, GEN, MIX, ROUTE, false, EXTR>(U, R, g, ph, m, seg, sg, line0, first, flags, mask,
+                                                                  sbuf[DIR == 0 ? wv : 0], abuf[0]);
     }
+}
+
+// One wave per SIMD for general meshes and for the mixed-precision routed
+// variant (both flux paths plus the FP64 reference in one loop): at two
+// waves they spill, which cost more (1.29 vs 0.93 ms at 256^3) than the
+// lost occupancy.
+template <int ND, int DIR, int SCHEME, bool GEN, bool MIX, bool ROUTE>
+__global__ void __launch_bounds__(64 * kWaves, GEN ? 1 : 2)
+k_sweep(const double *__restrict__ U, double *__restrict__ R, Grid g, Phys ph, Metrics m, int64_t seg,
+        int64_t nseg, int first, unsigned *flags, const uint8_t *__restrict__ mask) {
+    __shared__ SweepLds<ND> sbuf[DIR == 0 ? kWaves : 1];
+    __shared__ AheadLds<ND> abuf[DIR == 0 || GEN ? 1 : kWaves];
+    sweep_block<ND, DIR, SCHEME, GEN, MIX, ROUTE, false>(U, R, g, ph, m, seg, nseg, first, flags, mask, blockIdx.x,
+                                                         sbuf, abuf);
+}
+
+// The y and z sweeps of a 3D grid in one launch: the first nby blocks add y's
+// contribution to R, the others store z's into Z (ghosted layout), so that
+// neither waits for the other (64^3: 39 us, 25 + 26 one after the other).
+template <int SCHEME, bool MIX, bool ROUTE>
+__global__ void __launch_bounds__(64 * kWaves, 2)
+k_sweep_yz(const double *__restrict__ U, double *__restrict__ R, double *__restrict__ Z, Grid g, Phys ph, Metrics m,
+           int64_t segy, int64_t nsegy, int64_t segz, int64_t nsegz, int nby, unsigned *flags,
+           const uint8_t *__restrict__ masky, const uint8_t *__restrict__ maskz) {
+    __shared__ SweepLds<3> sbuf[1];
+    __shared__ AheadLds<3> abuf[kWaves];
+    if ((int)blockIdx.x < nby)
+        sweep_block<3, 1, SCHEME, false, MIX, ROUTE, false>(U, R, g, ph, m, segy, nsegy, 0, flags, masky, blockIdx.x,
+                                                            sbuf, abuf);
+    else
+        sweep_block<3, 2, SCHEME, false, MIX, ROUTE, true>(U, Z, g, ph, m, segz, nsegz, 1, flags, maskz,
+                                                           blockIdx.x - nby, sbuf, abuf);
 }
 
 // ---------------------------------------------------------------------------

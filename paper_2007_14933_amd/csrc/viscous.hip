@@ -611,7 +611,7 @@ struct LineOp {
 // BX, BY: lines along x, y are bounded.
 template <bool BX, bool BY>
 __global__ void __launch_bounds__(kSThreads, 2)
-k_visc_step(const double *__restrict__ Uin, double *__restrict__ Uout, const double *__restrict__ Racc,
+k_visc_step(const double *__restrict__ Uin, double *__restrict__ Uout, const double *__restrict__ Racc, bool more,
             double *__restrict__ dU, Grid g, Phys ph, Metrics m, RkStage rs, double dt, StepTiles T) {
     constexpr int NV = 4, NC = 5;
     __shared__ double prim[4][NV][kSPY][kSPX];
@@ -666,7 +666,7 @@ k_visc_step(const double *__restrict__ Uin, double *__restrict__ Uout, const dou
     double w[5][NV];    // the column's primitives at planes c-2 .. c+2
     double acc[5][NV];  // its divergence so far at planes c-2 .. c+2
     double ou[NC], hu[NC];         // states of the column and the halo node at plane c+3
-    double R[NC], d0[NC], u0[NC];  // residual, register and state of plane c-2
+    double R[NC], Z[NC], d0[NC], u0[NC];  // residual (two parts), register and state of plane c-2
 #pragma unroll
     for (int k = 0; k < 5; ++k)
 #pragma unroll
@@ -767,6 +767,8 @@ k_visc_step(const double *__restrict__ Uin, double *__restrict__ Uout, const dou
         if (own && d >= z0) {
             const int64_t pd = d * g.is[2], ed = d * sz;
 #pragma unroll
+            for (int k = 0; k < NC; ++k) R[k] += Z[k];
+#pragma unroll
             for (int v = 0; v < NV; ++v) R[1 + v] += acc[0][v];
 #pragma unroll
             for (int k = 0; k < NC; ++k) {
@@ -779,6 +781,8 @@ k_visc_step(const double *__restrict__ Uin, double *__restrict__ Uout, const dou
             const int64_t pd = (d + 1) * g.is[2], ed = (d + 1) * sz;
 #pragma unroll
             for (int k = 0; k < NC; ++k) R[k] = at32(Racc + (k * g.nint + pd), ci0);
+#pragma unroll
+            for (int k = 0; k < NC; ++k) Z[k] = more ? at32(Uout + (k * cs + ed), ecol) : 0.0;
 #pragma unroll
             for (int k = 0; k < NC; ++k) d0[k] = rs.first ? 0.0 : at32(dU + (k * g.nint + pd), ci0);
             load(ecol, ed, u0);
@@ -945,13 +949,13 @@ bool march_supported(const Grid &g, const osbli_params &p) {
 }
 
 hipError_t launch_viscous_step(const Grid &g, const Phys &ph, const Metrics &m, const double *Uin, double *Uout,
-                               const double *Racc, double *dU, RkStage rs, double dt, hipStream_t s) {
+                               const double *Racc, bool more, double *dU, RkStage rs, double dt, hipStream_t s) {
     const StepTiles T = step_tiles(g);
     const bool bx = !g.periodic[0], by = !g.periodic[1];
     const auto k = bx ? (by ? k_visc_step<true, true> : k_visc_step<true, false>)
                       : (by ? k_visc_step<false, true> : k_visc_step<false, false>);
-    hipLaunchKernelGGL(k, dim3((unsigned)(T.per * kXcds)), dim3(kSThreads), 0, s, Uin, Uout, Racc, dU, g, ph, m, rs, dt,
-                       T);
+    hipLaunchKernelGGL(k, dim3((unsigned)(T.per * kXcds)), dim3(kSThreads), 0, s, Uin, Uout, Racc, more, dU, g, ph, m, rs,
+                       dt, T);
     return hipGetLastError();
 }
 

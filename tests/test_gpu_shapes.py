@@ -207,3 +207,29 @@ def test_step_through_state_copies(n, ends, scheme, Re, sutherland):
     err = float(((a.U - b.U).abs() / scale).max())
     assert err <= 1e-13, err
     assert float(((a.dU - b.dU).abs() / scale).max()) <= 1e-13
+
+
+@pytest.mark.parametrize("scheme", ["WENOZ5", "TENO5", "TENO6", "WENOJS5", "WENOZ3", "WENOZ7"])
+@pytest.mark.parametrize("n", [(28, 29, 28), (64, 66, 31), (70, 40, 37)])
+def test_y_and_z_sweeps_together(n, scheme):
+    """Grids whose y and z sweeps run in one launch (lines of several segments,
+    rows of whole and of partial waves), each scheme: one step against the
+    separate calls, 1e-13 of the component's largest value (the sum over the
+    directions is rounded differently, nothing else)."""
+    import torch
+    from paper_2007_14933_amd import inputs as I
+    from paper_2007_14933_amd.solver import Solver
+    prob = I.smooth_random(3, n, seed=n[0], amp=0.2, Re=200.0).with_(scheme=getattr(I, scheme))
+    a, b = Solver(prob), Solver(prob)
+    for s in (a, b):
+        s.apply_bc()
+    dt = a.compute_dt(0.5)
+    a.step(dt)
+    for k in range(b.nstages):
+        b.substep(k, dt)
+        b.apply_bc()
+    a.check()
+    torch.cuda.synchronize()
+    scale = b.U.abs().amax(dim=(1, 2, 3), keepdim=True)
+    err = float(((a.U - b.U).abs() / scale).max())
+    assert err <= 1e-13, err
