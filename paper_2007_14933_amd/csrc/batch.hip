@@ -166,7 +166,7 @@ k_b_sweep_xl(const BProb *__restrict__ pr, const BState *__restrict__ st, const 
         for (int k = 0; k < nrun; ++k) {
             const int64_t J0 = (local * nrun + k) * 63;
             if (J0 + 1 >= totalJ) break;  // wave-uniform
-            sweep_x_lanes<2, SCHEME, MIX, ROUTE>(b.U, b.R, b.g, ph, m, J0, totalJ, first, flags,
+            sweep_x_lanes<2, SCHEME, false, MIX, ROUTE>(b.U, b.R, b.g, ph, m, J0, totalJ, first, flags,
                                                  ROUTE ? b.mask[0] : nullptr, sm[wv]);
         }
     }

@@ -35,8 +35,84 @@ struct Axes {
     static constexpr int T2 = (DIR + 2) % ND;
 };
 
-template <int ND>
-using SweepLds = double[ND + 2][kChunk][64];
+// The local frame (n, t1, t2) of an interface of a general mesh, and its area.
+template <int ND, int DIR>
+struct Frame {
+    double mag, nv[3], t1[3], t2[3];
+    // from the node area vectors S_DIR at the four nodes around the interface
+    __device__ __forceinline__ void set(const double (&a)[3], const double (&b)[3], const double (&c)[3],
+                                        const double (&d)[3]) {
+        double Sh[3] = {0.0, 0.0, 0.0};
+        double s2 = 0.0;
+#pragma unroll
+        for (int k = 0; k < ND; ++k) {
+            Sh[k] = (-a[k] + 7.0 * b[k] + 7.0 * c[k] - d[k]) / 12.0;
+            s2 += Sh[k] * Sh[k];
+        }
+        mag = sqrt(s2);
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            nv[k] = k < ND ? Sh[k] / mag : 0.0;
+            t1[k] = t2[k] = 0.0;
+        }
+        // tangent basis: t1 = normalise(e_{DIR+1} - (e_{DIR+1}.n) n), t2 = n x t1
+        if (ND >= 2) {
+            constexpr int TE = (DIR + 1) % (ND > 1 ? ND : 1);
+            const double en = nv[TE];
+            double tn = 0.0;
+#pragma unroll
+            for (int k = 0; k < ND; ++k) {
+                t1[k] = (k == TE ? 1.0 : 0.0) - en * nv[k];
+                tn += t1[k] * t1[k];
+            }
+            tn = sqrt(tn);
+#pragma unroll
+            for (int k = 0; k < ND; ++k) t1[k] /= tn;
+            if (ND == 3) {
+                t2[0] = nv[1] * t1[2] - nv[2] * t1[1];
+                t2[1] = nv[2] * t1[0] - nv[0] * t1[2];
+                t2[2] = nv[0] * t1[1] - nv[1] * t1[0];
+            }
+        }
+    }
+    __device__ __forceinline__ Loc<ND> local(const Pt<ND> &w) const {
+        double mn = 0.0, m1 = 0.0, m2 = 0.0;
+#pragma unroll
+        for (int k = 0; k < ND; ++k) {
+            mn += w.U[1 + k] * nv[k];
+            m1 += w.U[1 + k] * t1[k];
+            m2 += w.U[1 + k] * t2[k];
+        }
+        Loc<ND> o;
+        o.r = w.U[0];
+        o.mn = mn;
+        o.mt[0] = m1;
+        o.mt[1] = m2;
+        o.E = w.U[ND + 1];
+        o.p = w.p;
+        o.a = w.a;
+        o.ri = w.ri;
+        o.hu = mn * (0.5 * w.ri);
+        return o;
+    }
+    __device__ __forceinline__ void global(double Fr, double Fn, const double (&Ft)[2], double FE,
+                                           double (&F)[ND + 2]) const {
+        F[0] = Fr * mag;
+        F[ND + 1] = FE * mag;
+#pragma unroll
+        for (int k = 0; k < ND; ++k) {
+            double v = Fn * nv[k];
+            if (ND >= 2) v += Ft[0] * t1[k];
+            if (ND >= 3) v += Ft[1] * t2[k];
+            F[1 + k] = v * mag;
+        }
+    }
+};
+
+// staging buffer of one wave of an x sweep: a chunk of its rows' points (general
+// meshes: and of S_x and J)
+template <int ND, bool GEN = false>
+using SweepLds = double[ND + 2 + (GEN ? ND + 1 : 0)][kChunk][64];
 
 // ahead-load buffer of one wave of a y or z sweep: two slots of one point's
 // NC component rows (plus a spare row for odd NC)
@@ -51,7 +127,7 @@ template <int ND, int DIR, int SCHEME, bool GEN, bool MIX, bool ROUTE, bool AHEA
 __device__ __forceinline__ void sweep_wave(const double *__restrict__ U, double *__restrict__ R, const Grid &g,
                                            const Phys &ph, const Metrics &m, int64_t seg, int64_t sg, int64_t line0,
                                            int first, unsigned *flags, const uint8_t *__restrict__ mask,
-                                           SweepLds<ND> &sb, AheadLds<ND> &ab) {
+                                           SweepLds<ND, GEN> &sb, AheadLds<ND> &ab) {
     constexpr int NC = ND + 2;
     constexpr int NT = ND - 1;
     constexpr int O1 = DIR == 0 ? 1 : 0;
@@ -128,8 +204,14 @@ __device__ __forceinline__ void sweep_wave(const double *__restrict__ U, double 
     };
 
     int64_t cbase = p0 - 3 - kChunk;  // first point held in the chunk buffer
-    // point q's conserved state into w (from LDS along x, directly otherwise)
-    auto fetch = [&](int64_t qp, Pt<ND> &w) {
+    // General meshes along x: S_x and J come through LDS with the points, for the
+    // same reason (a lane is a row, so loaded directly each is 64 cache lines per
+    // interface: 97 x 80 x 101 130 us, 108 staged); elsewhere they are contiguous.
+    constexpr bool STAGED = GEN && DIR == 0;
+    constexpr int NM = STAGED ? ND + 1 : 1;
+    // point q's conserved state into w (from LDS along x, directly otherwise);
+    // STAGED: its S_x and J into mt
+    auto fetch = [&](int64_t qp, Pt<ND> &w, double (&mt)[NM]) {
         if (DIR == 0) {
             if (qp >= cbase + kChunk) {
                 cbase = qp;
@@ -145,6 +227,11 @@ __device__ __forceinline__ void sweep_wave(const double *__restrict__ U, double 
                     if (xp > last) xp = last;
 #pragma unroll
                     for (int c = 0; c < NC; ++c) sb[c][x][r] = U[rb + xp + c * cs];
+                    if constexpr (STAGED) {
+#pragma unroll
+                        for (int c = 0; c < ND; ++c) sb[NC + c][x][r] = m.S[c * cs + rb + xp];
+                        sb[NC + ND][x][r] = m.J[rb + xp];
+                    }
                 }
                 __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
                 __builtin_amdgcn_wave_barrier();
@@ -153,6 +240,10 @@ __device__ __forceinline__ void sweep_wave(const double *__restrict__ U, double 
             const int xi = (int)(qp - cbase);
 #pragma unroll
             for (int c = 0; c < NC; ++c) w.U[c] = sb[c][xi][lane];
+            if constexpr (STAGED) {
+#pragma unroll
+                for (int c = 0; c < NM; ++c) mt[c] = sb[NC + c][xi][lane];
+            }
         } else {
 #pragma unroll
             for (int c = 0; c < NC; ++c) w.U[c] = U[base + qp * st + c * cs];
@@ -162,13 +253,22 @@ __device__ __forceinline__ void sweep_wave(const double *__restrict__ U, double 
     };
 
     Pt<ND> w[6];
+    double mt[6][NM];
 #pragma unroll
-    for (int k = 0; k < 6; ++k) fetch(p0 - 3 + k, w[k]);
+    for (int k = 0; k < 6; ++k) fetch(p0 - 3 + k, w[k], mt[k]);
     if (ahead && p0 < p1) load_ahead(p0 + 3, (int)((p0 + 3) & 1));
 
     // general meshes: node area vectors S_DIR at f-1 .. f+2 for interface f+1/2
-    double Sw[4][3];
-    if (GEN) {
+    // (staged: and at f+3, with J at f .. f+3)
+    double Sw[5][3], Jw[4];
+    if constexpr (STAGED) {
+#pragma unroll
+        for (int k = 0; k < 5; ++k)
+#pragma unroll
+            for (int c = 0; c < ND; ++c) Sw[k][c] = mt[k + 1][c];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) Jw[k] = mt[k + 2][ND];
+    } else if (GEN) {
 #pragma unroll
         for (int k = 0; k < 4; ++k)
 #pragma unroll
@@ -228,7 +328,7 @@ __device__ __forceinline__ void sweep_wave(const double *__restrict__ U, double 
                 if (f + 1 < p1) load_ahead(f + 4, (int)((f + 4) & 1));
                 __builtin_amdgcn_sched_barrier(0);  // the residual loads stay behind the load
             } else {
-                fetch(f + 3, w[5]);
+                fetch(f + 3, w[5], mt[0]);
             }
             // this node's residual so far, requested now and used after the
             // flux: its memory latency hides behind the flux arithmetic
@@ -236,7 +336,17 @@ __device__ __forceinline__ void sweep_wave(const double *__restrict__ U, double 
 #pragma unroll
                 for (int c = 0; c < NC; ++c) rold[c] = R[c * rcs + ibase + f * ist];
             }
-            if (GEN) {
+            if constexpr (STAGED) {
+#pragma unroll
+                for (int c = 0; c < ND; ++c) {
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) Sw[k][c] = Sw[k + 1][c];
+                    Sw[4][c] = mt[0][c];
+                }
+#pragma unroll
+                for (int k = 0; k < 3; ++k) Jw[k] = Jw[k + 1];
+                Jw[3] = mt[0][ND];
+            } else if (GEN) {
 #pragma unroll
                 for (int k = 0; k < 3; ++k)
 #pragma unroll
@@ -248,63 +358,17 @@ __device__ __forceinline__ void sweep_wave(const double *__restrict__ U, double 
         // the node's metric factor, requested after the new point (whose wait
         // would otherwise cover it too) and used with the residual
         const int64_t fs = f >= p0 ? f : p0;
-        const double sc = GEN ? m.J[base + fs * st] : ih[fs];
+        const double sc = STAGED ? Jw[0] : (GEN ? m.J[base + fs * st] : ih[fs]);
         Loc<ND> P[6];
         double F[NC];
-        double Smag = 1.0;
-        double nv[3] = {0.0, 0.0, 0.0}, t1[3] = {0.0, 0.0, 0.0}, t2[3] = {0.0, 0.0, 0.0};
+        Frame<ND, DIR> fr;  // general meshes
         if (!GEN) {
 #pragma unroll
             for (int k = 0; k < 6; ++k) P[k] = local(w[k]);
         } else {
-            double Sh[3] = {0.0, 0.0, 0.0};
-            double s2 = 0.0;
+            fr.set(Sw[0], Sw[1], Sw[2], Sw[3]);
 #pragma unroll
-            for (int c = 0; c < ND; ++c) {
-                Sh[c] = (-Sw[0][c] + 7.0 * Sw[1][c] + 7.0 * Sw[2][c] - Sw[3][c]) / 12.0;
-                s2 += Sh[c] * Sh[c];
-            }
-            Smag = sqrt(s2);
-#pragma unroll
-            for (int c = 0; c < ND; ++c) nv[c] = Sh[c] / Smag;
-            // tangent basis: t1 = normalise(e_{DIR+1} - (e_{DIR+1}.n) n), t2 = n x t1
-            if (ND >= 2) {
-                constexpr int TE = (DIR + 1) % (ND > 1 ? ND : 1);
-                const double en = nv[TE];
-                double tn = 0.0;
-#pragma unroll
-                for (int c = 0; c < ND; ++c) {
-                    t1[c] = (c == TE ? 1.0 : 0.0) - en * nv[c];
-                    tn += t1[c] * t1[c];
-                }
-                tn = sqrt(tn);
-#pragma unroll
-                for (int c = 0; c < ND; ++c) t1[c] /= tn;
-                if (ND == 3) {
-                    t2[0] = nv[1] * t1[2] - nv[2] * t1[1];
-                    t2[1] = nv[2] * t1[0] - nv[0] * t1[2];
-                    t2[2] = nv[0] * t1[1] - nv[1] * t1[0];
-                }
-            }
-#pragma unroll
-            for (int k = 0; k < 6; ++k) {
-                double mn = 0.0, m1 = 0.0, m2 = 0.0;
-#pragma unroll
-                for (int c = 0; c < ND; ++c) {
-                    mn += w[k].U[1 + c] * nv[c];
-                    m1 += w[k].U[1 + c] * t1[c];
-                    m2 += w[k].U[1 + c] * t2[c];
-                }
-                P[k].r = w[k].U[0];
-                P[k].mn = mn;
-                P[k].mt[0] = m1;
-                P[k].mt[1] = m2;
-                P[k].E = w[k].U[ND + 1];
-                P[k].p = w[k].p;
-                P[k].a = w[k].a;
-                P[k].ri = w[k].ri;
-                P[k].hu = mn * (0.5 * w[k].ri);
-            }
+            for (int k = 0; k < 6; ++k) P[k] = fr.local(w[k]);
         }
         double Fr, Fn, Ft[2], FE;
         // per-interface routing: an interface evaluated by two waves (the
@@ -329,20 +393,14 @@ __device__ __forceinline__ void sweep_wave(const double *__restrict__ U, double 
                 SL = SR;
             }
         }
-        F[0] = Fr * Smag;
-        F[NC - 1] = FE * Smag;
         if (!GEN) {
+            F[0] = Fr;
             F[1 + DIR] = Fn;
             if (NT >= 1) F[1 + Axes<ND, DIR>::T1] = Ft[0];
             if (NT >= 2) F[1 + Axes<ND, DIR>::T2] = Ft[1];
+            F[NC - 1] = FE;
         } else {
-#pragma unroll
-            for (int c = 0; c < ND; ++c) {
-                double v = Fn * nv[c];
-                if (NT >= 1) v += Ft[0] * t1[c];
-                if (NT >= 2) v += Ft[1] * t2[c];
-                F[1 + c] = v * Smag;
-            }
+            fr.global(Fr, Fn, Ft, FE, F);
         }
         if (f >= p0 && active) {
             double v[NC];
@@ -372,7 +430,7 @@ template <int ND, int DIR, int SCHEME, bool GEN, bool MIX, bool ROUTE, bool EXTR
 __device__ __forceinline__ void sweep_block(const double *__restrict__ U, double *__restrict__ R, const Grid &g,
                                             const Phys &ph, const Metrics &m, int64_t seg, int64_t nseg, int first,
                                             unsigned *flags, const uint8_t *__restrict__ mask, int64_t blk,
-                                            SweepLds<ND> *sbuf, AheadLds<ND> *abuf) {
+                                            SweepLds<ND, GEN> *sbuf, AheadLds<ND> *abuf) {
     constexpr int O1 = DIR == 0 ? 1 : 0;
     constexpr int O2 = DIR == 2 ? 1 : 2;
     const int64_t lines = g.n[O1] * g.n[O2];
@@ -406,7 +464,7 @@ template <int ND, int DIR, int SCHEME, bool GEN, bool MIX, bool ROUTE>
 __global__ void __launch_bounds__(64 * kWaves, GEN ? 1 : 2)
 k_sweep(const double *__restrict__ U, double *__restrict__ R, Grid g, Phys ph, Metrics m, int64_t seg,
         int64_t nseg, int first, unsigned *flags, const uint8_t *__restrict__ mask) {
-    __shared__ SweepLds<ND> sbuf[DIR == 0 ? kWaves : 1];
+    __shared__ SweepLds<ND, GEN> sbuf[DIR == 0 ? kWaves : 1];
     __shared__ AheadLds<ND> abuf[DIR == 0 || GEN ? 1 : kWaves];
     sweep_block<ND, DIR, SCHEME, GEN, MIX, ROUTE, false>(U, R, g, ph, m, seg, nseg, first, flags, mask, blockIdx.x,
                                                          sbuf, abuf);
@@ -431,7 +489,10 @@ k_sweep_yz(const double *__restrict__ U, double *__restrict__ R, double *__restr
 }
 
 // ---------------------------------------------------------------------------
-// x sweep on separable meshes with lanes along x.  The interfaces of all rows
+// x sweep with lanes along x.  On general meshes it also keeps the six points in
+// the interface's frame only, not a window in the mesh's besides, so that two
+// waves fit a SIMD where the march has one (97 x 80 x 101 62 us, the march 108;
+// 1024 x 1024 47 and 97).  The interfaces of all rows
 // are numbered J = row * (N + 1) + (q + 1) for the interface q + 1/2,
 // q = -1 .. N-1 (the interface-grid order of the routing masks).  A wave owns
 // 64 consecutive interfaces J0 .. J0 + 63, J0 = 63 w: consecutive waves share
@@ -443,17 +504,17 @@ k_sweep_yz(const double *__restrict__ U, double *__restrict__ R, double *__restr
 // N + 1 >= 64 (at most one row start per wave).
 constexpr int kXlSlots = 64 + 10;
 
-template <int ND>
+template <int ND, bool GEN = false>
 struct XlLds {
-    double pt[ND + 5][kXlSlots];  // U[0..nc), ri, p, a of the staged points
+    double pt[ND + 5 + (GEN ? ND : 0)][kXlSlots];  // U[0..nc), ri, p, a (general meshes: S_x) of the staged points
     double fl[ND + 2][64];        // interface fluxes of the wave
 };
 
-template <int ND, int SCHEME, bool MIX, bool ROUTE>
+template <int ND, int SCHEME, bool GEN, bool MIX, bool ROUTE>
 __device__ __forceinline__ void sweep_x_lanes(const double *__restrict__ U, double *__restrict__ R, const Grid &g,
                                               const Phys &ph, const Metrics &m, int64_t J0, int64_t totalJ,
                                               int first, unsigned *flags, const uint8_t *__restrict__ mask,
-                                              XlLds<ND> &sm) {
+                                              XlLds<ND, GEN> &sm) {
     constexpr int NC = ND + 2;
     constexpr int NT = ND - 1;
     const int lane = threadIdx.x & 63;
@@ -487,13 +548,17 @@ __device__ __forceinline__ void sweep_x_lanes(const double *__restrict__ U, doub
     const int64_t rowb = ext_index(g, 0, yl, zl);
     bool bad = false;
 
-    auto put = [&](int slot, Pt<ND> &w) {
+    auto put = [&](int slot, Pt<ND> &w, const double (&S)[3]) {
         finish_point<ND>(ph, w, bad);
 #pragma unroll
         for (int c = 0; c < NC; ++c) sm.pt[c][slot] = w.U[c];
         sm.pt[NC][slot] = w.ri;
         sm.pt[NC + 1][slot] = w.p;
         sm.pt[NC + 2][slot] = w.a;
+        if constexpr (GEN) {
+#pragma unroll
+            for (int c = 0; c < ND; ++c) sm.pt[NC + 3 + c][slot] = S[c];
+        }
     };
     // Every lane stages the point q + 3 of its row.  Lanes 0..4 also stage
     // the points q0 - 2 .. q0 + 2 of lane 0's row, lanes 5..9 the points
@@ -518,21 +583,50 @@ __device__ __forceinline__ void sweep_x_lanes(const double *__restrict__ U, doub
         w0.U[c] = U[rowb + q + 3 + c * cs];
         w1.U[c] = U[xb + xp + c * cs];
     }
-    put(lane, w0);
-    if (extra) put(64 + lane, w1);
+    double S0[3] = {0.0, 0.0, 0.0}, S1[3] = {0.0, 0.0, 0.0};
+    if constexpr (GEN) {
+#pragma unroll
+        for (int c = 0; c < ND; ++c) {
+            S0[c] = m.S[rowb + q + 3 + c * cs];
+            S1[c] = m.S[xb + xp + c * cs];
+        }
+    }
+    put(lane, w0, S0);
+    if (extra) put(64 + lane, w1, S1);
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 
     // stencil q - 2 .. q + 3 of this lane
     const bool inrow0 = lane < Lnext;
+    auto slot_of = [&](int k) {
+        const int src = lane - 5 + k;
+        if (inrow0) return src >= 0 ? src : 64 + lane + k;
+        return src >= Lnext ? src : 69 + (lane - Lnext) + k;
+    };
     Loc<ND> P[6];
+    Frame<ND, 0> fr;  // general meshes
+    if constexpr (GEN) {
+        double S[4][3];
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+#pragma unroll
+            for (int c = 0; c < ND; ++c) S[k][c] = sm.pt[NC + 3 + c][slot_of(k + 1)];
+        fr.set(S[0], S[1], S[2], S[3]);
+    }
 #pragma unroll
     for (int k = 0; k < 6; ++k) {
-        const int src = lane - 5 + k;
-        int slot;
-        if (inrow0) slot = src >= 0 ? src : 64 + lane + k;
-        else slot = src >= Lnext ? src : 69 + (lane - Lnext) + k;
+        const int slot = slot_of(k);
+        if constexpr (GEN) {
+            Pt<ND> w;
+#pragma unroll
+            for (int c = 0; c < NC; ++c) w.U[c] = sm.pt[c][slot];
+            w.ri = sm.pt[NC][slot];
+            w.p = sm.pt[NC + 1][slot];
+            w.a = sm.pt[NC + 2][slot];
+            P[k] = fr.local(w);
+            continue;
+        }
         P[k].r = sm.pt[0][slot];
         P[k].mn = sm.pt[1][slot];
         if (NT >= 1) P[k].mt[0] = sm.pt[1 + Axes<ND, 0>::T1][slot];
@@ -556,14 +650,18 @@ __device__ __forceinline__ void sweep_x_lanes(const double *__restrict__ U, doub
     } else {
         // routed forms: full flux in FP64 (as in the marching sweeps)
         if (MIX && !ROUTE) char_flux_mixed<ND, SCHEME>(P, ph, Fr, Fn, Ft, FE);
-        else char_flux<ND, SCHEME, false>(P, ph, Fr, Fn, Ft, FE);
+        else char_flux<ND, SCHEME, GEN>(P, ph, Fr, Fn, Ft, FE);
     }
     double F[NC];
-    F[0] = Fr;
-    F[1] = Fn;
-    if (NT >= 1) F[1 + Axes<ND, 0>::T1] = Ft[0];
-    if (NT >= 2) F[1 + Axes<ND, 0>::T2] = Ft[1];
-    F[NC - 1] = FE;
+    if constexpr (GEN) {
+        fr.global(Fr, Fn, Ft, FE, F);
+    } else {
+        F[0] = Fr;
+        F[1] = Fn;
+        if (NT >= 1) F[1 + Axes<ND, 0>::T1] = Ft[0];
+        if (NT >= 2) F[1 + Axes<ND, 0>::T2] = Ft[1];
+        F[NC - 1] = FE;
+    }
 #pragma unroll
     for (int c = 0; c < NC; ++c) sm.fl[c][lane] = F[c];
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -571,7 +669,7 @@ __device__ __forceinline__ void sweep_x_lanes(const double *__restrict__ U, doub
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     // node q: its left interface belongs to lane - 1 of the same row
     if (valid && lane >= 1 && q >= 0 && lane != Lnext) {
-        const double sc = m.invh[0][q];
+        const double sc = GEN ? m.J[rowb + q] : m.invh[0][q];
         const int64_t oi = yl * g.is[1] + zl * g.is[2] + q;
         double v[NC];
 #pragma unroll
@@ -582,16 +680,17 @@ __device__ __forceinline__ void sweep_x_lanes(const double *__restrict__ U, doub
 }
 
 // three waves per SIMD (168 registers); TENO6's four stencils spill there,
-// so it runs at two (180 registers, x sweep 0.87 -> 0.86 ms at 256^3)
-template <int ND, int SCHEME, bool MIX, bool ROUTE>
-__global__ void __launch_bounds__(64 * kWaves, SCHEME == OSBLI_TENO6 ? 2 : 3)
+// so it runs at two (180 registers, x sweep 0.87 -> 0.86 ms at 256^3), and so
+// does the FP64 form on general 3D meshes (196 registers)
+template <int ND, int SCHEME, bool GEN, bool MIX, bool ROUTE>
+__global__ void __launch_bounds__(64 * kWaves, SCHEME == OSBLI_TENO6 || (GEN && ND == 3 && !MIX) ? 2 : 3)
 k_sweep_xl(const double *__restrict__ U, double *__restrict__ R, Grid g, Phys ph, Metrics m, int64_t totalJ,
            int first, unsigned *flags, const uint8_t *__restrict__ mask) {
-    __shared__ XlLds<ND> sm[kWaves];
+    __shared__ XlLds<ND, GEN> sm[kWaves];
     const int64_t gw = (int64_t)blockIdx.x * (blockDim.x >> 6) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t J0 = gw * 63;
     if (J0 + 1 >= totalJ) return;  // wave-uniform: no node left
-    sweep_x_lanes<ND, SCHEME, MIX, ROUTE>(U, R, g, ph, m, J0, totalJ, first, flags, mask, sm[threadIdx.x >> 6]);
+    sweep_x_lanes<ND, SCHEME, GEN, MIX, ROUTE>(U, R, g, ph, m, J0, totalJ, first, flags, mask, sm[threadIdx.x >> 6]);
 }
 
 }  // namespace cf
