@@ -389,8 +389,9 @@ int osbli_batch_create(osbli_batch **batch, osbli_ctx *const *ctxs, int nprob, d
  * captured graphs.  Synchronising. */
 int osbli_batch_set_tiles(osbli_batch *batch, const int64_t *seg, void *stream);
 
-/* Workgroups of each persistent sweep launch, 1..65536 (0: the defaults,
- * 2048 for the lanes-along-x sweep, 1024 for the marching ones).  Results do
+/* Workgroups of each persistent sweep launch, 1..65536 (0: the defaults, 8192
+ * for the one-pass stage, 2048 for the lanes-along-x sweep, 1024 for the
+ * marching ones).  Results do
  * not depend on it.  Drops any captured graphs. */
 int osbli_batch_set_grid(osbli_batch *batch, int sweep_blocks);
 
