@@ -258,3 +258,34 @@ def test_general_mesh_x_lanes(n, scheme):
     s.check()
     scale = b.abs().amax(dim=(1, 2, 3), keepdim=True)
     assert float(((a - b).abs() / scale).max()) <= 1e-13
+
+
+@pytest.mark.parametrize("n", [(33, 31, 40), (70, 40, 37)])
+def test_routed_step_3d(n):
+    """Learned routing in whole 3D steps (y and z sweeps in one launch with their
+    masks, FP64 form): one step with a random network against the separate calls,
+    1e-13 of the component's largest value; some interfaces go either way."""
+    import torch
+    from paper_2007_14933_amd import inputs as I
+    from paper_2007_14933_amd import sensor as SN
+    from paper_2007_14933_amd.solver import Solver
+    prob = I.smooth_random(3, n, seed=n[0], amp=0.2, Re=200.0).with_(scheme=I.TENO5)
+    w = SN.init_weights(4) * 3.0
+    w[1440] = 3.2  # output bias: near the network's spread on this flow
+    bits = SN.bf16_bits(w)
+    a, b = Solver(prob, sensor=1), Solver(prob, sensor=1)
+    for s in (a, b):
+        s.set_sensor(bits, 0.5, dilate=1)
+        s.apply_bc()
+    dt = a.compute_dt(0.5)
+    a.step(dt)
+    for k in range(b.nstages):
+        b.substep(k, dt)
+        b.apply_bc()
+    a.check()
+    smooth, total = a.sensor_stats()
+    say("[gpu shapes] routed 3D step, smooth", smooth, "of", total)
+    assert (smooth, total) == b.sensor_stats() and 0 < smooth < total
+    torch.cuda.synchronize()
+    scale = b.U.abs().amax(dim=(1, 2, 3), keepdim=True)
+    assert float(((a.U - b.U).abs() / scale).max()) <= 1e-13
