@@ -47,6 +47,30 @@ __global__ void k_ghosts(double *__restrict__ U, Grid g, Phys ph, int dir, int k
     ghost_fill<ND>(U, g, ph, dir, kind0, kind1, t);
 }
 
+// x ghosts that are copies (periodic, extrapolated; Dirichlet sides stay): a
+// thread per ghost node, so that a row's three nodes per side are one access.
+// With a thread per row and side (k_ghosts) neighbouring lanes are whole rows
+// apart: 512 x 256 x 256 74 us, 29 so.
+template <int ND>
+__global__ void k_ghosts_x(double *__restrict__ U, Grid g, int kind0, int kind1) {
+    constexpr int NC = ND + 2, per = 2 * kGhost;
+    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t row = t / per;
+    if (row >= g.e[1] * g.e[2]) return;
+    const int l = (int)(t - row * per), m = l % kGhost;
+    const bool right = l >= kGhost;
+    const int kind = right ? kind1 : kind0;
+    if (kind == OSBLI_DIRICHLET) return;
+    const int64_t N = g.n[0], base = (row % g.e[1]) * g.es[1] + (row / g.e[1]) * g.es[2] + kGhost;
+    const int64_t dst = base + (right ? N + m : m - kGhost);
+    const int64_t src = base + (kind == OSBLI_PERIODIC ? (right ? m : N - kGhost + m) : (right ? N - 1 : 0));
+    double v[NC];
+#pragma unroll
+    for (int c = 0; c < NC; ++c) v[c] = U[src + c * g.enpts];
+#pragma unroll
+    for (int c = 0; c < NC; ++c) U[dst + c * g.enpts] = v[c];
+}
+
 // All directions periodic: every ghost node (edges and corners included)
 // copies the interior node its wrapped coordinates name, in one launch (the
 // three direction passes compose to the same copies).  Items enumerate the
@@ -120,6 +144,15 @@ hipError_t bc_nd(const Grid &g, const Phys &ph, const osbli_params &p, double *U
     for (int d = 0; d < ND; ++d) {
         const int o1 = d == 0 ? 1 : 0, o2 = d == 2 ? 1 : 2;
         const int64_t nt = 2 * g.e[o1] * g.e[o2];
+        auto copies = [&](int kind) { return kind != OSBLI_ISOTHERMAL_WALL && kind != OSBLI_ADIABATIC_WALL; };
+        if (d == 0 && copies(p.bc_kind[0][0]) && copies(p.bc_kind[0][1])) {
+            const int64_t nx = 2 * kGhost * g.e[1] * g.e[2];
+            hipLaunchKernelGGL((k_ghosts_x<ND>), dim3((unsigned)((nx + bs - 1) / bs)), dim3(bs), 0, s, U, g,
+                               p.bc_kind[0][0], p.bc_kind[0][1]);
+            hipError_t e = hipGetLastError();
+            if (e != hipSuccess) return e;
+            continue;
+        }
         hipLaunchKernelGGL((k_ghosts<ND>), dim3((unsigned)((nt + bs - 1) / bs)), dim3(bs), 0, s, U, g, ph, d,
                            p.bc_kind[d][0], p.bc_kind[d][1]);
         hipError_t e = hipGetLastError();

@@ -289,3 +289,32 @@ def test_routed_step_3d(n):
     torch.cuda.synchronize()
     scale = b.U.abs().amax(dim=(1, 2, 3), keepdim=True)
     assert float(((a.U - b.U).abs() / scale).max()) <= 1e-13
+
+
+@pytest.mark.parametrize("n", [(5,), (300,), (6, 5), (67, 9), (6, 5, 7), (70, 11, 9)])
+@pytest.mark.parametrize("left,right", [("p", "p"), ("e", "e"), ("d", "d"), ("e", "d"), ("d", "e")])
+def test_x_ghost_copies(n, left, right):
+    """x ghosts of grids that are not periodic throughout: copies of the nodes that
+    the boundary kinds name, Dirichlet ghosts untouched; whole values, compared
+    exactly (the other directions are extrapolated)."""
+    from paper_2007_14933_amd import inputs as I
+    from paper_2007_14933_amd.solver import Solver
+    if left == "p" and (n[0] < 6 or len(n) == 1):
+        pytest.skip("periodic lines hold six nodes; a periodic line alone takes the other kernel")
+    nd, kind = len(n), {"p": I.PERIODIC, "e": I.EXTRAPOLATE, "d": I.DIRICHLET}
+    n3 = n + (1,) * (3 - nd)
+    prob = I.smooth_random(nd, n3, seed=3, amp=0.2).with_(
+        bc=((kind[left], kind[right]), (I.EXTRAPOLATE,) * 2, (I.EXTRAPOLATE,) * 2))
+    s = Solver(prob)
+    before = s.U.cpu().numpy().copy()
+    s.apply_bc()
+    U = s.U.cpu().numpy()
+    h = [3 if d < nd else 0 for d in range(3)]
+    core = before[:, h[2]:h[2] + n3[2], h[1]:h[1] + n3[1], :]
+    got = U[:, h[2]:h[2] + n3[2], h[1]:h[1] + n3[1], :]
+    N = n[0]
+    for side, k in ((0, left), (1, right)):
+        for m in range(3):
+            g = 3 + N + m if side else m
+            src = {"p": 3 + m if side else N + m, "e": 3 + N - 1 if side else 3, "d": g}[k]
+            assert np.array_equal(got[..., g], core[..., src]), (side, m)
