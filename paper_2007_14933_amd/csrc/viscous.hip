@@ -556,14 +556,15 @@ struct StepTiles {
 };
 
 // Runs of planes: a block's run costs its planes and about six steps (four
-// planes of fluxes more than it updates, the first loads), one block per CU.
+// planes of fluxes more than it updates, the first loads), one block per CU.  At
+// most 1024 runs are tried (the search is host time of every launch).
 inline StepTiles step_tiles(const Grid &g) {
     StepTiles T;
     T.tx = (int)((g.n[0] + kSX - 1) / kSX);
     T.ty = (int)((g.n[1] + kSY - 1) / kSY);
     int64_t cost = INT64_MAX;
     T.tz = 1;
-    for (int64_t k = 1; k <= g.n[2]; ++k) {
+    for (int64_t k = 1; k <= g.n[2] && k <= 1024; ++k) {
         const int64_t blocks = T.tx * T.ty * k, run = (g.n[2] + k - 1) / k;
         const int64_t t = (blocks + 255) / 256 * (run + 6);
         if (t < cost) {
