@@ -1,0 +1,122 @@
+"""GPU tests of calls that reach the same result by different kernels: whole
+steps against the separate calls, the batch's steps against its substeps."""
+import numpy as np
+import pytest
+
+from paper_2007_14933_amd import inputs as I
+from parity_util import say
+
+pytestmark = pytest.mark.gpu
+
+
+def jump_net(bias):
+    """Bits of a hand-set network: logit = bias - 10 (sum of the six log jumps)."""
+    from paper_2007_14933_amd import sensor as SN
+    w = np.zeros(1441, dtype=np.float32)
+    w[[i * 32 for i in range(4, 10)]] = 1.0  # W1[i][0]
+    w[352] = 1.0                             # W2[0][0]
+    w[1408] = -10.0                          # w3[0]
+    w[1440] = bias                           # b3
+    return SN.bf16_bits(w)
+
+
+def routing_net(prob):
+    """The jump_net that calls most interfaces of the problem's state smooth, but
+    not all."""
+    from paper_2007_14933_amd.solver import Solver
+    s = Solver(prob, sensor=1)
+    s.apply_bc()
+    best = None
+    for bias in range(61):
+        bits = jump_net(bias)
+        s.set_sensor(bits, 0.5)
+        s.sensor_update()
+        sm, tot = s.sensor_stats()
+        if best is None or abs(sm / tot - 0.7) < best[0]:
+            best = (abs(sm / tot - 0.7), bits)
+    assert best[0] < 0.25
+    return best[1]
+
+
+def step_and_separate(prob, steps, net=None, dilate=1, every=0, **kw):
+    """States after whole steps and after the same steps by separate calls."""
+    import torch
+    from paper_2007_14933_amd.solver import Solver
+    a, b = Solver(prob, **kw), Solver(prob, **kw)
+    for s in (a, b):
+        if net is not None:
+            s.set_sensor(net, 0.5, dilate=dilate, every_substage=every)
+        s.apply_bc()
+    dt = 0.5 * a.compute_dt(0.5)
+    for _ in range(steps):
+        a.step(dt)
+        for k in range(b.nstages):
+            b.substep(k, dt)
+            b.apply_bc()
+    a.check()
+    torch.cuda.synchronize()
+    if net is not None:
+        assert a.sensor_stats() == b.sensor_stats()
+    return a, b
+
+
+@pytest.mark.parametrize("form", [0, 1])
+@pytest.mark.parametrize("n", [(60,), (255,), (256,), (31, 6), (32, 7), (33, 8), (70, 64)])
+def test_routed_steps_equal_separate_calls(n, form):
+    """Learned routing through the one-pass stage, tiles of 255 and of 32 x 7 nodes
+    and their edges, every width of the neighbourhood, masks refreshed at every
+    step or substage: two steps give the bits of the separate calls."""
+    import torch
+    prob = I.smooth_random(len(n), n + (1,) * (3 - len(n)), seed=n[0], amp=0.2)
+    net = routing_net(prob)
+    for dilate, every in ((0, 0), (1, 0), (2, 0), (1, 1)):
+        a, b = step_and_separate(prob, 2, net, dilate, every, form=form, sensor=1)
+        err = float((a.U - b.U).abs().max())
+        say("[gpu routes] routed", n, "form", form, "dilate", dilate, "every", every, "max|diff|", err)
+        assert torch.equal(a.U, b.U), err
+
+
+@pytest.mark.parametrize("form,scheme,sensor", [(0, I.TENO5, 0), (0, I.WENOZ5, 0), (0, I.TENO5, 1), (1, I.TENO5, 1),
+                                                (1, I.TENO5, 0)])
+def test_batch_steps_substeps_and_solo_calls(form, scheme, sensor):
+    """A batch's steps, its substeps (captured or not, whatever their tiles) and the
+    problems alone by separate calls: the same bits after six steps."""
+    import torch
+    from paper_2007_14933_amd.batch import Batch
+    from paper_2007_14933_amd.solver import Solver
+    rng = np.random.default_rng(11)
+    probs = [I.riemann2d(n, rng, t_end=1e9, scheme=scheme) for n in (32, 100, 24, 64, 71)]
+    bits = jump_net(3.0)
+    kw = dict(weights=bits, threshold=0.5) if sensor else {}
+    make = lambda capture: Batch(probs, form=form, sensor=sensor, capture=capture, **kw)  # noqa: E731
+    whole, parts = make(True), [make(True)]
+    for seg, capture in ((1, False), (8, True), (1024, False)):
+        b = make(False)
+        b.set_tiles(np.full((len(probs), 2), seg))
+        if capture:
+            b.capture()
+        parts.append(b)
+    direct = make(False)
+    solo = [Solver(p, form=form, sensor=sensor) for p in probs]
+    for s in solo:
+        if sensor:
+            s.set_sensor(bits, 0.5)
+        s.apply_bc()
+    for _ in range(6):
+        whole.step()
+        direct.step()
+        for b in parts:
+            for k in range(3):
+                b.substep(k)
+        for s in solo:
+            dt = s.compute_dt(0.5)
+            for k in range(3):
+                s.substep(k, dt)
+                s.apply_bc()
+    torch.cuda.synchronize()
+    if sensor:
+        sm, tot = whole.solvers[1].sensor_stats()
+        assert 0 < sm < tot
+    for p, s in enumerate(solo):
+        for b in [whole, direct] + parts:
+            assert torch.equal(b.solvers[p].U, s.U), (p, float((b.solvers[p].U - s.U).abs().max()))
