@@ -489,7 +489,7 @@ k_sweep_yz(const double *__restrict__ U, double *__restrict__ R, double *__restr
 }
 
 // ---------------------------------------------------------------------------
-// x sweep with lanes along x.  On general meshes it also keeps the six points in
+// x sweep with lanes along x.  On general meshes (FP64 form) it also keeps the six points in
 // the interface's frame only, not a window in the mesh's besides, so that two
 // waves fit a SIMD where the march has one (97 x 80 x 101 62 us, the march 108;
 // 1024 x 1024 47 and 97).  The interfaces of all rows

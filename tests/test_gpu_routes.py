@@ -120,3 +120,33 @@ def test_batch_steps_substeps_and_solo_calls(form, scheme, sensor):
     for p, s in enumerate(solo):
         for b in [whole, direct] + parts:
             assert torch.equal(b.solvers[p].U, s.U), (p, float((b.solvers[p].U - s.U).abs().max()))
+
+
+def wavy(prob):
+    nd = prob.ndim
+    X = [np.array(c, dtype=float) for c in prob.coords[:nd]]
+    wave = sum(np.sin(2.0 * np.pi * c) for c in X)
+    return prob.with_(coords1d=None, coords_full=tuple(c + 0.02 * wave for c in X) + (None,) * (3 - nd))
+
+
+@pytest.mark.parametrize("scheme", ["WENOZ5", "TENO5"])
+@pytest.mark.parametrize("n", [(62, 30), (63, 30), (70, 131), (190, 9), (64, 7, 9), (97, 40, 33)])
+def test_precision_form_on_general_meshes(n, scheme):
+    """The precision form on wavy meshes around and beyond the width from which the
+    FP64 form's x lanes run along x: the launch shape of the x sweep does not
+    change a bit, and the residual is the FP64 form's to FP32 rounding (in the mean
+    2^-22 of each component's largest value: some four roundings of deviations no
+    larger than that; single nodes may flip a cut-off decision)."""
+    import torch
+    from paper_2007_14933_amd.solver import Solver
+    prob = wavy(I.smooth_random(len(n), n + (1,) * (3 - len(n)), seed=n[0], amp=0.2)).with_(scheme=getattr(I, scheme))
+    s, ref = Solver(prob, form=1), Solver(prob)
+    for q in (s, ref):
+        q.apply_bc()
+    a = s.residual().clone()
+    s.set_sweep_segments([n[0], 0, 0])
+    assert torch.equal(s.residual(), a)
+    r = ref.residual()
+    err = ((a - r).abs() / r.abs().amax(dim=(1, 2, 3), keepdim=True)).mean()
+    say("[gpu routes] precision form, general mesh", n, scheme, float(err))
+    assert float(err) <= 2.0 ** -22
