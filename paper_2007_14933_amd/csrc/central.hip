@@ -17,9 +17,10 @@
 // Two storage strategies for the same arithmetic (section 6.1, "low memory
 // intensity algorithms"):
 //   StoreSome: in 3D nothing is stored between the state and the residual where
-//     every stencil is centred (k_c_resid_zm); near non-periodic ends, and in
-//     1D and 2D, only the velocity gradients g_ab are (one pointwise pass) and
-//     everything else is recomputed inside the residual kernel;
+//     every stencil is centred (k_c_resid_zm); near non-periodic ends, on small
+//     bounded grids (zm_pays), and in 1D and 2D, only the velocity gradients g_ab
+//     are (one pointwise pass) and everything else is recomputed inside the
+//     residual kernel;
 //   store-all: every derivative goes to its own work array in its own pass
 //     (flux derivatives, first derivatives of u, T, mu~, kappa, second and
 //     mixed derivatives), and a pointwise pass assembles them, the practice
@@ -766,6 +767,29 @@ k_cb_assemble(const double *__restrict__ U, CWork W, Grid g, Phys ph, double *__
 
 inline size_t al256(size_t x) { return (x + 255) & ~size_t(255); }
 
+// Whether the z-marching pass is worth its company near bounded ends.  There the
+// node passes run too, and wherever a block of 64 x 4 nodes holds one such node
+// they cost almost what they cost for all of it: ends in x take every block of a
+// row of up to 128 nodes.  ends: the share of such blocks; lanes: the node
+// passes' threads, which their time goes by (0.16 to 0.21 ns each, inviscid
+// 0.05).  The march saves about the rest of that time less 0.3 of it, and its
+// launch and the blocks that only look cost some 30 us (inviscid 10).  Residuals,
+// both ways (march, node passes) in us: 32^3 bounded in x 43 and 24, in z 31 and
+// 20; 64^3 in z 43 and 53, in y and z 59 and 52; 96^3 in x 248 and 202, in y 104
+// and 182; 144^3 in x 594 and 774; inviscid 64^3 in z 22 and 16, 96^3 in y 37 and
+// 54, 144^3 in x 165 and 146, 256^3 in x 688 and 822.
+inline bool zm_pays(const Grid &g, bool visc) {
+    if (g.periodic[0] && g.periodic[1] && g.periodic[2]) return true;
+    const int64_t bx = (g.n[0] + kBX - 1) / kBX, by = (g.n[1] + kBY - 1) / kBY;
+    auto inner = [&](int d, int64_t blocks, int64_t two) {
+        return g.periodic[d] ? blocks : (blocks > two ? blocks - two : 0);
+    };
+    const double lanes = (double)(bx * kBX) * (double)g.n[1] * (double)g.n[2];
+    const double ends = 1.0 - (double)(inner(0, bx, 2) * inner(1, by, 2) * inner(2, g.n[2], 4)) /
+                                  ((double)(bx * by) * (double)g.n[2]);
+    return visc ? lanes * (0.85 - ends) >= 2e5 : lanes * (0.64 - ends) >= 3e5;
+}
+
 template <bool VISC, bool STEP>
 void launch_zm(const Grid &g, const Phys &ph, const Metrics &m, const double *U, double *out, double *dU, RkStage rs,
                double dt, hipStream_t s) {
@@ -783,14 +807,15 @@ hipError_t central_nd(const Grid &g, const Phys &ph, const Metrics &m, const dou
     const ColTiles T = col_tiles(g);
     const dim3 nb((unsigned)(8 * T.per)), bs(kBX, kBY);
     if (!work) {
-        if constexpr (ND == 3) {
-            launch_zm<VISC, false>(g, ph, m, U, R, nullptr, RkStage{0.0, 0.0, 1, 1}, 0.0, s);
-            if (!(g.periodic[0] && g.periodic[1] && g.periodic[2])) {
-                if (VISC) hipLaunchKernelGGL((k_c_grad<ND>), nb, bs, 0, s, U, Gs, g, m, T, 1);
-                hipLaunchKernelGGL((k_c_resid<ND, VISC>), nb, bs, 0, s, U, Gs, g, ph, m, R, T, 1);
+        if constexpr (ND == 3)
+            if (zm_pays(g, VISC)) {
+                launch_zm<VISC, false>(g, ph, m, U, R, nullptr, RkStage{0.0, 0.0, 1, 1}, 0.0, s);
+                if (!(g.periodic[0] && g.periodic[1] && g.periodic[2])) {
+                    if (VISC) hipLaunchKernelGGL((k_c_grad<ND>), nb, bs, 0, s, U, Gs, g, m, T, 1);
+                    hipLaunchKernelGGL((k_c_resid<ND, VISC>), nb, bs, 0, s, U, Gs, g, ph, m, R, T, 1);
+                }
+                return hipGetLastError();
             }
-            return hipGetLastError();
-        }
         if (VISC) hipLaunchKernelGGL((k_c_grad<ND>), nb, bs, 0, s, U, Gs, g, m, T, 0);
         hipLaunchKernelGGL((k_c_resid<ND, VISC>), nb, bs, 0, s, U, Gs, g, ph, m, R, T, 0);
         return hipGetLastError();

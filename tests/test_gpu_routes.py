@@ -150,3 +150,57 @@ def test_precision_form_on_general_meshes(n, scheme):
     err = ((a - r).abs() / r.abs().amax(dim=(1, 2, 3), keepdim=True)).mean()
     say("[gpu routes] precision form, general mesh", n, scheme, float(err))
     assert float(err) <= 2.0 ** -22
+
+
+def central(n, bounded, Re, sutherland=0, **kw):
+    bc = tuple((I.EXTRAPOLATE,) * 2 if d in bounded else (I.PERIODIC,) * 2 for d in range(3))
+    return I.smooth_random(3, n, seed=n[0], amp=0.05, Re=Re, M=0.5).with_(scheme=I.CENTRAL4, bc=bc,
+                                                                         sutherland=sutherland, **kw)
+
+
+@pytest.mark.parametrize("n,bounded,Re,sutherland", [
+    ((66, 18, 130), (2,), 200.0, 0), ((66, 18, 130), (2,), 200.0, 1), ((66, 34, 130), (2,), 0.0, 0),
+    ((300, 24, 64), (0,), 200.0, 0), ((321, 40, 40), (0, 1, 2), 200.0, 1), ((70, 97, 40), (1,), 200.0, 0),
+    ((96, 40, 33), (0,), 200.0, 0), ((96, 40, 33), (0,), 0.0, 0)])
+def test_central_bounded_grids(n, bounded, Re, sutherland):
+    """The central residual of bounded 3D grids large enough for the z-marching pass
+    with the node passes at the ends (the last two: not), one step against the
+    oracle at the run bound 1e-11."""
+    from parity_util import gpu_run, normwise_rel, oracle_run
+    prob = central(n, bounded, Re, sutherland)
+    say("[gpu routes] central", n, bounded, Re, sutherland)
+    Ug, tg, _ = gpu_run(prob, 1)
+    Uo, to = oracle_run(prob, 1)
+    err = normwise_rel(I.interior_view(3, Ug), I.interior_view(3, Uo))
+    assert abs(tg - to) <= 1e-12 * to and err.max() <= 1e-11, err
+
+
+def best_us(f, reps=50, rounds=8):
+    """Shortest mean time of f over some rounds, microseconds."""
+    import torch
+    f()
+    best = float("inf")
+    for _ in range(rounds):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        for _ in range(reps):
+            f()
+        b.record()
+        b.synchronize()
+        best = min(best, 1e3 * a.elapsed_time(b) / reps)
+    return best
+
+
+def test_central_small_bounded_grids_cost_alike():
+    """On a small cube the direction that is bounded does not decide the residual's
+    time (beside the z-marching pass the node passes at ends in x cost a whole pass
+    more: 1.9 times the time of ends in z)."""
+    from paper_2007_14933_amd.solver import Solver
+    t = []
+    for d in (0, 2):
+        s = Solver(central((48, 48, 48), (d,), 0.0))
+        s.apply_bc()
+        R = s.residual()
+        t.append(best_us(lambda: s.residual(R=R)))
+    say("[gpu routes] central 48^3 bounded in x, z: us", t)
+    assert t[0] <= 1.4 * t[1]
