@@ -359,27 +359,31 @@ k_c_resid(const double *__restrict__ U, const double *__restrict__ Gs, Grid g, P
 // A block owns a kCX x kCY tile of columns and marches zrun planes; a node's
 // primitives are computed once, into an LDS ring of three planes with a
 // two-node halo (72 KB: two blocks per CU, so that one works at the other's
-// barriers), from where its x and y neighbours read them; the z neighbours' are
-// a register window.  Bytes: read U, write the residual, 80 a node.  The
-// node-per-thread passes (gradients stored, every node's primitives computed
-// fifteen times, 75 values fetched per node through the caches) took 1.17 +
-// 0.36 ms at 192^3, this one 0.21 ms.  Nodes near a non-periodic end are left
-// to those passes.
+// barriers; with Sutherland's law 81 KB and one), from where its x and y
+// neighbours read them; the z neighbours' are a register window.  Bytes: read U,
+// write the residual, 80 a node.  The node-per-thread passes (gradients stored,
+// every node's primitives computed fifteen times, 75 values fetched per node
+// through the caches) took 1.17 + 0.36 ms at 192^3, this one 0.24 ms (with
+// Sutherland's law 1.52 and 0.34).  Nodes near a non-periodic end are left to
+// those passes.
 constexpr int kCX = 32, kCY = 8, kCHX = kCX + 4, kCHY = kCY + 4;
 constexpr int kCHalo = 4 * kCHX + 4 * kCY;
 static_assert(kCHalo <= kCX * kCY, "one halo position per thread");
 constexpr int kCZ = 64;       // the longest run of planes
-constexpr int kCSlots = 512;  // two blocks per CU
+// blocks that run at a time.  Runs planned for two blocks per CU with Sutherland's
+// law, which has one: 48^3 23 us, 15 as planned now; 96^3 54 and 44; 128^3 102 and
+// 89; from 192^3 on alike.
+constexpr int c_slots(bool suth) { return suth ? 256 : 512; }
 
 struct ZTiles {
     int tx, ty, nt, per, zrun;
 };
 
-inline ZTiles z_tiles(const Grid &g) {
+inline ZTiles z_tiles(const Grid &g, bool suth) {
     ZTiles T;
     T.tx = (int)((g.n[0] + kCX - 1) / kCX);
     T.ty = (int)((g.n[1] + kCY - 1) / kCY);
-    T.zrun = plane_run((int64_t)T.tx * T.ty, g.n[2], kCZ, kCSlots);
+    T.zrun = plane_run((int64_t)T.tx * T.ty, g.n[2], kCZ, c_slots(suth));
     T.nt = T.tx * T.ty * (int)((g.n[2] + T.zrun - 1) / T.zrun);
     T.per = (T.nt + kXcds - 1) / kXcds;
     return T;
@@ -416,7 +420,7 @@ __device__ __forceinline__ void cprim(const double (&u)[5], const Phys &ph, doub
 // copy of the state (Rout: that copy): 0.40 ms at 192^3, the residual and the
 // pointwise finish 0.50.
 template <bool VISC, bool SUTH, bool STEP>
-__global__ void __launch_bounds__(kCX * kCY, 2)
+__global__ void __launch_bounds__(kCX * kCY, c_slots(SUTH) / 256)
 k_c_resid_zm(const double *__restrict__ U, Grid g, Phys ph, Metrics m, double *__restrict__ Rout, ZTiles T,
              double *__restrict__ dU, RkStage rs, double dt) {
     constexpr int NV = !VISC ? 6 : (SUTH ? 8 : 7);  // values that neighbours read
@@ -793,9 +797,10 @@ inline bool zm_pays(const Grid &g, bool visc) {
 template <bool VISC, bool STEP>
 void launch_zm(const Grid &g, const Phys &ph, const Metrics &m, const double *U, double *out, double *dU, RkStage rs,
                double dt, hipStream_t s) {
-    const ZTiles Z = z_tiles(g);
+    const bool suth = VISC && ph.sutherland;
+    const ZTiles Z = z_tiles(g, suth);
     const dim3 zb((unsigned)(Z.per * kXcds)), zs(kCX, kCY);
-    if (VISC && ph.sutherland)
+    if (suth)
         hipLaunchKernelGGL((k_c_resid_zm<VISC, VISC, STEP>), zb, zs, 0, s, U, g, ph, m, out, Z, dU, rs, dt);
     else
         hipLaunchKernelGGL((k_c_resid_zm<VISC, false, STEP>), zb, zs, 0, s, U, g, ph, m, out, Z, dU, rs, dt);

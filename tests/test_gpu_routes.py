@@ -204,3 +204,19 @@ def test_central_small_bounded_grids_cost_alike():
         t.append(best_us(lambda: s.residual(R=R)))
     say("[gpu routes] central 48^3 bounded in x, z: us", t)
     assert t[0] <= 1.4 * t[1]
+
+
+def test_central_runs_of_planes_with_sutherlands_law():
+    """The z-marching pass holds one block per CU with Sutherland's law and two
+    without; its runs of planes are planned for that: on 48^3, one round of blocks
+    in either case, the law costs at most a quarter more (one value in seven more
+    to stage; runs planned for two blocks per CU take a second round)."""
+    from paper_2007_14933_amd.solver import Solver
+    t = []
+    for law in (1, 0):
+        s = Solver(central((48, 48, 48), (), 200.0, law))
+        s.apply_bc()
+        R = s.residual()
+        t.append(best_us(lambda: s.residual(R=R)))
+    say("[gpu routes] central 48^3, Sutherland's law and constant viscosity: us", t)
+    assert t[0] <= 1.25 * t[1]
