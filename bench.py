@@ -538,8 +538,10 @@ def batch_form(steps, warmup, cfl, tune, full):
              "tiles_tuned": bool(tune)}
         if tiles:
             r["tiles"] = {"%dx%d" % k: list(v) for k, v in sorted(tiles.items())}
-            r["tiles_note"] = ("per size class: [runs per tile of the lanes-along-x sweep, y segment]; "
-                               "sweep workgroups %d (0 = defaults)" % b.tune_report["sweep_blocks"])
+            r["tiles_note"] = ("per size class: [runs per tile of the lanes-along-x sweep, y segment]%s; "
+                               "workgroups per launch %d (0 = defaults)"
+                               % (" of substeps (steps of one pass per stage have tiles of their own)"
+                                  if b.one_pass else "", b.tune_report["sweep_blocks"]))
             r["tuned_vs_default"] = {"default_ms_per_step": b.tune_report["default_ms_per_step"],
                                      "tuned_ms_per_step": b.tune_report["tuned_ms_per_step"],
                                      "ratio": round(b.tune_report["default_ms_per_step"]

@@ -389,6 +389,10 @@ int osbli_batch_create(osbli_batch **batch, osbli_ctx *const *ctxs, int nprob, d
  * captured graphs.  Synchronising. */
 int osbli_batch_set_tiles(osbli_batch *batch, const int64_t *seg, void *stream);
 
+/* 1 if osbli_batch_step takes the one-pass stage, which has tiles of its own
+ * (osbli_batch_set_tiles then acts on osbli_batch_substep only), else 0. */
+int osbli_batch_one_pass(const osbli_batch *batch);
+
 /* Workgroups of each persistent sweep launch, 1..65536 (0: the defaults, 8192
  * for the one-pass stage, 2048 for the lanes-along-x sweep, 1024 for the
  * marching ones).  Results do

@@ -3,19 +3,20 @@ calls), with a tile autotuner.
 
 Every problem keeps its own context and state; one RK3 step of the whole
 ensemble is one launch of a captured graph of persistent kernels that walk a
-tile queue over all problems.  Each problem
-has its own CFL time step and end time, kept on the device.
+tile queue over all problems.  Each problem has its own CFL time step and end
+time, kept on the device.
 
     b = Batch(problems, form=1, sensor=1, weights=bits, threshold=thr)
     b.tune()          # optional: measured choice of sweep tiles per grid size
     b.run()           # until every problem reaches its end time
 
-The autotuner chooses, per grid size class, the runs per tile of the
-lanes-along-x sweep and the marching y sweep's segment length, then the
-workgroups per persistent sweep launch, by coordinate descent on the
-measured time of whole-ensemble steps, run on a scratch copy of the ensemble
-so that the real one is not advanced; results are cached per (device, form,
-sensor, grid size).
+The autotuner chooses the workgroups per persistent launch and, for forms whose
+steps run separate sweeps (the unrouted precision form; the others run one pass
+per stage, whose tiles are fixed), before that per grid size class the runs per
+tile of the lanes-along-x sweep and the marching y sweep's segment length.  It
+goes by coordinate descent on the measured time of whole-ensemble steps, run on
+a scratch copy of the ensemble so that the real one is not advanced; results are
+cached per (device, form, scheme, sensor, kind of step, grid size).
 """
 from __future__ import annotations
 
@@ -102,6 +103,7 @@ class Batch:
                                          self.t_end.ctypes.data_as(C.POINTER(C.c_double)), self.cfl,
                                          C.c_void_p(self.ws.data_ptr() + off), C.c_size_t(nb), self._s())
         B.check_batch(rc, self.b)
+        self.one_pass = bool(self.lib.osbli_batch_one_pass(self.b))  # steps, not substeps
         self.captured = False
         # x: runs per tile for rows of >= 64 interfaces (lanes-along-x sweep), else the segment
         self.tiles = np.array([[4 if p.n[0] + 1 >= 64 else default_seg(p.n[0], p.n[1]),
@@ -206,26 +208,33 @@ class Batch:
             self.capture()
 
     def tune(self, nsteps=4, cache=True, log=None):
-        """Measured choice of the launch knobs that change the ensemble's time:
-        per grid-size class, the runs per tile of the lanes-along-x sweep
-        (XL_RUNS; the marching x segment for narrow grids) and the marching y
-        sweep's segment (SEG_CANDIDATES), then the workgroups per persistent
-        sweep launch (GRID_CANDIDATES); coordinate descent on the mean time of
-        whole-ensemble steps, run on a scratch copy of the ensemble so the
-        real one does not advance.  Results are cached per (device, form,
-        sensor, size class).  Returns the choices and the default and tuned
-        milliseconds per step."""
+        """Measured choice of the launch knobs that change the time of a step.
+        Steps of one pass per stage have one, the workgroups per launch
+        (GRID_CANDIDATES; their tiles are fixed).  Steps of separate sweeps have
+        before it, per grid-size class, the runs per tile of the lanes-along-x
+        sweep (XL_RUNS; the marching x segment for narrow grids) and the
+        marching y sweep's segment (SEG_CANDIDATES).  Coordinate descent on the
+        mean time of whole-ensemble steps, run on a scratch copy of the ensemble
+        so the real one does not advance.  Results are cached per (device, form,
+        scheme, sensor, kind of step, size class); a cached choice that the final
+        timing finds slower than the defaults gives way to them.  Returns the
+        tiles and the default and tuned milliseconds per step."""
         sizes = sorted({(p.n[0], p.n[1]) for p in self.probs}, key=lambda s: -s[0] * s[1])
         dev = torch.cuda.get_device_name(self.device).replace(" ", "_")
-        key = lambda s: "v2|%s|form%d|sensor%d|%dx%d" % (dev, self.form, self.sensor, s[0], s[1])
-        gkey = "v2|%s|form%d|sensor%d|grid|%d" % (dev, self.form, self.sensor, self.P)
+        head = "v3|%s|form%d|scheme%d|sensor%d|%s|" % (dev, self.form, self.probs[0].scheme, self.sensor,
+                                                       "stage" if self.one_pass else "sweeps")
+        key = lambda s: head + "%dx%d" % s
+        gkey = head + "grid|%d" % self.P
         path = _cache_path()
         store = _cache_load(path) if cache else {}
         scratch = Batch(self.probs, form=self.form, sensor=self.sensor, weights=self.weights,
                         threshold=self.threshold, dilate=self.dilate, cfl=self.cfl,
                         t_end=np.full(self.P, 1e30), device=self.device, capture=True)
-        seg = scratch.tiles.copy()
+        seg = (self.tiles if self.one_pass else scratch.tiles).copy()
         default_ms = scratch.time_steps(nsteps)
+        if self.one_pass:
+            for i, p in enumerate(self.probs):
+                store[key((p.n[0], p.n[1]))] = [int(v) for v in seg[i]]
         todo = [s for s in sizes if key(s) not in store]
         fresh = bool(todo) or gkey not in store      # else every choice comes from the cache
         best_t = default_ms
@@ -250,7 +259,8 @@ class Batch:
                        best_t))
         for i, p in enumerate(self.probs):
             seg[i] = store[key((p.n[0], p.n[1]))]
-        scratch.set_tiles(seg)
+        if not self.one_pass:
+            scratch.set_tiles(seg)
         if gkey not in store:
             best_g, best_t = 0, scratch.time_steps(nsteps)
             for gb in GRID_CANDIDATES:
@@ -263,11 +273,13 @@ class Batch:
                 log("[tune] sweep workgroups %s, ensemble step %.3f ms" % (best_g or "default", best_t))
         # the search compares single short timings; confirm the choice against
         # the defaults with interleaved repeats (best of three each) and keep
-        # the defaults unless the choice is faster
+        # the defaults unless the choice is faster (a choice from the cache: not
+        # slower by more than such timings scatter)
         dflt = self.tiles.copy()
 
         def timed(tiles, grid):
-            scratch.set_tiles(tiles)
+            if not self.one_pass:
+                scratch.set_tiles(tiles)
             scratch.set_grid(grid)
             return scratch.time_steps(2 * nsteps)
         t_def, t_tun = [], []
@@ -275,7 +287,7 @@ class Batch:
             t_def.append(timed(dflt, 0))
             t_tun.append(timed(seg, store[gkey]))
         default_ms, tuned_ms = min(t_def), min(t_tun)
-        kept = tuned_ms < default_ms or not fresh
+        kept = tuned_ms < default_ms if fresh else tuned_ms <= 1.02 * default_ms
         if not kept:
             seg, tuned_ms = dflt, default_ms
             for s in sizes:
@@ -288,7 +300,8 @@ class Batch:
             _cache_store(path, store)
         for i, p in enumerate(self.probs):
             seg[i] = store[key((p.n[0], p.n[1]))]
-        self.set_tiles(seg)
+        if not self.one_pass:
+            self.set_tiles(seg)
         self.set_grid(store[gkey])
         self.tune_report = {"default_ms_per_step": round(default_ms, 4), "tuned_ms_per_step": round(tuned_ms, 4),
                             "sweep_blocks": int(store[gkey]), "search_kept": bool(kept)}

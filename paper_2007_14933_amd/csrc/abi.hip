@@ -1186,6 +1186,8 @@ int osbli_batch_set_tiles(osbli_batch *b, const int64_t *seg, void *stream) {
     return upload_tables(b, as_stream(stream));
 }
 
+int osbli_batch_one_pass(const osbli_batch *b) { return b && b->one_pass; }
+
 int osbli_batch_set_grid(osbli_batch *b, int sweep_blocks) {
     if (!b) return OSBLI_EINVAL;
     if (sweep_blocks < 0 || sweep_blocks > 65536) return bset_err(b, OSBLI_EINVAL, "sweep_blocks must lie in 0..65536");

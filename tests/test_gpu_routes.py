@@ -220,3 +220,46 @@ def test_central_runs_of_planes_with_sutherlands_law():
         t.append(best_us(lambda: s.residual(R=R)))
     say("[gpu routes] central 48^3, Sutherland's law and constant viscosity: us", t)
     assert t[0] <= 1.25 * t[1]
+
+
+@pytest.mark.parametrize("form", [0, 1])
+def test_tuner_searches_what_acts(form, tmp_path, monkeypatch):
+    """Steps of one pass per stage (FP64) do not depend on the sweeps' tiles: the
+    tuner leaves those alone there, and searches them for the unrouted precision
+    form; a workgroup count from a cache is not kept where it measures slower (one
+    workgroup in place of hundreds), in today's cache or in one written before the
+    step took one pass."""
+    import json
+    import torch
+    from paper_2007_14933_amd.batch import Batch
+    rng = np.random.default_rng(5)
+    probs = [I.riemann2d(n, rng, t_end=1e9) for n in (256, 192, 64)]
+    path = tmp_path / "tiles.json"
+    monkeypatch.setenv("OSBLI_TILE_CACHE", str(path))
+    dev = torch.cuda.get_device_name(0).replace(" ", "_")
+    old = {"v2|%s|form%d|sensor0|%dx%d" % (dev, form, p.n[0], p.n[1]): [4, 8] for p in probs}
+    old["v2|%s|form%d|sensor0|grid|3" % (dev, form)] = 1
+    path.write_text(json.dumps(old))
+    tried = []
+    set_tiles = Batch.set_tiles
+    monkeypatch.setattr(Batch, "set_tiles", lambda self, seg: (tried.append(np.array(seg)), set_tiles(self, seg)))
+    b = Batch(probs, form=form)
+    default = b.tiles.copy()
+    chosen = b.tune(nsteps=2)
+    assert b.sweep_blocks != 1
+    moved = [t for t in tried if not np.array_equal(np.asarray(t).reshape(default.shape), default)]
+    if form == 0:
+        assert not moved and np.array_equal(b.tiles, default)
+        assert all(tuple(chosen[(p.n[0], p.n[1])]) == tuple(t) for p, t in zip(probs, default))
+    else:
+        assert moved
+    store = json.loads(path.read_text())
+    new = [k for k in store if "|grid|" in k and k not in old]
+    assert new
+    for k in new:
+        store[k] = 1
+    path.write_text(json.dumps(store))
+    c = Batch(probs, form=form)
+    c.tune(nsteps=2)
+    assert c.sweep_blocks != 1
+    assert json.loads(path.read_text())[new[0]] != 1
