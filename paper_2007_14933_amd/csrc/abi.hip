@@ -47,9 +47,11 @@ void *resolve_scratch(int dev, hipError_t *err) {
 }
 }  // namespace
 
-// Pinned host words of the dt reduction, one slot per context out of one page
-// that lives while any context does.  A context that finds the page full or
-// not allocatable does without (it copies the device result back).
+// Pinned host words of the dt reduction, one slot per context that reduces time
+// steps, out of one page that lives while any context does.  The page is
+// allocated and freed with the contexts, a slot taken at a context's first time
+// step (the contexts of an ensemble never ask for one).  A context that finds no
+// slot, or no page, does without (it copies the device result back).
 namespace {
 constexpr int kDtSlots = 64;
 std::mutex dt_mu;
@@ -58,17 +60,23 @@ struct alignas(64) DtCell {
 };
 DtCell *dt_page = nullptr;
 uint64_t dt_used = 0;
+int64_t dt_ctxs = 0;
+
+void join_dt_page() {
+    std::lock_guard<std::mutex> lk(dt_mu);
+    ++dt_ctxs;
+    if (dt_page) return;
+    void *p = nullptr;
+    if (hipHostMalloc(&p, sizeof(DtCell) * kDtSlots, hipHostMallocPortable | hipHostMallocMapped) != hipSuccess) {
+        (void)hipGetLastError();
+        return;
+    }
+    dt_page = static_cast<DtCell *>(p);
+}
 
 DtSlot *take_dt_slot() {
     std::lock_guard<std::mutex> lk(dt_mu);
-    if (!dt_page) {
-        void *p = nullptr;
-        if (hipHostMalloc(&p, sizeof(DtCell) * kDtSlots, hipHostMallocPortable | hipHostMallocMapped) != hipSuccess) {
-            (void)hipGetLastError();
-            return nullptr;
-        }
-        dt_page = static_cast<DtCell *>(p);
-    }
+    if (!dt_page) return nullptr;
     for (int k = 0; k < kDtSlots; ++k)
         if (!((dt_used >> k) & 1)) {
             dt_used |= uint64_t(1) << k;
@@ -78,14 +86,12 @@ DtSlot *take_dt_slot() {
     return nullptr;
 }
 
-void give_dt_slot(DtSlot *s) {
-    if (!s) return;
+void leave_dt_page(DtSlot *s) {
     std::lock_guard<std::mutex> lk(dt_mu);
-    dt_used &= ~(uint64_t(1) << (reinterpret_cast<DtCell *>(s) - dt_page));
-    if (dt_used == 0) {
-        (void)hipHostFree(dt_page);
-        dt_page = nullptr;
-    }
+    if (s) dt_used &= ~(uint64_t(1) << (reinterpret_cast<DtCell *>(s) - dt_page));
+    if (--dt_ctxs > 0 || !dt_page) return;
+    (void)hipHostFree(dt_page);
+    dt_page = nullptr;
 }
 }  // namespace
 
@@ -125,7 +131,8 @@ struct osbli_ctx {
     double rkA[5], rkB[5]; // their 2N coefficients
     void *cwork;           // central path: the store-all strategy's work arrays (null: StoreSome)
     double *W[2];          // state copies of whole steps (null: separate passes)
-    DtSlot *dt_slot;       // the dt reduction's host words (null: copy back)
+    DtSlot *dt_slot;       // the dt reduction's host words (null: none taken)
+    int dt_joined;
     unsigned long long dt_seq;
     char err[320];
 };
@@ -517,7 +524,8 @@ int osbli_init_grid(osbli_ctx **out, const osbli_params *p, const double *x, con
     // the allocation-free substep's scratch on this device (a failure here
     // only disables that entry point)
     c->scratch = static_cast<char *>(resolve_scratch(c->device, &c->scratch_err));
-    c->dt_slot = take_dt_slot();
+    join_dt_page();
+    c->dt_joined = 1;
     hipStream_t s = as_stream(stream);
     c->last = s;
     c->ws = static_cast<char *>(workspace);
@@ -767,6 +775,7 @@ int osbli_compute_dt(osbli_ctx *c, const double *U, double cfl, double *dt_out, 
     if (!c || !U || !dt_out) return set_err(c, OSBLI_EINVAL, "null argument");
     hipStream_t s = as_stream(stream);
     c->last = s;
+    if (!c->dt_slot) c->dt_slot = take_dt_slot();
     const unsigned long long seq = ++c->dt_seq;
     {
         Timed t(c, OSBLI_K_DT, s);
@@ -956,7 +965,7 @@ void osbli_destroy(osbli_ctx *c) {
     if (!c) return;
     resolve_profile(c);
     for (hipEvent_t e : c->prof.pool) hipEventDestroy(e);
-    give_dt_slot(c->dt_slot);
+    if (c->dt_joined) leave_dt_page(c->dt_slot);
     delete c;
 }
 

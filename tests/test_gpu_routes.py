@@ -263,3 +263,61 @@ def test_tuner_searches_what_acts(form, tmp_path, monkeypatch):
     c.tune(nsteps=2)
     assert c.sweep_blocks != 1
     assert json.loads(path.read_text())[new[0]] != 1
+
+
+def test_time_step_beside_idle_contexts():
+    """Contexts that never ask for a time step (an ensemble's) do not slow down one
+    that does: the reduction returns through pinned words, of which 64 contexts at
+    a time have some (else by a copy and a synchronisation, twice the time)."""
+    import gc
+    import time
+    from paper_2007_14933_amd.solver import Solver
+
+    def best(s, reps=200, rounds=8):
+        s.compute_dt(0.5)
+        out = float("inf")
+        for _ in range(rounds):
+            t = time.perf_counter()
+            for _ in range(reps):
+                s.compute_dt(0.5)
+            out = min(out, (time.perf_counter() - t) / reps)
+        return 1e6 * out
+    gc.collect()
+    first = Solver(I.sod(100))
+    first.apply_bc()
+    alone = best(first)
+    idle = [Solver(I.sod(20)) for _ in range(70)]
+    s = Solver(I.sod(100))
+    s.apply_bc()
+    beside = best(s)
+    say("[gpu routes] time step alone, beside %d contexts: us" % len(idle), alone, beside)
+    assert beside <= 1.5 * alone
+
+
+def test_time_steps_of_more_contexts_than_slots():
+    """Every context gets its own right time step, with pinned words or without (70
+    at once), in any order, and again once the first ones are gone."""
+    import gc
+    from paper_2007_14933_amd.solver import Solver
+    gc.collect()
+    probs = [I.smooth_random(1, (40 + k, 1, 1), seed=k, amp=0.2) for k in range(70)]
+    ss = [Solver(p) for p in probs]
+    for s in ss:
+        s.apply_bc()
+    want = []
+    for s in ss:
+        U = s.interior()[:, 0, 0]
+        u = U[1] / U[0]
+        a = np.sqrt(1.4 * 0.4 * (U[2] - 0.5 * U[0] * u * u) / U[0])
+        want.append(0.5 / ((np.abs(u) + a) * s.prob.n[0]).max())
+    for order in (range(70), range(69, -1, -1)):
+        for k in order:
+            assert abs(ss[k].compute_dt(0.5) - want[k]) <= 1e-12 * want[k], k
+    del ss[:40]
+    del s
+    gc.collect()
+    late = Solver(probs[0])
+    late.apply_bc()
+    assert abs(late.compute_dt(0.5) - want[0]) <= 1e-12 * want[0]
+    for k in range(30):
+        assert abs(ss[k].compute_dt(0.5) - want[40 + k]) <= 1e-12 * want[40 + k]
