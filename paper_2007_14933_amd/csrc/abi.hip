@@ -62,10 +62,19 @@ DtCell *dt_page = nullptr;
 uint64_t dt_used = 0;
 int64_t dt_ctxs = 0;
 
+// allocations beside a graph capture of some other stream of this thread or
+// another one (a solver may be collected while one runs) leave it valid
+struct CaptureAside {
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    CaptureAside() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+    ~CaptureAside() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+};
+
 void join_dt_page() {
     std::lock_guard<std::mutex> lk(dt_mu);
     ++dt_ctxs;
     if (dt_page) return;
+    CaptureAside aside;
     void *p = nullptr;
     if (hipHostMalloc(&p, sizeof(DtCell) * kDtSlots, hipHostMallocPortable | hipHostMallocMapped) != hipSuccess) {
         (void)hipGetLastError();
@@ -90,6 +99,7 @@ void leave_dt_page(DtSlot *s) {
     std::lock_guard<std::mutex> lk(dt_mu);
     if (s) dt_used &= ~(uint64_t(1) << (reinterpret_cast<DtCell *>(s) - dt_page));
     if (--dt_ctxs > 0 || !dt_page) return;
+    CaptureAside aside;
     (void)hipHostFree(dt_page);
     dt_page = nullptr;
 }

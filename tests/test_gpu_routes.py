@@ -321,3 +321,30 @@ def test_time_steps_of_more_contexts_than_slots():
     assert abs(late.compute_dt(0.5) - want[0]) <= 1e-12 * want[0]
     for k in range(30):
         assert abs(ss[k].compute_dt(0.5) - want[40 + k]) <= 1e-12 * want[40 + k]
+
+
+def test_solver_dropped_during_a_capture():
+    """A solver collected while some other stream captures a graph (the last one: its
+    context frees the page of pinned words) leaves the capture valid."""
+    import gc
+    import torch
+    from paper_2007_14933_amd.solver import Solver
+    gc.collect()
+    s = Solver(I.sod(50))
+    s.apply_bc()
+    s.compute_dt(0.5)
+    x = torch.zeros(1000, device="cuda:0")
+    stream, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph, stream=stream):
+        x.add_(1.0)
+        del s
+        gc.collect()
+        x.add_(1.0)
+    for k in range(3):
+        graph.replay()
+        torch.cuda.synchronize()
+        assert float(x.min()) == float(x.max()) == 2.0 * (k + 1)
+    t = Solver(I.sod(50))
+    t.apply_bc()
+    assert t.compute_dt(0.5) > 0.0
