@@ -116,15 +116,25 @@ __device__ __forceinline__ double lin5(const R5 &r) {
 // only up to a common factor, so nothing is divided by prod(e): WENO-Z takes
 // alpha_r = d_r (D^2 + (tau prod_{s != r} e_s)^2) with D = e0 e1 e2, TENO's test
 // c_r ~ (e_r + tau) prod_{s != r} e_s, brought near one (the sixth powers stay
-// in range) by the bare hardware estimate of 1/D.
-template <int SCHEME>
+// in range) by the bare hardware estimate of 1/D.  WENO-Z's sixth powers take
+// indicators up to 1e51 (flux jumps of 1e25 of the characteristic variables); WIDE
+// divides by D and takes them to 1e102, as lanes along x in one dimension always
+// did (in more, the marching sweeps share the smaller range).
+template <int SCHEME, bool WIDE>
 __device__ __forceinline__ double recon5_gen(const R5 &r, const Phys &ph, bool *kept) {
     const double q0 = r.f0 + (2.0 / 3.0) * r.d3 - (1.0 / 6.0) * r.d4;
     const double q1 = r.f0 + (1.0 / 6.0) * r.d2 + (1.0 / 3.0) * r.d3;
     const double q2 = r.f0 - (1.0 / 3.0) * r.d1 + (5.0 / 6.0) * r.d2;
     const double e0 = r.b0 + ph.eps34, e1 = r.b1 + ph.eps34, e2 = r.b2 + ph.eps34;
     const double e01 = e0 * e1, e02 = e0 * e2, e12 = e1 * e2;
-    if (SCHEME == OSBLI_WENOZ5) {
+    if (SCHEME == OSBLI_WENOZ5 && WIDE) {
+        const double t = r.tau * rcp64(e01 * e2);
+        const double x0 = e12 * t, x1 = e02 * t, x2 = e01 * t;
+        const double a0 = 0.3 * (1.0 + x0 * x0);
+        const double a1 = 0.6 * (1.0 + x1 * x1);
+        const double a2 = 0.1 * (1.0 + x2 * x2);
+        return (a0 * q0 + a1 * q1 + a2 * q2) * rcp64(a0 + a1 + a2);
+    } else if (SCHEME == OSBLI_WENOZ5) {
         const double D = e01 * e2, D2 = D * D;
         const double y0 = r.tau * e12, y1 = r.tau * e02, y2 = r.tau * e01;
         const double a0 = 0.3 * (D2 + y0 * y0);
@@ -288,7 +298,7 @@ __device__ __forceinline__ double recon7_z(double fm3, double fm2, double fm1, d
 // field; it keeps both sides' indicators live, which the marching sweeps can
 // afford and the lane-per-interface sweep cannot (it spills), so that one
 // branches per side.
-template <int SCHEME, bool JOINT, int W>
+template <int SCHEME, bool JOINT, int W, bool WIDE>
 __device__ __forceinline__ double split_recon(const double (&V)[W], const double (&gh)[W], double ha,
                                               const Phys &ph, bool *kept = nullptr) {
     double gp[W], gm[W];
@@ -313,11 +323,11 @@ __device__ __forceinline__ double split_recon(const double (&V)[W], const double
         const R5 a = recon5_ind(gp[0], gp[1], gp[2], gp[3], gp[4]);
         const R5 b = recon5_ind(gm[5], gm[4], gm[3], gm[2], gm[1]);
         if (SCHEME == OSBLI_TENO5 && (teno5_all_kept(a, ph) & teno5_all_kept(b, ph))) return lin5(a) + lin5(b);
-        return recon5_gen<SCHEME>(a, ph, kept) + recon5_gen<SCHEME>(b, ph, kept);
+        return recon5_gen<SCHEME, WIDE>(a, ph, kept) + recon5_gen<SCHEME, WIDE>(b, ph, kept);
     } else {
         auto side = [&](const R5 &r) -> double {
             if (SCHEME == OSBLI_TENO5 && teno5_all_kept(r, ph)) return lin5(r);
-            return recon5_gen<SCHEME>(r, ph, kept);
+            return recon5_gen<SCHEME, WIDE>(r, ph, kept);
         };
         const double ha5 = side(recon5_ind(gp[0], gp[1], gp[2], gp[3], gp[4]));
         return ha5 + side(recon5_ind(gm[5], gm[4], gm[3], gm[2], gm[1]));
@@ -333,6 +343,7 @@ __device__ __forceinline__ void char_flux_sides(const Loc<ND> (&P)[W], const Sid
                                                 const Phys &ph, double &Fr, double &Fn, double (&Ft)[2], double &FE,
                                                 bool *kept = nullptr) {
     constexpr int NT = ND - 1;  // tangents
+    constexpr bool WIDE = ND == 1 && !JOINT;
     // averaged state at the half node (Roe, or arithmetic mean with unit weights)
     const double sl = SL.s, sr = SR.s;
     const double iw = rcp64(sl + sr);
@@ -379,21 +390,21 @@ __device__ __forceinline__ void char_flux_sides(const Loc<ND> (&P)[W], const Sid
         V[k] = A[k] + B[k];
         gh[k] = hu[k] * V[k] + P[k].p * (hb * hu[k] - cm);
     }
-    const double h0 = split_recon<SCHEME, JOINT, W>(V, gh, 0.5 * aminus, ph, kept);
+    const double h0 = split_recon<SCHEME, JOINT, W, WIDE>(V, gh, 0.5 * aminus, ph, kept);
     // field u_n + a
 #pragma unroll
     for (int k = 0; k < W; ++k) {
         V[k] = A[k] - B[k];
         gh[k] = hu[k] * V[k] + P[k].p * (hb * hu[k] - cp);
     }
-    const double h4 = split_recon<SCHEME, JOINT, W>(V, gh, 0.5 * aplus, ph, kept);
+    const double h4 = split_recon<SCHEME, JOINT, W, WIDE>(V, gh, 0.5 * aplus, ph, kept);
     // entropy field: V = rho - b (K rho - u.m + E), g = u_n V + p b (un - u_n)
 #pragma unroll
     for (int k = 0; k < W; ++k) {
         V[k] = P[k].r - 2.0 * A[k];
         gh[k] = hu[k] * V[k] + P[k].p * (hbun - b * hu[k]);
     }
-    const double h1 = split_recon<SCHEME, JOINT, W>(V, gh, a0, ph, kept);
+    const double h1 = split_recon<SCHEME, JOINT, W, WIDE>(V, gh, a0, ph, kept);
     // shear fields: V = m_t - ut rho, g = u_n V
     double ht[2] = {0.0, 0.0};
 #pragma unroll
@@ -403,7 +414,7 @@ __device__ __forceinline__ void char_flux_sides(const Loc<ND> (&P)[W], const Sid
             V[k] = P[k].mt[s] - ut[s] * P[k].r;
             gh[k] = hu[k] * V[k];
         }
-        ht[s] = split_recon<SCHEME, JOINT, W>(V, gh, a0, ph, kept);
+        ht[s] = split_recon<SCHEME, JOINT, W, WIDE>(V, gh, a0, ph, kept);
     }
     // back to physical space: F = R ghat
     const double hs = h0 + h1 + h4;

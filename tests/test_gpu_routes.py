@@ -348,3 +348,34 @@ def test_solver_dropped_during_a_capture():
     t = Solver(I.sod(50))
     t.apply_bc()
     assert t.compute_dt(0.5) > 0.0
+
+
+@pytest.mark.parametrize("scheme", ["WENOZ5", "TENO5"])
+def test_shock_tube_in_large_units(scheme):
+    """The shock tube with its unit of time 2^90 times as long (speeds of 1e27, so
+    that indicators reach 1e54 and their products 1e162): five steps against the
+    oracle at the run bound 1e-11, by whole steps and by separate calls."""
+    from parity_util import normwise_rel, oracle_run
+    from paper_2007_14933_amd.solver import Solver
+    k = 2.0 ** 90
+    prob = I.sod(100).with_(scheme=getattr(I, scheme))
+    U0 = prob.U0.copy()
+    U0[1] *= k
+    U0[2] *= k * k
+    prob = prob.with_(U0=U0)
+    Uo, to = oracle_run(prob, 5)
+    assert np.isfinite(Uo).all()
+    for whole in (True, False):
+        s = Solver(prob)
+        s.apply_bc()
+        for _ in range(5):
+            dt = s.compute_dt(0.5)
+            if whole:
+                s.step(dt)
+            else:
+                for st in range(3):
+                    s.substep(st, dt)
+                    s.apply_bc()
+        err = normwise_rel(I.interior_view(1, s.state()), I.interior_view(1, Uo))
+        say("[gpu routes] tube in large units", scheme, whole, err)
+        assert err.max() <= 1e-11, err
