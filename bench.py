@@ -281,6 +281,13 @@ def form_error(prob, form, steps, cfl):
     return res
 
 
+def sweep_times(prof, axes="xyz"):
+    """(sweeps, their total ms): one direction each; a launch of two directions
+    (y and z of a small grid) and the one-pass stage of 2D problems count as two."""
+    n = sum(prof["sweep_%s" % a][0] for a in axes) + 2 * (prof["sweep_yz"][0] + prof["stage"][0])
+    return n, sum(prof["sweep_%s" % a][1] for a in axes) + prof["sweep_yz"][1] + prof["stage"][1]
+
+
 def sweep_valu_frac(prob, sweep_ms, launches):
     """Effective rate of the convective sweeps against the FP64 vector peak
     (the precision form's FP32 runs at the same rate: packed FP32 is not
@@ -311,7 +318,8 @@ def tgv_learned(prob, args, plain_value, plain_extra):
         w, _, p, ex = timed_run(prob, form, args.steps, args.warmup, args.cfl, sensor=1, bits=bits, thr=thr,
                                 keep_rho=True, dilate=dil)
         v = npts * 3 * args.steps / w / 1e6
-        sw = sum(p["sweep_%s" % a][1] for a in "xyz") / max(1, sum(p["sweep_%s" % a][0] for a in "xyz"))
+        cnt, ms = sweep_times(p)
+        sw = ms / max(1, cnt)
         res[name] = {"value": round(v, 3), "speedup_vs_plain": round(v / plain_value, 3),
                      "sweep_avg_ms": round(sw, 4), "valu_frac_effective": sweep_valu_frac(prob, sw, 1),
                      "sensor_ms_per_step": round(p["sensor"][1] / max(1, args.steps), 4),
@@ -402,9 +410,7 @@ def sensor_form(cfl):
         prof = s.profile_read()
         rho = s.interior()[0]
         v = npts * 3 * s.nsteps_done / wall / 1e6
-        # the one-pass stage evaluates both directions (and updates)
-        sweeps = sum(prof["sweep_%s" % a][1] for a in "xy") + prof["stage"][1]
-        groups = sum(prof["sweep_%s" % a][0] for a in "xy") + 2 * prof["stage"][0]
+        groups, sweeps = sweep_times(prof, "xy")
         r = {"value": round(v, 3), "steps": s.nsteps_done, "t_end": round(s.t, 6),
              "gpu_ms": round(ev0.elapsed_time(ev1), 3), "sweep_ms": round(sweeps, 3),
              "valu_frac_effective": sweep_valu_frac(prob, sweeps, groups),
@@ -442,7 +448,8 @@ def schemes_form(steps, warmup, cfl, n=256):
         prob = inputs.tgv(n).with_(**kw)
         nst = inputs.rk_stages(prob.rk)
         wall, _, prof, _ = timed_run(prob, 0, steps, warmup, cfl)
-        sw = sum(prof["sweep_%s" % a][1] for a in "xyz") / max(1, sum(prof["sweep_%s" % a][0] for a in "xyz"))
+        cnt, ms = sweep_times(prof)
+        sw = ms / max(1, cnt)
         out[name] = {"value": round(n ** 3 * nst * steps / wall / 1e6, 3), "ms_per_step": round(wall * 1e3 / steps, 4),
                      "substages_per_step": nst, "sweep_avg_ms": round(sw, 4)}
     out["workload"] = "TGV %d^3 periodic, Re=1600, M=0.1, viscous, CFL 0.5, FP64; %d timed steps" % (n, steps)
@@ -609,8 +616,7 @@ def main():
     value = npts * 3 * args.steps / wall / 1e6
 
     # dominant kernel: the convective sweeps (one launch per direction and substage)
-    sweep_cnt = sum(prof["sweep_%s" % a][0] for a in "xyz")
-    sweep_ms = sum(prof["sweep_%s" % a][1] for a in "xyz")
+    sweep_cnt, sweep_ms = sweep_times(prof)
     fl_if = cost.flops_per_interface(3, prob.scheme)
     fl_launch = fl_if * sum(cost.interfaces_per_sweep(prob.n, 3, d) for d in range(3)) / 3.0
     avg_ms = sweep_ms / max(1, sweep_cnt)
@@ -663,7 +669,8 @@ def main():
         log("precision form on TGV")
         wm, _, pm, _ = timed_run(prob, 1, args.steps, args.warmup, args.cfl)
         vm = npts * 3 * args.steps / wm / 1e6
-        sm = sum(pm["sweep_%s" % a][1] for a in "xyz") / max(1, sum(pm["sweep_%s" % a][0] for a in "xyz"))
+        cnt, ms = sweep_times(pm)
+        sm = ms / max(1, cnt)
         out["forms"] = {"mixed_fp32": {
             "value": round(vm, 3), "speedup_vs_fp64": round(vm / value, 3),
             "sweep_avg_ms": round(sm, 4), "valu_frac_effective": sweep_valu_frac(prob, sm, 1),

@@ -439,7 +439,8 @@ enum osbli_kernel_class {
     OSBLI_K_SENSOR = 7,    /* learned-sensor routing masks */
     OSBLI_K_CENTRAL = 8,   /* central path: derivative and residual passes */
     OSBLI_K_STAGE = 9,     /* one-pass stage of osbli_rk_step: fluxes, update, BCs */
-    OSBLI_K_COUNT = 10
+    OSBLI_K_SWEEP_YZ = 10, /* y and z sweeps of a small 3D grid in one launch (not under 1 and 2) */
+    OSBLI_K_COUNT = 11
 };
 
 /* Instrumentation (not part of the method): when enabled, each launch group

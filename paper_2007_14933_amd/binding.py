@@ -93,9 +93,10 @@ _SIGS = {
     "osbli_batch_destroy": (None, [_VP]),
 }
 
-K_SWEEP_X, K_SWEEP_Y, K_SWEEP_Z, K_VISC_FLUX, K_FINISH, K_BC, K_DT, K_SENSOR, K_CENTRAL, K_STAGE = range(10)
+K_SWEEP_X, K_SWEEP_Y, K_SWEEP_Z, K_VISC_FLUX, K_FINISH, K_BC, K_DT, K_SENSOR, K_CENTRAL, K_STAGE, \
+    K_SWEEP_YZ = range(11)
 K_NAMES = ["sweep_x", "sweep_y", "sweep_z", "visc_flux", "finish", "bc", "dt", "sensor", "central",
-           "stage"]
+           "stage", "sweep_yz"]
 
 
 def load():

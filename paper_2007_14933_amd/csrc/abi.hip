@@ -462,7 +462,7 @@ hipError_t convective_all(osbli_ctx *c, const double *U, double *R, double *Z, h
     const bool route = c->p.sensor && c->sensor_ready;
     for (int d = 0; d < c->g.nd; ++d) {
         if (Z && d == 1) {
-            Timed t(c, OSBLI_K_SWEEP_Y, s);
+            Timed t(c, OSBLI_K_SWEEP_YZ, s);
             return launch_convective_yz(c->g, c->ph, c->m, U, R, Z, c->flags, route ? c->mask[1] : nullptr,
                                         route ? c->mask[2] : nullptr, c->seg, s);
         }

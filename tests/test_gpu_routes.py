@@ -379,3 +379,24 @@ def test_shock_tube_in_large_units(scheme):
         err = normwise_rel(I.interior_view(1, s.state()), I.interior_view(1, Uo))
         say("[gpu routes] tube in large units", scheme, whole, err)
         assert err.max() <= 1e-11, err
+
+
+@pytest.mark.parametrize("n", [(40, 40, 40), (128, 130, 128)])
+def test_profile_counts_every_sweep(n):
+    """The profile of a 3D step accounts for three directions per substage: a launch
+    of y and z together (small grids) is a class of its own, counted as two."""
+    import sys
+    import os
+    sys.path.insert(0, os.path.dirname(os.path.dirname(os.path.abspath(__file__))))
+    import bench
+    from paper_2007_14933_amd.solver import Solver
+    s = Solver(I.smooth_random(3, n, seed=1, Re=200.0))
+    s.apply_bc()
+    s.profile()
+    s.step(1e-4)
+    p = s.profile_read()
+    sweeps, ms = bench.sweep_times(p)
+    assert sweeps == 9 and ms > 0.0
+    together = p["sweep_yz"][0]
+    assert together in (0, 3) and (together == 3) == (n[0] == 40)
+    assert p["sweep_y"][0] == p["sweep_z"][0] == 3 - together
