@@ -400,3 +400,45 @@ def test_profile_counts_every_sweep(n):
     together = p["sweep_yz"][0]
     assert together in (0, 3) and (together == 3) == (n[0] == 40)
     assert p["sweep_y"][0] == p["sweep_z"][0] == 3 - together
+
+
+@pytest.mark.parametrize("form,every", [(0, 0), (1, 0), (0, 1), (1, 1)])
+@pytest.mark.parametrize("n", [(33, 31, 40), (70, 40, 37)])
+def test_routed_3d_steps(n, form, every):
+    """Learned routing in whole 3D steps (y and z sweeps in one launch), FP64 and
+    precision form, masks refreshed per step or substage: one step against the
+    separate calls.  FP64: 1e-13 of the component's largest value.  Precision form:
+    a last bit of the FP64 state moves a deviation by one FP32 rounding, 2^-24 of
+    it, which a step weighs by its CFL number: 2^-24 of that value."""
+    prob = I.smooth_random(3, n, seed=n[0], amp=0.2, Re=200.0)
+    net = routing_net(prob)
+    for dilate in (0, 2):
+        a, b = step_and_separate(prob, 1, net, dilate, every, form=form, sensor=1)
+        scale = b.U.abs().amax(dim=(1, 2, 3), keepdim=True)
+        err = float(((a.U - b.U).abs() / scale).max())
+        say("[gpu routes] routed 3D", n, "form", form, "every", every, "dilate", dilate, err)
+        assert err <= (1e-13 if form == 0 else 2.0 ** -24)
+
+
+@pytest.mark.parametrize("n", [(40, 33, 20), (50, 61)])
+def test_march_segments_on_wavy_meshes(n):
+    """Segments of the marching sweeps where the metrics vary (the x sweep's staged
+    area vectors among them): every length gives the bits of one segment per line,
+    and those are the oracle's residual to the parity bound."""
+    import torch
+    from oracle import oracle as O
+    from paper_2007_14933_amd.solver import Solver
+    from parity_util import flux_scale
+    prob = wavy(I.smooth_random(len(n), n + (1,) * (3 - len(n)), seed=9, amp=0.2))
+    s = Solver(prob)
+    s.apply_bc()
+    s.set_sweep_segments([200, 200, 200])
+    ref = s.residual().clone()
+    for seg in (1, 2, 3, 5, 16):
+        s.set_sweep_segments([seg, seg, seg])
+        assert torch.equal(s.residual(), ref), seg
+    U = O.apply_bc(prob, prob.U0.copy())
+    S, J = O.metrics(prob)
+    err = np.abs(ref.cpu().numpy() - O.residual(prob, S, J, U)).max(axis=(1, 2, 3)) / flux_scale(prob, U, J, S)
+    say("[gpu routes] wavy march", n, err)
+    assert err.max() <= 1e-13, err
