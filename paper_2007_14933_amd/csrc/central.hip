@@ -363,9 +363,9 @@ k_c_resid(const double *__restrict__ U, const double *__restrict__ Gs, Grid g, P
 // neighbours read them; the z neighbours' are a register window.  Bytes: read U,
 // write the residual, 80 a node.  The node-per-thread passes (gradients stored,
 // every node's primitives computed fifteen times, 75 values fetched per node
-// through the caches) took 1.17 + 0.36 ms at 192^3, this one 0.24 ms (with
-// Sutherland's law 1.52 and 0.34).  Nodes near a non-periodic end are left to
-// those passes.
+// through the caches) took 1.17 + 0.36 ms at 192^3, this one 0.29 ms (with
+// Sutherland's law, which cost them no more, 0.38).  Nodes near a non-periodic end
+// are left to those passes.
 constexpr int kCX = 32, kCY = 8, kCHX = kCX + 4, kCHY = kCY + 4;
 constexpr int kCHalo = 4 * kCHX + 4 * kCY;
 static_assert(kCHalo <= kCX * kCY, "one halo position per thread");
@@ -418,7 +418,8 @@ __device__ __forceinline__ void cprim(const double (&u)[5], const Phys &ph, doub
 
 // STEP: the node's Runge-Kutta update instead of its residual, into another
 // copy of the state (Rout: that copy): 0.40 ms at 192^3, the residual and the
-// pointwise finish 0.50.
+// pointwise finish 0.29 + 0.21 (Sutherland's law 0.49).  With constant viscosity it
+// spills 17 registers (the residual form 10) to have two blocks on a CU.
 template <bool VISC, bool SUTH, bool STEP>
 __global__ void __launch_bounds__(kCX * kCY, c_slots(SUTH) / 256)
 k_c_resid_zm(const double *__restrict__ U, Grid g, Phys ph, Metrics m, double *__restrict__ Rout, ZTiles T,

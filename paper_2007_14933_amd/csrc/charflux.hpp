@@ -71,12 +71,14 @@ __device__ __forceinline__ void finish_point(const Phys &ph, Pt<ND> &w, bool &ba
 // outer difference; the coefficients are exact), ten operations where second
 // differences and their combinations take fifteen.  Every e_r below is
 // (3/4)(beta_r + eps), which leaves all ratios tau / (beta_r + eps) unchanged.
-// The sweeps are bound by FP64 issue (84 % of the cycles, at a clock that the
-// power limit holds near 2 GHz), so operations are their time: with these
-// forms, the linear value on the differences, weights without a division by
-// prod(e) and both sides tested in one branch, 1020 -> 905 VALU instructions
-// per interface of a 256^3 Taylor-Green box with small disturbances, y and z
-// sweeps 0.637 -> 0.577 ms, x 0.692 -> 0.665 ms.
+// The sweeps are bound by FP64 issue (VALU busy two thirds of the time at the
+// nominal clock of 2.4 GHz), so operations are their time: with these forms, the
+// linear value on the differences, weights without a division by prod(e), both
+// sides tested in one branch and the left node's Side carried along the march
+// (which gave nothing that could be measured by itself), 1061 -> 998 VALU
+// instructions per interface along x, 886 -> 752 along y and 876 -> 740 along z on
+// the 256^3 Taylor-Green vortex; with small disturbances of it, where stencils
+// are cut, y and z sweeps 0.637 -> 0.577 ms, x 0.692 -> 0.665 ms.
 constexpr double kP = 39.0 / 64.0;
 
 struct R5 {

@@ -456,10 +456,8 @@ __device__ __forceinline__ void sweep_block(const double *__restrict__ U, double
     }
 }
 
-// One wave per SIMD for general meshes and for the mixed-precision routed
-// variant (both flux paths plus the FP64 reference in one loop): at two
-// waves they spill, which cost more (1.29 vs 0.93 ms at 256^3) than the
-// lost occupancy.
+// One wave per SIMD for general meshes: at two they spill 40 to 72 registers,
+// which costs more (y of 97 x 80 x 101 73 -> 122 us) than the lost occupancy.
 template <int ND, int DIR, int SCHEME, bool GEN, bool MIX, bool ROUTE>
 __global__ void __launch_bounds__(64 * kWaves, GEN ? 1 : 2)
 k_sweep(const double *__restrict__ U, double *__restrict__ R, Grid g, Phys ph, Metrics m, int64_t seg,
@@ -681,9 +679,9 @@ __device__ __forceinline__ void sweep_x_lanes(const double *__restrict__ U, doub
 
 // three waves per SIMD (168 registers); TENO6's four stencils spill there,
 // so it runs at two (180 registers, x sweep 0.87 -> 0.86 ms at 256^3), and so
-// does the FP64 form on general 3D meshes (196 registers)
+// do general 3D meshes (196 registers)
 template <int ND, int SCHEME, bool GEN, bool MIX, bool ROUTE>
-__global__ void __launch_bounds__(64 * kWaves, SCHEME == OSBLI_TENO6 || (GEN && ND == 3 && !MIX) ? 2 : 3)
+__global__ void __launch_bounds__(64 * kWaves, SCHEME == OSBLI_TENO6 || (GEN && ND == 3) ? 2 : 3)
 k_sweep_xl(const double *__restrict__ U, double *__restrict__ R, Grid g, Phys ph, Metrics m, int64_t totalJ,
            int first, unsigned *flags, const uint8_t *__restrict__ mask) {
     __shared__ XlLds<ND, GEN> sm[kWaves];
