@@ -147,7 +147,8 @@ typedef struct osbli_params {
     int32_t scheme;            /* enum osbli_scheme */
     double Ts_over_Tref;       /* Sutherland constant T_s / T_ref */
     double teno_CT;            /* TENO cut-off C_T */
-    double eps;                /* epsilon of the nonlinear weights (1e-16; accepted range [1e-40, 1]) */
+    double eps;                /* epsilon of the nonlinear weights (1e-16; accepted range [1e-40, 1]); WENO-Z5's
+                                * weights take smoothness indicators up to 1e51 (1D rows of 63 nodes and more 1e102) */
     int32_t roe_avg;           /* 1: Roe average, 0: arithmetic mean of u, H */
     int32_t form;              /* enum osbli_form */
     int32_t sensor;            /* 1: learned-sensor routing (TENO5, separable mesh) */
@@ -200,7 +201,9 @@ int osbli_rk_substep(osbli_ctx *ctx, int stage, double dt, double *U, double *dU
 
 /* One whole Runge-Kutta step: every stage in order, each followed by the
  * boundary conditions (the state afterwards is that of osbli_rk_substep and
- * osbli_apply_bc stage by stage, to rounding).  U's ghosts must be valid.
+ * osbli_apply_bc stage by stage: bit for bit with one launch per stage, else to
+ * rounding, which the precision form's FP32 deviations carry to 2^-24 of a step's
+ * change).  U's ghosts must be valid.
  * Inviscid 1D and 2D problems on separable meshes with periodic or
  * extrapolated ends (six-point schemes; FP64 or routed forms; at most 2^24
  * nodes) take one launch per stage through two state copies in the workspace.
