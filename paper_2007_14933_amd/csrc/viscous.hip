@@ -529,7 +529,7 @@ k_finish_zm(const double *__restrict__ Racc, const double *__restrict__ G, Grid 
 // has its state copies, so neighbours still read the old state), for grids
 // that are periodic along z.  The two passes above write nine flux arrays and
 // read them back with their neighbours, 18 of the 48 values a node costs them;
-// here a node's fluxes never leave the CU.  256^3: 0.99 to 1.05 ms from box to box
+// here a node's fluxes never leave the CU.  256^3: 0.99 to 1.05 ms from card to card
 // (0.42 + 0.89), 192^3 0.41 (0.58), 96^3 0.059 (0.076), 512 x 256 x 256 with a wall
 // and Sutherland's law 2.13 (2.87), 64^3 and below as before or a little faster.
 // Bounded along x or y alone 256^3 takes 0.05 ms more; along both the kernel spills
